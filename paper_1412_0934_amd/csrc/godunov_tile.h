@@ -94,6 +94,20 @@ __device__ __forceinline__ void load5(const T *__restrict__ p, int64_t vstride, 
     for (int q = 0; q < 5; ++q) U[q] = p[q * vstride];
 }
 
+// The five variables of a cell whose plane is the same for every lane (p, a
+// scalar) and whose place in the plane is a byte offset of its own. A plane
+// holds at most (16384 + 128)^2 cells, so the offset fits 32 bits, and the
+// loads take a scalar base and a 32-bit vector offset: no vector address
+// arithmetic.
+template <typename T>
+__device__ __forceinline__ void load5_plane(const T *__restrict__ p, int64_t vstride, uint32_t at,
+                                            T U[5])
+{
+#pragma unroll
+    for (int q = 0; q < 5; ++q)
+        U[q] = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p + q * vstride) + at);
+}
+
 // ------------------------------------------------------------ CFL reduction
 
 // |u| + |v| + |w| + 3c of a conserved state, c = sqrt(g p / rho) evaluated as
@@ -106,7 +120,7 @@ __device__ __forceinline__ double cell_signal(const T U[5], const Phys<T> &ph, i
     prim_from_cons(U, W, inv, ph, hits);
     T gp = ph.gamma * W[4];
     T c = gp * fast_rsqrt(gp * W[0]);
-    return (double)(fabs(W[1]) + fabs(W[2]) + fabs(W[3]) + T(3) * c);
+    return (double)fma(T(3), c, fabs(W[1]) + fabs(W[2]) + fabs(W[3]));
 }
 
 __device__ __forceinline__ double wave_max(double v)
@@ -145,28 +159,39 @@ struct TileSmem {
     // primitives of plane k with its two-deep x-y halo (the column's own
     // planes k-1 and k+1 live in registers)
     T w[5][TY + 4][TX + 4];
-    // face states of the plane, indexed as TileGeom::xface / yface, left
-    // (lower) state in fl and right (upper) state in fr, y faces in rotated
-    // slots (yslot). The flux through a face overwrites its left state (the
-    // thread that evaluates a face is the only one touching it).
-    T fl[5][TileGeom<TX, TY>::NF];
-    T fr[5][TileGeom<TX, TY>::NF];
+    // one slot per x and y face of a plane, indexed as TileGeom::xface /
+    // yface, y faces in rotated component order (yslot): first the right
+    // (upper) state of the face, then its flux, written by the one thread
+    // that solves the face. Two planes, in turn.
+    T f[2][5][TileGeom<TX, TY>::NF];
 };
 
 enum { ROLE_NONE = -1, ROLE_INT = 0, ROLE_BOTTOM = 1, ROLE_TOP = 2, ROLE_LEFT = 3, ROLE_RIGHT = 4 };
 
 // One tile: interior columns [x0, x0+TX) x [y0, y0+TY) (clipped to the
-// patch), planes [z0, z1). Per plane k (after a prologue plane z0-1 that only
-// produces the z+ face states, and before an epilogue plane z1 that only
-// produces the z- face states):
-//   A  each column owner reads plane k+1 of its column, stages plane k in
-//      LDS; halo threads stage the depth-2 halo and the corner cells;
-//   B  owners: slopes, predictor, face states (x and y into LDS; the z
-//      states of interior columns stay in registers);
-//   C  all threads: the x and y faces of the plane as uniform tasks, each
-//      face once; then interior columns: the z face below the plane, which
-//      completes plane k-1;
-//   D  interior: x-y flux divergence accumulated for plane k.
+// patch), planes [z0, z1). Every face is solved by the owner of the cell on
+// its left (lower) side, which keeps that cell's upper-face states in
+// registers; only the lower-face states pass through LDS, and the flux goes
+// back into the slot its right state came from, where the cell above finds
+// it. Per plane k (with a prologue plane z0-1 that only produces the z+ face
+// states, and an epilogue plane z1 that only produces the z- face states):
+//   I   the x-y flux divergence of plane k-1; slopes, predictor and face
+//       states of plane k; the z face below the plane, which completes and
+//       stores plane k-1;
+//   II  the plane's x and y faces (interior columns their upper ones, the
+//       ring columns to the left and below the tile's first ones); the
+//       column's plane k+2 from its loads, plane k+1 staged in LDS.
+// Two barriers a plane. The march is bound by latency, not by issue (a 2%
+// gain from 15% fewer vector instructions): what counts is how much work
+// stands between barriers, and registers and LDS for three workgroups per CU.
+// Against both states of every face passed through LDS to a thread picked for
+// the face, with four barriers a plane: 256^3 FP64 box with 24x8 tiles and
+// z-ranges of 32 planes 0.713 -> 0.641 ms, 250 x 190 x 141 FP32 with 24x8 / 16
+// 0.181 -> 0.165 ms, the 4096-patch batch in 16x8 tiles 1.210 -> 1.151 ms. Vector
+// instructions issue in 63% of the cycles (11.4 per cell), and 65 LDS
+// accesses per column and plane stand where 98 did. Loading U(k-1) before the
+// slopes instead of where it is used spills 14 registers; a fifth wave per
+// SIMD in FP32 spills 10 and is 4% (batch: 20%) slower.
 // STREAM_OUT: write the new state with streaming (non-temporal) stores. The
 // batched launches do: there the outputs of many small patches would
 // otherwise evict from the L2 the inputs that neighbouring tiles still read
@@ -180,8 +205,8 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
                              const Phys<T> &ph, int x0, int y0, int z0, int z1,
                              TileSmem<T, TX, TY> &sm, int &hits, bool want_cfl, double &smax)
 {
+#pragma clang fp contract(off)
     using Geo = TileGeom<TX, TY, NT>;
-    constexpr int NF = Geo::NF;
     const int tid = threadIdx.x;
     const int ax = min(TX, P.nx - x0);
     const int ay = min(TY, P.ny - y0);
@@ -203,8 +228,17 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
     }
     const bool owner = role != ROLE_NONE;
     const bool interior = role == ROLE_INT;
+    // a ring column has one face with the tile: an x face for the left and
+    // right columns, a y face for the bottom and top rows; the left and bottom
+    // columns hold its left (lower) state and solve it
+    const bool ring_x = role == ROLE_LEFT || role == ROLE_RIGHT;
+    const bool ring_lo = role == ROLE_LEFT || role == ROLE_BOTTOM;
     const int gi = x0 + ci, gj = y0 + cj;     // patch coordinates of the owned column
-    const int64_t col = view.column(gi, gj);
+    const uint32_t col = (uint32_t)view.column(gi, gj) * (uint32_t)sizeof(T);
+    // the face solved first (interior: the upper x face)
+    const int face1 = interior ? Geo::xface(ci + 1, cj)
+                               : (ring_x ? Geo::xface(ci + ring_lo, cj) : Geo::yface(ci, cj + ring_lo));
+    const bool solves = interior || ring_lo;
 
     // ---- depth-2 halo and depth-1 corner cells of a plane, one per thread
     int hi = 0, hj = 0;
@@ -222,7 +256,7 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
             hj = (c & 2) ? ay : -1;
         }
     }
-    const int64_t hcol = view.column(x0 + hi, y0 + hj);
+    const uint32_t hcol = (uint32_t)view.column(x0 + hi, y0 + hj) * (uint32_t)sizeof(T);
 
     // boundary-flux sheets of this patch
     const bool want_flux = bflux_base != nullptr && P.flux_off >= 0;
@@ -232,86 +266,67 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
     T *__restrict__ out = u_out_base + P.out_off;
     const int64_t ostride = (int64_t)P.nx * P.ny * P.nz;
     const double inv_dx = 1.0 / P.dx;
-    const int64_t ocol = (int64_t)gj * P.nx + gi;
+    const uint32_t ocol = (uint32_t)(gj * P.nx + gi) * (uint32_t)sizeof(T);
 
     // ---- registers of the owned column
     T Wm[5], W0[5], Wp[5], inv0 = T(1), invp = T(1);
-    T zprev[5], acc[5], zm[5], zpn[5];
+    T zprev[5], acc[5];
+    T up1[5], up2[5];       // upper-face states, then the fluxes solved from them
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
         Wm[q] = W0[q] = Wp[q] = T(0);
-        zprev[q] = acc[q] = zm[q] = zpn[q] = T(0);
+        zprev[q] = acc[q] = up1[q] = up2[q] = T(0);
     }
 
     // Column loads run one plane ahead of their use: the raw conserved state
-    // of plane k+1 (Upf) and of the halo of plane k (Hpf) are in flight while
-    // plane k-1 is computed. The last plane a column reads is z1+1 for an
+    // of plane k+2 (Upf) and of the halo of plane k+1 (Hpf) are in flight
+    // while plane k is computed. The last plane a column reads is z1+1 for an
     // interior column and z1 for a ring column.
     const int last_plane = interior ? z1 + 1 : z1;
-    T Upf[5], Hpf[5], Uold[5];
+    T Upf[5], Hpf[5];
 #pragma unroll
-    for (int q = 0; q < 5; ++q) Upf[q] = Hpf[q] = Uold[q] = T(0);
+    for (int q = 0; q < 5; ++q) Upf[q] = Hpf[q] = T(0);
 
-    // prologue: plane z0-2 (interior only, into W0, which the first step
-    // moves to Wm), plane z0-1 (into Wp) and the loads of plane z0
+    // prologue: planes z0-2 (interior only), z0-1 and z0, and the loads of
+    // plane z0+1
     if (owner) {
-        T U[5], inv;
-        if (interior) {
-            load5(uin + view.plane(z0 - 2) + col, view.vstride, U);
-            prim_from_cons(U, W0, inv, ph, hits);
-        }
-        load5(uin + view.plane(z0 - 1) + col, view.vstride, U);
-        prim_from_cons(U, Wp, invp, ph, hits);
-        load5(uin + view.plane(z0) + col, view.vstride, Upf);
-    }
-    if (halo) load5(uin + view.plane(z0) + hcol, view.vstride, Hpf);
-
-    // the faces this thread evaluates in phase C1, and whether each lies in
-    // the clipped tile
-    unsigned fact = 0;
-#pragma unroll
-    for (int s = 0; s < Geo::NSLOT; ++s) {
-        const int t = tid + s * Geo::NT;
-        int i, j;
-        const bool isx = Geo::face_ij(t, i, j);
-        if (t < NF && (isx ? (i <= ax && j < ay) : (i < ax && j <= ay))) fact |= 1u << s;
+        T Ua[5], Ub[5], Uc[5], inv;
+        if (interior) load5_plane(uin + view.plane(z0 - 2), view.vstride, col, Ua);
+        load5_plane(uin + view.plane(z0 - 1), view.vstride, col, Ub);
+        load5_plane(uin + view.plane(z0), view.vstride, col, Uc);
+        if (halo) load5_plane(uin + view.plane(z0), view.vstride, hcol, Hpf);
+        if (z0 + 1 <= last_plane) load5_plane(uin + view.plane(z0 + 1), view.vstride, col, Upf);
+        if (interior) prim_from_cons(Ua, Wm, inv, ph, hits);
+        prim_from_cons(Ub, W0, inv0, ph, hits);
+        prim_from_cons(Uc, Wp, invp, ph, hits);
+    } else if (halo) {
+        load5_plane(uin + view.plane(z0), view.vstride, hcol, Hpf);
     }
 
     const int lx = ci + 2, ly = cj + 2;
     const T half = T(0.5);
-    for (int k = z0 - 1; k <= z1; ++k) {
+    if (owner) {
+#pragma unroll
+        for (int q = 0; q < 5; ++q) sm.w[q][ly][lx] = W0[q];
+    }
+    __syncthreads();
+    int b = 0;
+    for (int k = z0 - 1;; ++k, b ^= 1) {
         const bool pre = k < z0;
         const bool post = k == z1;
+        T(&f)[5][Geo::NF] = sm.f[b];
 
-        // ---- A: advance the column, stage plane k. Every thread has
-        // finished reading plane k-1 from LDS (phase B, then a barrier)
-        // before it is overwritten here.
+        // ---- I
+        if (interior) {
+            if (k > z0) {
+                const T(&g)[5][Geo::NF] = sm.f[b ^ 1];
 #pragma unroll
-        for (int q = 0; q < 5; ++q) {
-            Wm[q] = W0[q];
-            W0[q] = Wp[q];
+                for (int q = 0; q < 5; ++q)
+                    acc[q] = ((up1[q] - g[q][Geo::xface(ci, cj)]) +
+                              (up2[yslot(q)] - g[yslot(q)][Geo::yface(ci, cj)])) + acc[q];
+            }
         }
-        inv0 = invp;
-        if (owner && k + 1 <= last_plane) {
-            prim_from_cons(Upf, Wp, invp, ph, hits);
-            if (k + 2 <= last_plane) load5(uin + view.plane(k + 2) + col, view.vstride, Upf);
-        }
-        if (owner) {
-#pragma unroll
-            for (int q = 0; q < 5; ++q) sm.w[q][ly][lx] = W0[q];
-        }
-        if (!pre && !post && halo) {
-            T Wh[5], invh;
-            prim_from_cons(Hpf, Wh, invh, ph, hits);
-#pragma unroll
-            for (int q = 0; q < 5; ++q) sm.w[q][hj + 2][hi + 2] = Wh[q];
-            if (k + 1 < z1) load5(uin + view.plane(k + 1) + hcol, view.vstride, Hpf);
-        }
-        __syncthreads();
-
-        // ---- B: slopes, predictor, face states
-        const bool work = pre || post ? interior : owner;
-        if (work) {
+        if (interior || (owner && !pre && !post)) {
             T Sx[5], Sy[5], Sz[5], Ws[5];
 #pragma unroll
             for (int q = 0; q < 5; ++q) {
@@ -321,135 +336,157 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
                 Sz[q] = limited_slope<LIM>(c - Wm[q], Wp[q] - c);
             }
             predictor(W0, inv0, Sx, Sy, Sz, lam, ph.gamma, Ws);
-            if (pre) {
-                face_state(Ws, Sz, half, zprev, ph, hits);
-            } else if (post) {
-                face_state(Ws, Sz, -half, zm, ph, hits);
-            } else if (interior) {
-                T st[5];
-                face_state(Ws, Sx, half, st, ph, hits);
+            if (interior) {
+                T zm[5], zpn[5], dx[5], dy[5];
 #pragma unroll
-                for (int q = 0; q < 5; ++q) sm.fl[q][Geo::xface(ci + 1, cj)] = st[q];
-                face_state(Ws, Sx, -half, st, ph, hits);
+                for (int q = 0; q < 5; ++q) {
+                    zm[q] = fma(-half, Sz[q], Ws[q]);
+                    zpn[q] = fma(half, Sz[q], Ws[q]);
+                    dx[q] = fma(-half, Sx[q], Ws[q]);
+                    up1[q] = fma(half, Sx[q], Ws[q]);
+                    dy[q] = fma(-half, Sy[q], Ws[q]);
+                    up2[yslot(q)] = fma(half, Sy[q], Ws[q]);
+                }
+                // the lowest of the six densities and of the six pressures: a
+                // fused multiply-add is monotone, so it is the one of the
+                // largest slope; only below the floor are the states looked at
+                const T rmin = fma(-half, fmax(fmax(fabs(Sx[0]), fabs(Sy[0])), fabs(Sz[0])), Ws[0]);
+                const T pmin = fma(-half, fmax(fmax(fabs(Sx[4]), fabs(Sy[4])), fabs(Sz[4])), Ws[4]);
+                if (__builtin_expect(rmin < ph.rho_floor || pmin < ph.p_floor, 0)) {
+                    // the prologue and epilogue planes use (and count) one state
+                    int none = 0;
+                    int &xy = pre || post ? none : hits;
+                    zm[0] = floored(zm[0], ph.rho_floor, pre ? none : hits);
+                    zm[4] = floored(zm[4], ph.p_floor, pre ? none : hits);
+                    zpn[0] = floored(zpn[0], ph.rho_floor, post ? none : hits);
+                    zpn[4] = floored(zpn[4], ph.p_floor, post ? none : hits);
+                    dx[0] = floored(dx[0], ph.rho_floor, xy);
+                    dx[4] = floored(dx[4], ph.p_floor, xy);
+                    up1[0] = floored(up1[0], ph.rho_floor, xy);
+                    up1[4] = floored(up1[4], ph.p_floor, xy);
+                    dy[0] = floored(dy[0], ph.rho_floor, xy);
+                    dy[4] = floored(dy[4], ph.p_floor, xy);
+                    up2[0] = floored(up2[0], ph.rho_floor, xy);
+                    up2[4] = floored(up2[4], ph.p_floor, xy);
+                }
 #pragma unroll
-                for (int q = 0; q < 5; ++q) sm.fr[q][Geo::xface(ci, cj)] = st[q];
-                face_state(Ws, Sy, half, st, ph, hits);
+                for (int q = 0; q < 5; ++q) {
+                    f[q][Geo::xface(ci, cj)] = dx[q];
+                    f[yslot(q)][Geo::yface(ci, cj)] = dy[q];
+                }
+                if (!pre) {
+                    // the z face below the plane; completes plane k-1
+                    T F[5];
+                    face_flux<RS, 2, SQ_Z>(zprev, zm, ph, F);
+                    if (want_flux && (k == 0 || k == P.nz)) {
+                        T *sheet = bf + 10 * sxs + 10 * sys + (k == 0 ? 0 : 5 * szs);
 #pragma unroll
-                for (int q = 0; q < 5; ++q) sm.fl[yslot(q)][Geo::yface(ci, cj + 1)] = st[q];
-                face_state(Ws, Sy, -half, st, ph, hits);
+                        for (int q = 0; q < 5; ++q) sheet[q * szs + (int64_t)gj * P.nx + gi] = F[q];
+                    }
+                    if (k > z0) {
+                        // U' = U - dt/dx (acc + F_z(k-1/2)), acc = div_xy(k-1) - F_z(k-3/2)
+                        T Uold[5], Un[5];
+                        load5_plane(uin + view.plane(k - 1), view.vstride, col, Uold);
+                        T *o = out + (int64_t)(k - 1) * P.nx * P.ny;
 #pragma unroll
-                for (int q = 0; q < 5; ++q) sm.fr[yslot(q)][Geo::yface(ci, cj)] = st[q];
-                face_state(Ws, Sz, -half, zm, ph, hits);
-                face_state(Ws, Sz, half, zpn, ph, hits);
+                        for (int q = 0; q < 5; ++q) {
+                            Un[q] = fma(-dtdx, acc[q] + F[q], Uold[q]);
+                            T *dst = reinterpret_cast<T *>(
+                                reinterpret_cast<char *>(o + q * ostride) + ocol);
+                            if constexpr (STREAM_OUT) __builtin_nontemporal_store(Un[q], dst);
+                            else *dst = Un[q];
+                        }
+                        if (want_cfl) {
+                            // signal speed of the new state, exactly as cfl_dt computes it
+                            int unused = 0;
+                            smax = fmax(smax, cell_signal(Un, ph, unused) * inv_dx);
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) acc[q] = -F[q];
+                }
+#pragma unroll
+                for (int q = 0; q < 5; ++q) zprev[q] = zpn[q];
             } else {
                 // a ring column: the one state its face with the tile needs,
-                // direction and side selected per lane, so that a wave holding
-                // ring columns of all four sides evaluates a single face state.
-                // The face is an x face for the left and right columns, a y
-                // face for the bottom and top rows; the left and bottom
-                // columns hold the face's left (lower) state.
-                const bool ring_x = role == ROLE_LEFT || role == ROLE_RIGHT;
-                const bool ring_lo = role == ROLE_LEFT || role == ROLE_BOTTOM;
-                const int ring_face =
-                    ring_x ? Geo::xface(ci + ring_lo, cj) : Geo::yface(ci, cj + ring_lo);
-                T S[5], st[5];
+                // direction and side selected per lane
+                T st[5];
 #pragma unroll
-                for (int q = 0; q < 5; ++q) S[q] = ring_x ? Sx[q] : Sy[q];
-                face_state(Ws, S, ring_lo ? half : -half, st, ph, hits);
-                T *dst = ring_lo ? &sm.fl[0][ring_face] : &sm.fr[0][ring_face];
+                for (int q = 0; q < 5; ++q)
+                    st[q] = fma(ring_lo ? half : -half, ring_x ? Sx[q] : Sy[q], Ws[q]);
+                st[0] = floored(st[0], ph.rho_floor, hits);
+                st[4] = floored(st[4], ph.p_floor, hits);
 #pragma unroll
-                for (int q = 0; q < 5; ++q) dst[(ring_x ? q : yslot(q)) * NF] = st[q];
-            }
-        }
-        if (!post) __syncthreads();
-        if (pre) continue;
-
-        // ---- C1: the x and y faces of the plane, NSLOT per thread (face t =
-        // tid + s NT). Both orientations read their states from and write their
-        // flux to slots 0..4 of face t, so the task needs no per-face address
-        // arithmetic; only the boundary-flux sheets need the face's (i, j).
-        if (!post) {
-            // not unrolled: two faces in flight at once would double the
-            // registers the Riemann solver holds
-#pragma unroll 1
-            for (int s = 0; s < Geo::NSLOT; ++s) {
-                if (!((fact >> s) & 1u)) continue;
-                const int t = tid + s * Geo::NT;
-                T L[5], R[5], G[5];
+                for (int q = 0; q < 5; ++q) up1[q] = ring_x ? st[q] : st[q == 1 ? 2 : (q == 2 ? 3 : (q == 3 ? 1 : q))];
+                if (!ring_lo) {
 #pragma unroll
-                for (int q = 0; q < 5; ++q) {
-                    L[q] = sm.fl[q][t];
-                    R[q] = sm.fr[q][t];
+                    for (int q = 0; q < 5; ++q) f[q][face1] = up1[q];
                 }
-                riemann<RS>(L, R, ph, G);
-#pragma unroll
-                for (int q = 0; q < 5; ++q) sm.fl[q][t] = G[q];
-                if (want_flux) {
-                    int i, j;
-                    const bool isx = Geo::face_ij(t, i, j);
-                    const int fi = x0 + i, fj = y0 + j;
-                    if (isx && (fi == 0 || fi == P.nx)) {
-                        T *sheet = bf + (fi == 0 ? 0 : 5 * sxs);
-#pragma unroll
-                        for (int q = 0; q < 5; ++q) sheet[q * sxs + (int64_t)k * P.ny + fj] = G[q];
-                    }
-                    if (!isx && (fj == 0 || fj == P.ny)) {
-                        T *sheet = bf + 10 * sxs + (fj == 0 ? 0 : 5 * sys);
-#pragma unroll
-                        for (int q = 0; q < 5; ++q)
-                            sheet[q * sys + (int64_t)k * P.nx + fi] = G[yslot(q)];
-                    }
-                }
-            }
-        }
-
-        // ---- C2: the z face below the plane; completes plane k-1
-        if (interior) {
-            T F[5];
-            face_flux<RS, 2>(zprev, zm, ph, F);
-            if (want_flux && (k == 0 || k == P.nz)) {
-                T *sheet = bf + 10 * sxs + 10 * sys + (k == 0 ? 0 : 5 * szs);
-#pragma unroll
-                for (int q = 0; q < 5; ++q) sheet[q * szs + (int64_t)gj * P.nx + gi] = F[q];
-            }
-            if (k > z0) {
-                // loaded here rather than ahead: the registers a prefetch would
-                // hold keep the kernel within three waves per SIMD without spills
-                load5(uin + view.plane(k - 1) + col, view.vstride, Uold);
-                // U' = U - dt/dx (acc + F_z(k-1/2)), acc = div_xy(k-1) - F_z(k-3/2)
-                T *o = out + (int64_t)(k - 1) * P.nx * P.ny + ocol;
-                T Un[5];
-#pragma unroll
-                for (int q = 0; q < 5; ++q) {
-                    Un[q] = Uold[q] - dtdx * (acc[q] + F[q]);
-                    if constexpr (STREAM_OUT)
-                        __builtin_nontemporal_store(Un[q], &o[q * ostride]);
-                    else
-                        o[q * ostride] = Un[q];
-                }
-                if (want_cfl) {
-                    // signal speed of the new state, exactly as cfl_dt computes it
-                    int unused = 0;
-                    smax = fmax(smax, cell_signal(Un, ph, unused) * inv_dx);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < 5; ++q) {
-                acc[q] = -F[q];
-                zprev[q] = zpn[q];
             }
         }
         if (post) break;
         __syncthreads();
 
-        // ---- D: x-y flux divergence of the plane
-        if (interior) {
+        // ---- II
+        if (!pre && solves) {
+            T R[5], G[5];
 #pragma unroll
-            for (int q = 0; q < 5; ++q)
-                acc[q] = ((sm.fl[q][Geo::xface(ci + 1, cj)] - sm.fl[q][Geo::xface(ci, cj)]) +
-                          (sm.fl[yslot(q)][Geo::yface(ci, cj + 1)] -
-                           sm.fl[yslot(q)][Geo::yface(ci, cj)])) + acc[q];
+            for (int q = 0; q < 5; ++q) R[q] = f[q][face1];
+            riemann<RS, SQ_XY>(up1, R, ph, G);
+#pragma unroll
+            for (int q = 0; q < 5; ++q) f[q][face1] = up1[q] = G[q];
+            if (want_flux) {
+                // the face's index along its axis: gi+1 (an interior column's
+                // upper face, or the left ring's), gj+1 for the bottom ring
+                if (interior || ring_x) {
+                    if (gi + 1 == (interior ? P.nx : 0)) {
+                        T *sheet = bf + (interior ? 5 * sxs : 0);
+#pragma unroll
+                        for (int q = 0; q < 5; ++q) sheet[q * sxs + (int64_t)k * P.ny + gj] = G[q];
+                    }
+                } else if (gj + 1 == 0) {
+                    T *sheet = bf + 10 * sxs;
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) sheet[q * sys + (int64_t)k * P.nx + gi] = G[yslot(q)];
+                }
+            }
+            if (interior) {
+                const int face2 = Geo::yface(ci, cj + 1);
+#pragma unroll
+                for (int q = 0; q < 5; ++q) R[q] = f[q][face2];
+                riemann<RS, SQ_XY>(up2, R, ph, G);
+#pragma unroll
+                for (int q = 0; q < 5; ++q) f[q][face2] = up2[q] = G[q];
+                if (want_flux && gj + 1 == P.ny) {
+                    T *sheet = bf + 10 * sxs + 5 * sys;
+#pragma unroll
+                    for (int q = 0; q < 5; ++q) sheet[q * sys + (int64_t)k * P.nx + gi] = G[yslot(q)];
+                }
+            }
         }
+        // the column moves up: plane k+1 staged, plane k+2 from its loads
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            Wm[q] = W0[q];
+            W0[q] = Wp[q];
+        }
+        inv0 = invp;
+        if (owner) {
+#pragma unroll
+            for (int q = 0; q < 5; ++q) sm.w[q][ly][lx] = W0[q];
+            if (k + 2 <= last_plane) {
+                prim_from_cons_march(Upf, Wp, invp, ph, hits);
+                if (k + 3 <= last_plane) load5_plane(uin + view.plane(k + 3), view.vstride, col, Upf);
+            }
+        }
+        if (halo && k + 1 < z1) {
+            T Wh[5], invh;
+            prim_from_cons_march(Hpf, Wh, invh, ph, hits);
+#pragma unroll
+            for (int q = 0; q < 5; ++q) sm.w[q][hj + 2][hi + 2] = Wh[q];
+            if (k + 2 < z1) load5_plane(uin + view.plane(k + 2), view.vstride, hcol, Hpf);
+        }
+        __syncthreads();
     }
 }
 
