@@ -82,7 +82,7 @@ struct gd_ctx {
     BatchCache ppm_batch;                // work items of the fused PPM batched step
     BatchCache cfl;                      // descriptor cache used by cfl_dt
     Scratch adj;                         // adjoint scratch (grown on demand)
-    Scratch mhd;                         // MHD step scratch (grown on demand)
+    Scratch mhd;                         // FP32 MHD step scratch (grown on demand)
     Scratch ppm_s;                       // PPM face-state scratch (grown on demand)
     std::vector<void *> retired;         // captured buffers replaced since; freed at destroy
     gd_stream_state *stream = nullptr;   // streamed batches (created on first use)
@@ -950,11 +950,11 @@ int step_mhd_impl(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int nz, cons
     if ((r = set_device(ctx))) return r;
     hipStream_t s = (hipStream_t)hip_stream;
     const size_t need = gd::mhd_scratch_bytes(opts->dtype, nx, ny, nz);
-    if ((r = ensure_scratch(ctx, ctx->mhd, need, s, "MHD"))) return r;
+    if (need && (r = ensure_scratch(ctx, ctx->mhd, need, s, "MHD"))) return r;
     gd::MhdScalars sc{ gamma, opts->rho_floor, opts->p_floor, dx, dt, ch, alpha };
     int e = gd::launch_mhd_step(opts->dtype, opts->limiter, nx, ny, nz, u_in, u_out, sc, dt_dev,
-                                ch_dev, ctx->mhd.p, cfl, dt_next, ch_next,
-                                slot_for(ctx, s).u64 + 6, s);
+                                ch_dev, ctx->mhd.p, cfl, dt_next, ch_next, slot_for(ctx, s).u64 + 6,
+                                ctx->num_cus, s);
     if (e) return hip_fail(ctx, e, "godunov_step_mhd launch");
     return GD_OK;
 }

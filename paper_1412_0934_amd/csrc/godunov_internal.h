@@ -103,7 +103,8 @@ struct MhdScalars {
     double gamma, rho_floor, p_floor, dx, dt, ch, alpha;
 };
 
-// Bytes of device scratch one MHD step of an nx x ny x nz box needs.
+// Bytes of device scratch one MHD step of an nx x ny x nz box needs (none in
+// double precision).
 size_t mhd_scratch_bytes(int dtype, int nx, int ny, int nz);
 
 // One step; dt_dev / ch_dev, when not null, replace sc.dt / sc.ch. With
@@ -113,7 +114,7 @@ size_t mhd_scratch_bytes(int dtype, int nx, int ny, int nz);
 int launch_mhd_step(int dtype, int limiter, int nx, int ny, int nz, const void *u_in, void *u_out,
                     const MhdScalars &sc, const double *dt_dev, const double *ch_dev,
                     void *scratch, double cfl, double *dt_next, double *ch_next,
-                    unsigned long long *acc, hipStream_t s);
+                    unsigned long long *acc, int num_cus, hipStream_t s);
 
 // dt = cfl dx / max sum_d (|u_d| + cf_d) and ch = max_d (|u_d| + cf_d) into
 // device scalars (either may be null); acc: two zeroed 64-bit accumulators,

@@ -14,17 +14,25 @@
 // Kusano (2005) with that normal field gives the other seven fluxes; then
 // U' = U - dt/dx ((dF_x + dF_y) + dF_z) and psi' <- psi' exp(-alpha ch dt/dx).
 //
-// Two launches per step over a library-owned scratch: predict (one thread per
-// cell: 7-point stencil, slopes, half step, six predicted face states) and a
-// flux sweep (z-marching column tiles: x and y faces through LDS, z faces in
-// registers, the update, and optionally the signal speeds of the new state).
+// Double precision takes one launch per step (and a one-thread launch for the
+// next dt and ch): the tile march of the Euler step (godunov_tile.h) with nine
+// variables; the predicted face states never leave the chip.
+// Single precision takes two launches over a library-owned scratch: predict
+// (one thread per cell: 7-point stencil, slopes, half step, six predicted face
+// states) and a flux sweep (z-marching column tiles: x and y faces through LDS,
+// z faces in registers, the update, and optionally the signal speeds of the
+// new state). Its time step is a double that callers compare to far below a
+// single ulp, so the state keeps the bits it always had.
 // Every value is written by one thread and the reductions are maxima:
 // deterministic.
 #include "godunov_internal.h"
 #include "godunov_math.h"
+#include "godunov_tile.h"
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 namespace gd {
 
@@ -40,6 +48,7 @@ struct Par {
     T h;                      // dt / (2 dx)
     T c;                      // dt / dx
     T ch, ch2;                // cleaning speed and its square
+    T ich2;                   // 1 / (2 ch)
     T damp;                   // exp(-alpha ch dt / dx)
 };
 
@@ -365,7 +374,7 @@ __global__ __launch_bounds__(256) void k_predict(Par<T> P, const T *__restrict__
     }
 }
 
-// ------------------------------------------------------------ flux sweep
+// ------------------------------------------------------------ flux sweep (FP32)
 
 // A workgroup owns a 16 x 16 column tile and marches up a z-range. Per plane,
 // the predicted x-face states of the tile (and of one halo cell at each end
@@ -528,6 +537,539 @@ void k_sweep(Par<T> P, const T *__restrict__ dyn,
     }
 }
 
+// ------------------------------------------------------------ one launch (FP64)
+
+// dt and ch of a step: the host's values, or device scalars where they are
+// given.
+struct Dynamic {
+    const double *dt_dev, *ch_dev;
+    double dx, alpha;
+};
+
+// A value that every lane holds, moved to scalar registers.
+__device__ __forceinline__ double uniform(double v)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(unsigned)b);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// The time-dependent parameters of a step whose dt or ch come from the device.
+template <typename T>
+__device__ __forceinline__ void take_scalars(Par<T> &P, const Dynamic &D, double dt, double ch)
+{
+    if (!D.dt_dev && !D.ch_dev) return;
+    if (D.dt_dev) dt = *D.dt_dev;
+    if (D.ch_dev) ch = *D.ch_dev;
+    P.h = uniform(T(dt / (2.0 * D.dx)));
+    P.c = uniform(T(dt / D.dx));
+    P.ch = uniform(T(ch));
+    P.ch2 = uniform(T(ch * ch));
+    P.ich2 = uniform(T(1.0 / (2.0 * ch)));
+    P.damp = uniform(T(exp(-D.alpha * ch * dt / D.dx)));
+}
+
+// GLM + HLLD flux through a face, states and flux rotated to its frame:
+// (rho, u_n, u_t1, u_t2, p, B_n, B_t1, B_t2, psi) and the fluxes of
+// (rho, m_n, m_t1, m_t2, E, B_n, B_t1, B_t2, psi).
+// The flux of every region is the physical flux of the state the face lies in
+// -- K itself, K* or K** on the side K of the contact -- with the normal
+// velocity S_M and total pressure p_T* of the fan (u_K and p_TK outside it):
+// F_K + S_K (U*_K - U_K) + S*_K (U**_K - U*_K) collapses to it by the jump
+// conditions, so neither side's conserved vector nor flux is formed. In the
+// degenerate case, whose star field keeps the side's tangential values, the
+// induction flux keeps u_K instead of S_M on them, as the sum above does.
+// Products and sums are fused as written, so that all inlined copies give the
+// same bits.
+template <typename T>
+__device__ __forceinline__ void glm_hlld(const Par<T> &P, const T L[NV], const T R[NV], T F[NV])
+{
+#pragma clang fp contract(off)
+    const T half = T(0.5);
+    const T Bn = fma(-(R[8] - L[8]), P.ich2, half * (L[5] + R[5]));
+    F[5] = fma(-half * P.ch, R[5] - L[5], half * (L[8] + R[8]));
+    F[8] = P.ch2 * Bn;
+    const T Bn2 = Bn * Bn;
+    // total pressure and fast speed of both sides
+    T pT[2], cf[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const T *W = s ? R : L;
+        const T B2 = fma(W[7], W[7], fma(W[6], W[6], Bn2));
+        pT[s] = fma(half, B2, W[4]);
+        const T ir = fast_rcp(W[0]);
+        const T a2 = P.gamma * W[4] * ir;
+        const T q = fma(B2, ir, a2);
+        const T disc = fma(q, q, T(-4) * a2 * (Bn2 * ir));
+        cf[s] = hw_sqrt(half * (q + hw_sqrt(disc < T(0) ? T(0) : disc)));
+    }
+    const T SL = fmin(L[1] - cf[0], R[1] - cf[1]);
+    const T SR = fmax(L[1] + cf[0], R[1] + cf[1]);
+    const T dL = (SL - L[1]) * L[0], dR = (SR - R[1]) * R[0];
+    const T idd = fast_rcp(dR - dL);
+    T SM = fma(dR, R[1], fma(-dL, L[1], pT[0] - pT[1])) * idd;
+    T pS = fma(dL * dR, R[1] - L[1], fma(dR, pT[0], -(dL * pT[1]))) * idd;
+
+    // K, the side of the contact the face lies on, and O, the other one
+    const bool supL = SL >= T(0), supR = SR <= T(0);
+    const bool left = supL || (!supR && SM >= T(0));
+    const bool sup = supL || supR;
+    const T rK = left ? L[0] : R[0], uK = left ? L[1] : R[1];
+    const T vK = left ? L[2] : R[2], wK = left ? L[3] : R[3];
+    const T pK = left ? L[4] : R[4], pTK = left ? pT[0] : pT[1];
+    const T yK = left ? L[6] : R[6], zK = left ? L[7] : R[7];
+    const T SK = left ? SL : SR, dK = left ? dL : dR;
+    const T uO = left ? R[1] : L[1], vO = left ? R[2] : L[2], wO = left ? R[3] : L[3];
+    const T yO = left ? R[6] : L[6], zO = left ? R[7] : L[7];
+    const T SO = left ? SR : SL, dO = left ? dR : dL;
+
+    // single-star states of both sides; outside the fan K* is K
+    const T SMK = sup ? uK : SM;
+    pS = sup ? pTK : pS;
+    const T isd = fast_rcp(SK - SMK);
+    const T rs = dK * isd;
+    const T ddK = dK * (SK - uK);
+    const T denK = fma(dK, SK - SMK, -Bn2);
+    const bool badK = fabs(denK) <= T(1e-12) * (ddK + Bn2);
+    const T idK = fast_rcp(denK);
+    const T tK = badK ? T(0) : Bn * (SMK - uK) * idK;
+    const T fK = badK ? T(1) : (ddK - Bn2) * idK;
+    const T vs = fma(-yK, tK, vK), ws = fma(-zK, tK, wK), ys = yK * fK, zs = zK * fK;
+    const T rO = dO * fast_rcp(SO - SM);
+    const T ddO = dO * (SO - uO);
+    const T denO = fma(dO, SO - SM, -Bn2);
+    const bool badO = fabs(denO) <= T(1e-12) * (ddO + Bn2);
+    const T idO = fast_rcp(denO);
+    const T tO = badO ? T(0) : Bn * (SM - uO) * idO;
+    const T fO = badO ? T(1) : (ddO - Bn2) * idO;
+    const T vo = fma(-yO, tO, vO), wo = fma(-zO, tO, wO), yo = yO * fO, zo = zO * fO;
+
+    const T B2K = fma(zK, zK, fma(yK, yK, Bn2));
+    const T EK = fma(half, fma(rK, fma(wK, wK, fma(vK, vK, uK * uK)), B2K), pK * P.inv_gm1);
+    const T uB = fma(wK, zK, fma(vK, yK, uK * Bn));
+    const T uBs = fma(ws, zs, fma(vs, ys, SMK * Bn));
+    T E = isd * fma(Bn, uB - uBs, fma(pS, SMK, fma(SK - uK, EK, -(pTK * uK))));
+
+    // between the Alfven waves: the double-star state
+    const T iq = fast_rsqrt(rs), sqK = rs * iq, sqO = hw_sqrt(rO);
+    const T sg = left ? T(1) : T(-1);
+    // S*_K = S_M -+ |B_n| / sqrt(rho*): the face lies inside it when S*_K has
+    // passed it
+    const bool dbl = !sup && sg * SM - fabs(Bn) * iq < T(0);
+    const T sgn = Bn > T(0) ? sg : (Bn < T(0) ? -sg : T(0));
+    const T iss = fast_rcp(sqK + sqO);
+    const T sK = sqK * iss, sO = sqO * iss, si = sgn * iss, sp = sgn * (sqK * sO);
+    const T vd = fma(si, yo - ys, fma(sO, vo, sK * vs));
+    const T wd = fma(si, zo - zs, fma(sO, wo, sK * ws));
+    const T yd = fma(sp, vo - vs, fma(sO, ys, sK * yo));
+    const T zd = fma(sp, wo - ws, fma(sO, zs, sK * zo));
+    const T uBd = fma(wd, zd, fma(vd, yd, SMK * Bn));
+    const T v = dbl ? vd : vs, w = dbl ? wd : ws, y = dbl ? yd : ys, z = dbl ? zd : zs;
+    const T uBf = dbl ? uBd : uBs;
+    E = fma(-(sgn * sqK), uBs - uBf, E);
+
+    const T mass = rs * SMK;
+    F[0] = mass;
+    F[1] = fma(mass, SMK, pS - Bn2);
+    F[2] = fma(mass, v, -(Bn * y));
+    F[3] = fma(mass, w, -(Bn * z));
+    F[4] = fma(SMK, E + pS, -(Bn * uBf));
+    const T du = badK ? uK - SMK : T(0);
+    F[6] = fma(du, yK, fma(SMK, y, -(Bn * v)));
+    F[7] = fma(du, zK, fma(SMK, z, -(Bn * w)));
+}
+
+// Position of natural component q in the frame of a face normal to D
+template <int D>
+__host__ __device__ constexpr int slot(int q)
+{
+    return q == 0 || q == 4 || q == 8 ? q : (q < 4 ? 1 + (q - 1 - D + 3) % 3 : 5 + (q - 5 - D + 3) % 3);
+}
+
+// A face state after the half step: the conserved values of W +- S/2 plus the
+// increment h dU common to the cell's six faces.
+template <typename T>
+__device__ __forceinline__ void half_step(const Par<T> &P, const T W[NV], const T dU[NV], T Wn[NV])
+{
+    T U[NV], V[NV];
+    to_cons(P, W, U);
+#pragma unroll
+    for (int q = 0; q < NV; ++q) U[q] += P.h * dU[q];
+    to_prim<false>(P, U, V);
+#pragma unroll
+    for (int q = 0; q < NV; ++q) Wn[q] = V[q];
+}
+
+template <typename T, int TX, int TY>
+struct MhdSmem {
+    T w[NV][TY + 4][TX + 4];                 // plane k with its two-deep x-y halo
+    T f[NV][TileGeom<TX, TY>::NF];           // a face's right state, then its flux
+    double red[2][TileGeom<TX, TY>::NT / 64];
+};
+
+// The loads and stores of one cell, plane base and variable stride scalar
+template <typename T>
+__device__ __forceinline__ void load9(const T *__restrict__ p, int n, uint32_t at, T U[NV])
+{
+#pragma unroll
+    for (int q = 0; q < NV; ++q)
+        U[q] = *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p + (size_t)q * n) + at);
+}
+
+// One workgroup: a TX x TY column tile and planes [z0, z1), marched as in
+// godunov_tile: a ring of columns around the tile holds the predicted states
+// its outer faces need; every face is solved once, by the owner of its lower
+// cell, which keeps the upper-face states in registers; lower-face states and
+// fluxes pass through LDS. Per plane, between three barriers:
+//   slopes, half step | face states, z face, update of plane k-1 | x and y
+//   faces, plane k+1 staged | (x-y flux divergence, then the next plane)
+// Bound by registers: nine FP64 variables leave no room for a second buffer of
+// faces or for the column's own plane (it is read back from LDS); two
+// workgroups of four waves per CU at 256 registers. With one loop for all
+// waves, halo loads held by every thread and the slopes kept from the half step
+// to the face states, 70 registers spilled, the prefetched plane among them
+// (its whole latency then stood between two barriers), and a step took
+// 0.635 ms. 128^3 box, dt and ch on the device: 0.333 ms a step against 0.593 ms
+// for the two launches over 54 staged values per cell.
+template <typename T, int LIM, int TX, int TY>
+__global__ __launch_bounds__(tile_threads(TX, TY))
+__attribute__((amdgpu_waves_per_eu(2))) void k_step(
+    Par<T> P, Dynamic D, double dt_host, double ch_host, const T *__restrict__ u,
+    T *__restrict__ out, int ntx, int nty, int zlen, int nitem, int per_xcd,
+    unsigned long long *__restrict__ speed_acc)
+{
+    using Geo = TileGeom<TX, TY>;
+    __shared__ MhdSmem<T, TX, TY> sm;
+    // workgroups are dealt to the eight XCDs in turn: give each XCD a
+    // contiguous range of work items, so that neighbouring tiles share its L2
+    const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (item >= nitem) return;
+    take_scalars(P, D, dt_host, ch_host);
+    const int bx = item % ntx, br = item / ntx;
+    const int x0 = bx * TX, y0 = (br % nty) * TY, z0 = (br / nty) * zlen;
+    const int z1 = min(z0 + zlen, P.nz);
+    const int tid = threadIdx.x;
+    const int ax = min(TX, P.nx - x0), ay = min(TY, P.ny - y0);
+
+    // byte offset in a plane; two wraps cover the stencil's reach of two cells
+    // for every extent
+    auto place = [&](int i, int j) {
+        i = wrap_once(wrap_once(x0 + i, P.nx), P.nx);
+        j = wrap_once(wrap_once(y0 + j, P.ny), P.ny);
+        return (uint32_t)(j * P.nx + i) * (uint32_t)sizeof(T);
+    };
+    auto plane = [&](int k) {
+        return u + (size_t)wrap_once(wrap_once(k, P.nz), P.nz) * (P.nx * P.ny);
+    };
+    double smax = 0.0, dmax = 0.0;
+    // The tile's waves and the ring's run loops of their own (the branch is the
+    // same for a whole wave, and both loops pass the same barriers): the ring
+    // has no z face, no update and no second face, and stages the halo instead,
+    // so neither side pays registers for what the other one holds.
+    if (uniform(tid >> 6) < Geo::NINT / 64) {
+        const int ci = tid % TX, cj = tid / TX;
+        const bool own = ci < ax && cj < ay;
+        const int lx = ci + 2, ly = cj + 2;
+        const uint32_t col = own ? place(ci, cj) : 0;
+        const int xlo = Geo::xface(ci, cj), xhi = Geo::xface(ci + 1, cj);
+        const int ylo = Geo::yface(ci, cj), yhi = Geo::yface(ci, cj + 1);
+        // planes k-1 and k+1 of the column (plane k is in LDS); zprev the upper
+        // z state of plane k-1; up1, up2 the upper x and y states, then fluxes
+        T Wm[NV], Wp[NV], zprev[NV], acc[NV], up1[NV], up2[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+            Wm[q] = Wp[q] = zprev[q] = acc[q] = up1[q] = T(0);
+            up2[q] = T(0);
+        }
+        if (own) {
+            T Ua[NV], Ub[NV], Uc[NV];
+            load9(plane(z0 - 2), P.n, col, Ua);
+            load9(plane(z0 - 1), P.n, col, Ub);
+            load9(plane(z0), P.n, col, Uc);
+            to_prim<false>(P, Ua, Wm);
+            to_prim<false>(P, Uc, Wp);
+            to_prim<false>(P, Ub, Uc);
+#pragma unroll
+            for (int q = 0; q < NV; ++q) sm.w[q][ly][lx] = Uc[q];
+        }
+        __syncthreads();
+        for (int k = z0 - 1;; ++k) {
+            const bool pre = k < z0, post = k == z1;
+            // the column's cell of plane k and its limited slopes along axis d;
+            // formed twice, for the half step and for the face states, rather
+            // than held (54 registers) in between
+            T W0[NV], S[NV], dU[NV];
+            auto slopes = [&](int d) {
+#pragma unroll
+                for (int q = 0; q < NV; ++q) {
+                    const T c = W0[q] = sm.w[q][ly][lx];
+                    if (d == 0) S[q] = limited_slope<LIM>(c - sm.w[q][ly][lx - 1], sm.w[q][ly][lx + 1] - c);
+                    else if (d == 1) S[q] = limited_slope<LIM>(c - sm.w[q][ly - 1][lx], sm.w[q][ly + 1][lx] - c);
+                    else S[q] = limited_slope<LIM>(c - Wm[q], Wp[q] - c);
+                }
+            };
+            // ---- the x-y flux divergence of plane k-1; the half step of plane k
+            if (own) {
+                if (k > z0) {
+#pragma unroll
+                    for (int q = 0; q < NV; ++q)
+                        acc[q] = ((up1[q] - sm.f[q][xlo]) +
+                                  (up2[slot<1>(q)] - sm.f[slot<1>(q)][ylo])) + acc[q];
+                }
+#pragma unroll
+                for (int q = 0; q < NV; ++q) dU[q] = T(0);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    // axis after axis: interleaved they would hold three times
+                    // the registers
+                    __builtin_amdgcn_sched_barrier(0);
+                    slopes(d);
+                    T up[NV], dn[NV], Fu[NV], Fd[NV];
+                    face_values(P, W0, S, up, dn);
+                    if (d == 0) { phys_flux<0>(P, up, Fu); phys_flux<0>(P, dn, Fd); }
+                    else if (d == 1) { phys_flux<1>(P, up, Fu); phys_flux<1>(P, dn, Fd); }
+                    else { phys_flux<2>(P, up, Fu); phys_flux<2>(P, dn, Fd); }
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) dU[q] -= Fu[q] - Fd[q];
+                }
+            }
+            __syncthreads();
+            if (own) {
+                T up[NV], dn[NV];
+                slopes(2);
+                face_values(P, W0, S, up, dn);
+                half_step(P, dn, dU, dn);
+                half_step(P, up, dU, up);
+                __builtin_amdgcn_sched_barrier(0);
+                if (!pre) {
+                    // the z face below the plane; completes plane k-1
+                    T L[NV], R[NV], F[NV];
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) {
+                        L[slot<2>(q)] = zprev[q];
+                        R[slot<2>(q)] = dn[q];
+                    }
+                    glm_hlld(P, L, R, F);
+                    if (k > z0) {
+                        T U[NV];
+                        load9(plane(k - 1), P.n, col, U);
+                        T *o = out + (size_t)(k - 1) * (P.nx * P.ny);
+#pragma unroll
+                        for (int q = 0; q < NV; ++q) {
+                            U[q] = U[q] - P.c * (acc[q] + F[slot<2>(q)]);
+                            if (q == 8) U[q] *= P.damp;
+                            __builtin_nontemporal_store(
+                                U[q], reinterpret_cast<T *>(
+                                          reinterpret_cast<char *>(o + (size_t)q * P.n) + col));
+                        }
+                        if (speed_acc) {
+                            T W[NV];
+                            to_prim<true>(P, U, W);
+                            double sum = 0.0;
+#pragma unroll
+                            for (int d = 0; d < 3; ++d) {
+                                const double v = (double)fabs(W[1 + d]) +
+                                                 (double)fast_speed<true>(P, W, W[5 + d]);
+                                sum += v;
+                                dmax = fmax(dmax, v);
+                            }
+                            smax = fmax(smax, sum);
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) acc[q] = -F[slot<2>(q)];
+                }
+#pragma unroll
+                for (int q = 0; q < NV; ++q) zprev[q] = up[q];
+                __builtin_amdgcn_sched_barrier(0);
+                slopes(0);
+                face_values(P, W0, S, up1, dn);
+                half_step(P, dn, dU, dn);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) sm.f[q][xlo] = dn[q];
+                half_step(P, up1, dU, up1);
+                __builtin_amdgcn_sched_barrier(0);
+                slopes(1);
+                face_values(P, W0, S, up, dn);
+                half_step(P, dn, dU, dn);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) sm.f[slot<1>(q)][ylo] = dn[q];
+                half_step(P, up, dU, up);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) up2[slot<1>(q)] = up[q];
+            }
+            if (post) break;
+            __syncthreads();
+
+            // ---- the load of plane k+2, in flight through the solves of the
+            // cell's upper x and y faces; the column moves up
+            T Un[NV], R[NV];
+            const bool more = own && k + 2 <= z1 + 1;
+            if (more) load9(plane(k + 2), P.n, col, Un);
+            if (own && !pre) {
+#pragma unroll
+                for (int q = 0; q < NV; ++q) R[q] = sm.f[q][xhi];
+                glm_hlld(P, up1, R, up1);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) sm.f[q][xhi] = up1[q];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) R[q] = sm.f[q][yhi];
+                glm_hlld(P, up2, R, up2);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) sm.f[q][yhi] = up2[q];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (own) {
+#pragma unroll
+                for (int q = 0; q < NV; ++q) {
+                    Wm[q] = sm.w[q][ly][lx];
+                    sm.w[q][ly][lx] = Wp[q];
+                }
+                if (more) to_prim<false>(P, Un, Wp);
+            }
+            __syncthreads();
+        }
+    } else {
+        // ---- a ring column: its one face with the tile (an x face for the
+        // left and right columns, a y face for the bottom and top rows), whose
+        // left (lower) state the left and bottom columns hold and solve; and
+        // the halo cell behind it, the first four lanes a corner cell too
+        const int r = tid - Geo::NINT;
+        const bool own = r < 2 * (ax + ay);
+        const bool ring_x = r >= 2 * ax;
+        const int e = ring_x ? r - 2 * ax : r;
+        const bool far = e >= (ring_x ? ay : ax);             // right or top
+        const int at = far ? e - (ring_x ? ay : ax) : e;
+        const int ci = ring_x ? (far ? ax : -1) : at, cj = ring_x ? at : (far ? ay : -1);
+        const int hi = ring_x ? (far ? ax + 1 : -2) : at, hj = ring_x ? at : (far ? ay + 1 : -2);
+        const int ki = (r & 1) ? ax : -1, kj = (r & 2) ? ay : -1;
+        const bool corner = r < 4;
+        const int lx = ci + 2, ly = cj + 2;
+        const int dx = ring_x, dy = !ring_x;
+        const uint32_t col = own ? place(ci, cj) : 0, hcol = own ? place(hi, hj) : 0;
+        const uint32_t kcol = place(ki, kj);
+        const int face = ring_x ? Geo::xface(ci + !far, cj) : Geo::yface(ci, cj + !far);
+        T Wm[NV], Wp[NV], up1[NV];
+#pragma unroll
+        for (int q = 0; q < NV; ++q) Wm[q] = Wp[q] = up1[q] = T(0);
+        if (own) {
+            T Ub[NV], Uc[NV];
+            load9(plane(z0 - 1), P.n, col, Ub);
+            load9(plane(z0), P.n, col, Uc);
+            to_prim<false>(P, Uc, Wp);
+            to_prim<false>(P, Ub, Uc);
+#pragma unroll
+            for (int q = 0; q < NV; ++q) sm.w[q][ly][lx] = Uc[q];
+        }
+        __syncthreads();
+        for (int k = z0 - 1;; ++k) {
+            const bool pre = k < z0, post = k == z1;
+            const bool active = own && !pre && !post;
+            T W0[NV], S[NV], dU[NV];
+            if (active) {
+#pragma unroll
+                for (int q = 0; q < NV; ++q) dU[q] = T(0);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) {
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) {
+                        const T c = W0[q] = sm.w[q][ly][lx];
+                        if (d == 0) S[q] = limited_slope<LIM>(c - sm.w[q][ly][lx - 1], sm.w[q][ly][lx + 1] - c);
+                        else if (d == 1) S[q] = limited_slope<LIM>(c - sm.w[q][ly - 1][lx], sm.w[q][ly + 1][lx] - c);
+                        else S[q] = limited_slope<LIM>(c - Wm[q], Wp[q] - c);
+                    }
+                    T up[NV], dn[NV], Fu[NV], Fd[NV];
+                    face_values(P, W0, S, up, dn);
+                    if (d == 0) { phys_flux<0>(P, up, Fu); phys_flux<0>(P, dn, Fd); }
+                    else if (d == 1) { phys_flux<1>(P, up, Fu); phys_flux<1>(P, dn, Fd); }
+                    else { phys_flux<2>(P, up, Fu); phys_flux<2>(P, dn, Fd); }
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) dU[q] -= Fu[q] - Fd[q];
+                }
+            }
+            __syncthreads();
+            if (active) {
+                T up[NV], dn[NV];
+#pragma unroll
+                for (int q = 0; q < NV; ++q) {
+                    const T c = W0[q] = sm.w[q][ly][lx];
+                    S[q] = limited_slope<LIM>(c - sm.w[q][ly - dy][lx - dx], sm.w[q][ly + dy][lx + dx] - c);
+                }
+                face_values(P, W0, S, up, dn);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) up[q] = far ? dn[q] : up[q];
+                half_step(P, up, dU, up);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) up1[q] = up[q];
+                if (!ring_x) {
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) up1[slot<1>(q)] = up[q];
+                }
+                if (far) {
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) sm.f[q][face] = up1[q];
+                }
+            }
+            if (post) break;
+            __syncthreads();
+
+            T Un[NV], Hn[NV], Kn[NV];
+            const bool more = own && k + 2 <= z1, halo = own && k + 1 < z1;
+            if (more) load9(plane(k + 2), P.n, col, Un);
+            if (halo) load9(plane(k + 1), P.n, hcol, Hn);
+            if (halo && corner) load9(plane(k + 1), P.n, kcol, Kn);
+            if (active && !far) {
+                T R[NV];
+#pragma unroll
+                for (int q = 0; q < NV; ++q) R[q] = sm.f[q][face];
+                glm_hlld(P, up1, R, up1);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) sm.f[q][face] = up1[q];
+            }
+            if (own) {
+#pragma unroll
+                for (int q = 0; q < NV; ++q) {
+                    Wm[q] = sm.w[q][ly][lx];
+                    sm.w[q][ly][lx] = Wp[q];
+                }
+                if (more) to_prim<false>(P, Un, Wp);
+            }
+            if (halo) {
+                to_prim<false>(P, Hn, W0);
+#pragma unroll
+                for (int q = 0; q < NV; ++q) sm.w[q][hj + 2][hi + 2] = W0[q];
+                if (corner) {
+                    to_prim<false>(P, Kn, W0);
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) sm.w[q][kj + 2][ki + 2] = W0[q];
+                }
+            }
+            __syncthreads();
+        }
+    }
+    if (!speed_acc) return;
+    // block maxima: wave maxima by shuffles, then the first wave over the waves
+    for (int o = 32; o > 0; o >>= 1) {
+        smax = fmax(smax, __shfl_xor(smax, o));
+        dmax = fmax(dmax, __shfl_xor(dmax, o));
+    }
+    const int w = tid / 64;
+    if ((tid & 63) == 0) { sm.red[0][w] = smax; sm.red[1][w] = dmax; }
+    __syncthreads();
+    if (tid == 0) {
+        for (int q = 1; q < Geo::NT / 64; ++q) {
+            smax = fmax(smax, sm.red[0][q]);
+            dmax = fmax(dmax, sm.red[1][q]);
+        }
+        atomicMax(&speed_acc[0], (unsigned long long)__double_as_longlong(smax));
+        atomicMax(&speed_acc[1], (unsigned long long)__double_as_longlong(dmax));
+    }
+}
+
 // max over cells of sum_d (|u_d| + cf_d) and of max_d (|u_d| + cf_d): block
 // maxima through LDS, one atomicMax per block on the bit patterns of the
 // non-negative doubles (which order like the values)
@@ -597,18 +1139,33 @@ __global__ void k_params(T *dyn, const double *dt_dev, const double *ch_dev, dou
 
 size_t mhd_scratch_bytes(int dtype, int nx, int ny, int nz)
 {
-    const size_t n = (size_t)nx * ny * nz;
-    const size_t el = dtype == 0 ? 8 : 4;
-    // six face states of 9 values per cell, plus the step's device-side
-    // parameters
-    return 6 * 9 * n * el + 512;
+    // single precision: six face states of 9 values per cell, plus the step's
+    // device-side parameters
+    return dtype == 0 ? 0 : 6 * 9 * (size_t)nx * ny * nz * sizeof(float) + 512;
+}
+
+template <typename T, int LIM, int TX, int TY>
+static void launch_mhd_tiles(const mhd::Par<T> &P, const mhd::Dynamic &D, const MhdScalars &sc,
+                             const void *u_in, void *u_out, unsigned long long *acc, int num_cus,
+                             hipStream_t st)
+{
+    const int ntx = (P.nx + TX - 1) / TX, nty = (P.ny + TY - 1) / TY;
+    // z-ranges: as many as the chip holds workgroups, as long as that leaves
+    // four planes to a range (a range recomputes the plane below it and the
+    // plane above it)
+    const int resident = 2 * num_cus;
+    int nseg = std::max(1, resident / std::max(1, ntx * nty));
+    nseg = std::min(nseg, (P.nz + 3) / 4);
+    const int zlen = (P.nz + nseg - 1) / nseg;
+    nseg = (P.nz + zlen - 1) / zlen;
+    const int nitem = ntx * nty * nseg, per_xcd = (nitem + 7) / 8;
+    hipLaunchKernelGGL((mhd::k_step<T, LIM, TX, TY>), dim3(8 * per_xcd), dim3(tile_threads(TX, TY)), 0,
+                       st, P, D, sc.dt, sc.ch, (const T *)u_in, (T *)u_out, ntx, nty, zlen, nitem,
+                       per_xcd, acc);
 }
 
 template <typename T>
-static int run_mhd(int limiter, int nx, int ny, int nz, const void *u_in, void *u_out,
-                   const MhdScalars &sc, const double *dt_dev, const double *ch_dev, void *scratch,
-                   double cfl, double *dt_next, double *ch_next, unsigned long long *acc,
-                   hipStream_t st)
+static mhd::Par<T> make_par(int nx, int ny, int nz, const MhdScalars &sc)
 {
     mhd::Par<T> P{};
     P.nx = nx; P.ny = ny; P.nz = nz; P.n = nx * ny * nz;
@@ -616,8 +1173,37 @@ static int run_mhd(int limiter, int nx, int ny, int nz, const void *u_in, void *
     P.rho_floor = (T)sc.rho_floor; P.p_floor = (T)sc.p_floor;
     P.h = (T)(sc.dt / (2.0 * sc.dx));
     P.c = (T)(sc.dt / sc.dx);
-    P.ch = (T)sc.ch; P.ch2 = (T)(sc.ch * sc.ch);
+    P.ch = (T)sc.ch; P.ch2 = (T)(sc.ch * sc.ch); P.ich2 = (T)(1.0 / (2.0 * sc.ch));
     P.damp = (T)exp(-sc.alpha * sc.ch * sc.dt / sc.dx);
+    return P;
+}
+
+static int run_mhd_f64(int limiter, int nx, int ny, int nz, const void *u_in, void *u_out,
+                       const MhdScalars &sc, const double *dt_dev, const double *ch_dev, double cfl,
+                       double *dt_next, double *ch_next, unsigned long long *acc, int num_cus,
+                       hipStream_t st)
+{
+    const mhd::Par<double> P = make_par<double>(nx, ny, nz, sc);
+    const mhd::Dynamic D{ dt_dev, ch_dev, sc.dx, sc.alpha };
+    unsigned long long *a = dt_next || ch_next ? acc : nullptr;
+    switch (limiter) {
+    case 1: launch_mhd_tiles<double, 1, 24, 8>(P, D, sc, u_in, u_out, a, num_cus, st); break;
+    case 2: launch_mhd_tiles<double, 2, 24, 8>(P, D, sc, u_in, u_out, a, num_cus, st); break;
+    default: launch_mhd_tiles<double, 0, 24, 8>(P, D, sc, u_in, u_out, a, num_cus, st); break;
+    }
+    if (a)
+        hipLaunchKernelGGL(mhd::k_speeds_finish, dim3(1), dim3(64), 0, st, cfl, sc.dx, a, dt_next,
+                           ch_next);
+    return (int)hipGetLastError();
+}
+
+static int run_mhd_f32(int limiter, int nx, int ny, int nz, const void *u_in, void *u_out,
+                       const MhdScalars &sc, const double *dt_dev, const double *ch_dev,
+                       void *scratch, double cfl, double *dt_next, double *ch_next,
+                       unsigned long long *acc, hipStream_t st)
+{
+    using T = float;
+    const mhd::Par<T> P = make_par<T>(nx, ny, nz, sc);
     const size_t n = (size_t)P.n;
     T *fs = (T *)scratch;
     T *dyn = nullptr;
@@ -653,13 +1239,13 @@ static int run_mhd(int limiter, int nx, int ny, int nz, const void *u_in, void *
 int launch_mhd_step(int dtype, int limiter, int nx, int ny, int nz, const void *u_in, void *u_out,
                     const MhdScalars &sc, const double *dt_dev, const double *ch_dev,
                     void *scratch, double cfl, double *dt_next, double *ch_next,
-                    unsigned long long *acc, hipStream_t s)
+                    unsigned long long *acc, int num_cus, hipStream_t s)
 {
     if (dtype == 0)
-        return run_mhd<double>(limiter, nx, ny, nz, u_in, u_out, sc, dt_dev, ch_dev, scratch, cfl,
-                               dt_next, ch_next, acc, s);
-    return run_mhd<float>(limiter, nx, ny, nz, u_in, u_out, sc, dt_dev, ch_dev, scratch, cfl,
-                          dt_next, ch_next, acc, s);
+        return run_mhd_f64(limiter, nx, ny, nz, u_in, u_out, sc, dt_dev, ch_dev, cfl, dt_next,
+                           ch_next, acc, num_cus, s);
+    return run_mhd_f32(limiter, nx, ny, nz, u_in, u_out, sc, dt_dev, ch_dev, scratch, cfl, dt_next,
+                       ch_next, acc, s);
 }
 
 template <typename T>
