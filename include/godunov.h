@@ -249,7 +249,10 @@ int gd_get_config(gd_ctx *ctx, int dtype, int *shape_single, int *zlen_single,
  * zlen_single in [1, 4096];
  * zpolicy_batched in {0, 1, 2}. zlen_single is an upper bound: a patch that
  * would give fewer workgroups than the device holds at once is cut into
- * shorter z-ranges (down to one plane). The choice never changes results: every
+ * shorter z-ranges (down to one plane). The initial values (16x16 tiles with
+ * ranges of 32 planes for a single patch, 16x16 with policy 1 for a batch)
+ * stand for the library's own choice by the sizes of each call, and setting
+ * them returns to it. The choice never changes results: every
  * face flux and every update is evaluated by the same arithmetic whatever
  * the tiling, so outputs are bitwise identical across configurations. */
 int gd_set_config(gd_ctx *ctx, int dtype, int shape_single, int zlen_single, int shape_batched,
