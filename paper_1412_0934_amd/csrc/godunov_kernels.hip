@@ -93,7 +93,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_eu<T>()))) void step_kernel(
     godunov_tile<T, LIM, RS, TX, TY>(P, u_in, u_out, bflux, dtdx, lam, ph, x0, y0, z0, z1, sm, hits,
                                      want_cfl, smax);
     flush_hits(hits, hits_ctr);
-    if (want_cfl) cfl_block_max(smax, co.smax_bits);
+    if (want_cfl) cfl_finish(smax, co);
 }
 
 // A batch: a persistent grid; each workgroup pulls (patch, tile, z-range)
@@ -128,7 +128,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_eu<T>()))) void step_batched_kernel
         __syncthreads();
     }
     flush_hits(hits, hits_ctr);
-    if (want_cfl) cfl_block_max(smax, co.smax_bits);
+    if (want_cfl) cfl_finish(smax, co);
     if (threadIdx.x == 0) {
         __threadfence();
         unsigned done = atomicAdd(&queue[1], 1u);
@@ -179,7 +179,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_eu<T>()))) void step_batched_pair_k
         __syncthreads();
     }
     flush_hits(hits, hits_ctr);
-    if (want_cfl) cfl_block_max(smax, co.smax_bits);
+    if (want_cfl) cfl_finish(smax, co);
     if (threadIdx.x == 0) {
         __threadfence();
         unsigned done = atomicAdd(&queue[1], 1u);
@@ -193,9 +193,7 @@ __attribute__((amdgpu_waves_per_eu(waves_per_eu<T>()))) void step_batched_pair_k
 template <typename T>
 __global__ __launch_bounds__(256) void cfl_kernel(const PatchDesc *__restrict__ patches,
                                                   const CflItem *__restrict__ items, int nitems,
-                                                  const T *__restrict__ u, Scalars sc, double cfl,
-                                                  double *dt_out, unsigned long long *smax_bits,
-                                                  unsigned *done, unsigned long long *hits_ctr)
+                                                  const T *__restrict__ u, Scalars sc, CflOut co)
 {
     const Phys<T> ph = make_phys<T>(sc);
     double vmax = 0.0;
@@ -214,18 +212,12 @@ __global__ __launch_bounds__(256) void cfl_kernel(const PatchDesc *__restrict__ 
             vmax = fmax(vmax, cell_signal(U, ph, hits) * inv_dx);
         }
     }
-    (void)hits_ctr;
-    (void)cfl;
-    (void)dt_out;
-    (void)done;
-    cfl_block_max(vmax, smax_bits);
+    cfl_finish(vmax, co);
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void cfl_single_kernel(PatchDesc P, const T *__restrict__ u,
-                                                         Scalars sc, double cfl, double *dt_out,
-                                                         unsigned long long *smax_bits,
-                                                         unsigned *done)
+                                                         Scalars sc, CflOut co)
 {
     const Phys<T> ph = make_phys<T>(sc);
     const InputView view = make_view(P);
@@ -243,18 +235,30 @@ __global__ __launch_bounds__(256) void cfl_single_kernel(PatchDesc P, const T *_
         load5(base + view.plane(k) + view.column(i, j), view.vstride, U);
         vmax = fmax(vmax, cell_signal(U, ph, hits) * inv_dx);
     }
-    (void)cfl;
-    (void)dt_out;
-    (void)done;
-    cfl_block_max(vmax, smax_bits);
+    cfl_finish(vmax, co);
 }
 
 // ------------------------------------------------------------ launchers
 
+// The CFL output of a launch of `blocks` workgroups: with its completion
+// counter or without.
+static CflOut counted(CflOut co, int64_t blocks)
+{
+    if (blocks > CFL_COUNT_BLOCKS) co.done = nullptr;
+    return co;
+}
+
+static void finalize(const CflOut &co, hipStream_t s)
+{
+    if (co.dt_next && !co.done)
+        hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(64), 0, s, co.cfl, co.dt_next,
+                           co.smax_bits);
+}
+
 template <typename T, int LIM, int RS, int TX, int TY>
 static int launch_step_t(const PatchDesc &P, const void *u_in, void *u_out, void *bflux,
                          const double *dt_dev, const Scalars &sc, unsigned long long *hits,
-                         int zlen, int min_blocks, const CflOut &co, hipStream_t s)
+                         int zlen, int min_blocks, const CflOut &want, hipStream_t s)
 {
     const int ntx = (P.nx + TX - 1) / TX, nty = (P.ny + TY - 1) / TY;
     const int64_t ntiles = (int64_t)ntx * nty;
@@ -268,12 +272,11 @@ static int launch_step_t(const PatchDesc &P, const void *u_in, void *u_out, void
     const int nseg = (P.nz + zlen - 1) / zlen;
     const int64_t nblocks = (int64_t)ntx * nty * nseg;
     if (nblocks <= 0 || nblocks > 0x7fffffff) return (int)hipErrorInvalidValue;
+    const CflOut co = counted(want, nblocks);
     hipLaunchKernelGGL((step_kernel<T, LIM, RS, TX, TY>), dim3((unsigned)nblocks),
                        dim3(TileGeom<TX, TY>::NT), 0, s, P, (const T *)u_in, (T *)u_out, (T *)bflux,
                        dt_dev, sc, hits, ntx, nty, zlen, co);
-    if (co.dt_next)
-        hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(64), 0, s, co.cfl, co.dt_next,
-                           co.smax_bits);
+    finalize(co, s);
     return (int)hipGetLastError();
 }
 
@@ -281,14 +284,13 @@ template <typename T, int LIM, int RS, int TX, int TY>
 static int launch_batched_t(const PatchDesc *d_patches, const WorkItem *d_items, int nitems,
                             const void *u_in, void *u_out, void *bflux, const double *dt_dev,
                             const Scalars &sc, unsigned long long *hits, unsigned *d_queue,
-                            int grid, const CflOut &co, hipStream_t s)
+                            int grid, const CflOut &want, hipStream_t s)
 {
+    const CflOut co = counted(want, grid);
     hipLaunchKernelGGL((step_batched_kernel<T, LIM, RS, TX, TY>), dim3(grid),
                        dim3(TileGeom<TX, TY>::NT), 0, s, d_patches, d_items, nitems,
                        (const T *)u_in, (T *)u_out, (T *)bflux, dt_dev, sc, hits, d_queue, co);
-    if (co.dt_next)
-        hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(64), 0, s, co.cfl, co.dt_next,
-                           co.smax_bits);
+    finalize(co, s);
     return (int)hipGetLastError();
 }
 
@@ -311,14 +313,13 @@ template <typename T, int LIM, int RS, int TXB, int TYB>
 static int launch_batched_pair_t(const PatchDesc *d_patches, const WorkItem *d_items, int nitems,
                                  const void *u_in, void *u_out, void *bflux, const double *dt_dev,
                                  const Scalars &sc, unsigned long long *hits, unsigned *d_queue,
-                                 int grid, const CflOut &co, hipStream_t s)
+                                 int grid, const CflOut &want, hipStream_t s)
 {
+    const CflOut co = counted(want, grid);
     hipLaunchKernelGGL((step_batched_pair_kernel<T, LIM, RS, TXB, TYB>), dim3(grid),
                        dim3(pair_threads(TXB, TYB)), 0, s, d_patches, d_items, nitems,
                        (const T *)u_in, (T *)u_out, (T *)bflux, dt_dev, sc, hits, d_queue, co);
-    if (co.dt_next)
-        hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(64), 0, s, co.cfl, co.dt_next,
-                           co.smax_bits);
+    finalize(co, s);
     return (int)hipGetLastError();
 }
 
@@ -376,13 +377,14 @@ int launch_cfl(int dtype, const PatchDesc *d_patches, const CflItem *d_items, in
                const void *u, const Scalars &sc, double cfl, double *dt_out,
                unsigned long long *smax_bits, unsigned *done, int grid, hipStream_t s)
 {
+    const CflOut co = counted(CflOut{ cfl, dt_out, smax_bits, done }, grid);
     if (dtype == 1)
         hipLaunchKernelGGL(cfl_kernel<float>, dim3(grid), dim3(256), 0, s, d_patches, d_items,
-                           nitems, (const float *)u, sc, cfl, dt_out, smax_bits, done, nullptr);
+                           nitems, (const float *)u, sc, co);
     else
         hipLaunchKernelGGL(cfl_kernel<double>, dim3(grid), dim3(256), 0, s, d_patches, d_items,
-                           nitems, (const double *)u, sc, cfl, dt_out, smax_bits, done, nullptr);
-    hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(64), 0, s, cfl, dt_out, smax_bits);
+                           nitems, (const double *)u, sc, co);
+    finalize(co, s);
     return (int)hipGetLastError();
 }
 
@@ -394,13 +396,14 @@ int launch_cfl_single(int dtype, const PatchDesc &P, const void *u, const Scalar
     int64_t blocks = (ncell + 255) / 256;
     if (blocks > 2048) blocks = 2048;
     if (blocks < 1) blocks = 1;
+    const CflOut co = counted(CflOut{ cfl, dt_out, smax_bits, done }, blocks);
     if (dtype == 1)
         hipLaunchKernelGGL(cfl_single_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, s, P,
-                           (const float *)u, sc, cfl, dt_out, smax_bits, done);
+                           (const float *)u, sc, co);
     else
         hipLaunchKernelGGL(cfl_single_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, s, P,
-                           (const double *)u, sc, cfl, dt_out, smax_bits, done);
-    hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(64), 0, s, cfl, dt_out, smax_bits);
+                           (const double *)u, sc, co);
+    finalize(co, s);
     return (int)hipGetLastError();
 }
 

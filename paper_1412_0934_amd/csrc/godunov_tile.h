@@ -134,8 +134,9 @@ __device__ __forceinline__ double wave_max(double v)
 // non-negative double (which orders like the value). Thread 0 reads the
 // running value first and issues the device-wide atomic only when the
 // block's maximum exceeds it, so a grid of thousands of workgroups performs
-// few same-address atomics. A one-thread launch (cfl_finalize_kernel) then
-// turns the maximum into dt and clears it for the next use.
+// few same-address atomics. The maximum is turned into dt and cleared for the
+// next use by the last workgroup (cfl_finish) or by a one-thread launch
+// (cfl_finalize_kernel).
 __device__ void cfl_block_max(double v, unsigned long long *smax_bits)
 {
     __shared__ double part[16];
@@ -148,6 +149,23 @@ __device__ void cfl_block_max(double v, unsigned long long *smax_bits)
         for (int i = 0; i < (int)(blockDim.x + 63) / 64; ++i) m = fmax(m, part[i]);
         const unsigned long long b = (unsigned long long)__double_as_longlong(m);
         if (b > __atomic_load_n(smax_bits, __ATOMIC_RELAXED)) atomicMax(smax_bits, b);
+    }
+}
+
+// cfl_block_max, then (with a completion counter) the last workgroup's store
+// of dt. A block's maximum has reached the device's atomics before the block
+// counts itself, so the last one reads the maximum of all; no fence, which
+// would write back the caches.
+__device__ __forceinline__ void cfl_finish(double v, const CflOut &co)
+{
+    cfl_block_max(v, co.smax_bits);
+    if (co.done && threadIdx.x == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (atomicAdd(co.done, 1u) == gridDim.x - 1) {
+            const unsigned long long b = atomicExch(co.smax_bits, 0ull);
+            *co.dt_next = co.cfl / __longlong_as_double((long long)b);
+            atomicExch(co.done, 0u);
+        }
     }
 }
 
