@@ -177,30 +177,47 @@ class Context:
 _contexts: dict = {}
 
 
+# A call on a small patch is bound by this module's own work (13 us a call for
+# an 8^3 patch whose kernel takes 6), so the helpers of every call are kept
+# cheap: no availability query once a context exists, the stream handle
+# without a Stream object, pointers as plain integers, and the option records
+# (a function of their values alone, only read by the library) kept for reuse.
+
 def context(device=None) -> Context:
-    if not torch.cuda.is_available():
+    if not _contexts and not torch.cuda.is_available():
         raise RuntimeError("no GPU: the Godunov library has no CPU path")
     dev = torch.cuda.current_device() if device is None else int(device)
     key = (threading.get_ident(), dev)
-    if key not in _contexts:
-        _contexts[key] = Context(dev)
-    return _contexts[key]
+    ctx = _contexts.get(key)
+    if ctx is None:
+        ctx = _contexts[key] = Context(dev)
+    return ctx
+
+
+_opts_cache: dict = {}
 
 
 def _opts(dtype, periodic, limiter, riemann, rho_floor, p_floor) -> gd_opts:
     if dtype not in DTYPES:
         raise TypeError(f"unsupported dtype {dtype}")
-    return gd_opts(DTYPES[dtype], 1 if periodic else 0, LIMITERS[limiter], RIEMANN[riemann],
-                   float(rho_floor), float(p_floor))
+    key = (DTYPES[dtype], 1 if periodic else 0, LIMITERS[limiter], RIEMANN[riemann],
+           float(rho_floor), float(p_floor))
+    o = _opts_cache.get(key)
+    if o is None:
+        if len(_opts_cache) >= 256:
+            _opts_cache.clear()
+        o = _opts_cache[key] = gd_opts(*key)
+    return o
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _check_tensor(t, name, dtype=None):
@@ -313,9 +330,8 @@ def cfl_dt(u, gamma, dx, cfl=0.5, *, ng=2, periodic=False, out=None, rho_floor=R
     _check_scalar(out, "out")
     ctx = context(u.device.index)
     o = _opts(u.dtype, periodic, "minmod", "hllc", rho_floor, p_floor)
-    desc = np.zeros(1, dtype=PATCH_DTYPE)
-    desc[0] = (nx, ny, nz, 0 if periodic else ng, 0, 0, -1, float(dx), 0.0)
-    ctx.check(ctx.lib.cfl_dt(ctx.handle, ctypes.byref(o), 1, desc.ctypes.data, _ptr(u),
+    desc = gd_patch(nx, ny, nz, 0 if periodic else ng, 0, 0, -1, float(dx), 0.0)
+    ctx.check(ctx.lib.cfl_dt(ctx.handle, ctypes.byref(o), 1, ctypes.addressof(desc), _ptr(u),
                              float(gamma), float(cfl), _ptr(out), _stream(stream)))
     return out
 
