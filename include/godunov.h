@@ -197,7 +197,7 @@ int godunov_step_batched_cfl(gd_ctx *ctx, const gd_opts *opts, int npatch,
  * the derivative of the branch the forward step takes is used. Every
  * element of lam_in is written exactly once (gather form, deterministic).
  * GD_F64 only (GD_E_UNSUPPORTED otherwise); lam_in must not overlap any
- * input (GD_E_ARG). The library keeps a device scratch of 324 bytes per
+ * input (GD_E_ARG). The library keeps a device scratch of 164 bytes per
  * cell of the scratch box -- the box itself when periodic, the box extended
  * by two layers, (nx+4)(ny+4)(nz+4), when ghosted -- grown on first use
  * (the growth synchronises the device; GD_E_NOMEM if it fails); boxes whose

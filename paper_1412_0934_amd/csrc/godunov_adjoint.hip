@@ -5,22 +5,18 @@
 // which depends on the primitive state of the cell and its limited slopes.
 // The adjoint runs the chain backwards in gather form -- every output value
 // is a sum written by exactly one thread, in a fixed order, with no atomics
-// -- so it is bitwise deterministic. Three kernels share a scratch area over
-// the cells whose predicted states the step uses: the extended box
-// [-2, n+2)^3 of a ghosted patch, or the periodic box itself, whose
-// neighbours wrap (x fastest):
-//   1 predict  per predicted cell: primitives of its 7-point stencil (from
-//              U), limited slopes S, predicted state W*, and a 2-bit code per
-//              slope recording the limiter branch taken
-//   2 cells    per 16x16 column tile of predicted cells, marching up a
-//              z-range: for every face of a plane of the tile, dL/dF = dt/dx
-//              (lam_right - lam_left) (+ dL/dbflux on the patch boundary),
-//              reversed through the Riemann solver and the face floors; the x
-//              and y faces go through LDS (faces on a tile border are
-//              evaluated by both tiles), the z face above a cell stays in
-//              registers and serves the plane above as its lower face; then
-//              per cell the reverse predictor: dL/dW (direct part) and dL/dS
-//   3 input    per input cell: dL/dW gathered from its own predictor term
+// -- so it is bitwise deterministic. Two kernels share a scratch area over the
+// cells whose predicted states the step uses: the extended box [-2, n+2)^3 of a
+// ghosted patch, or the periodic box itself, whose neighbours wrap (x fastest):
+//   1 march    per 24x8 column tile of predicted cells and z-range: the step's
+//              tile march (godunov_tile.h) with the reverse of each face in
+//              place of its flux -- slopes, predicted state and face states
+//              from the staged primitives, dL/dF = dt/dx (lam_right - lam_left)
+//              (+ dL/dbflux on the patch boundary) reversed through the Riemann
+//              solver and the face floors by the owner of the face's lower cell
+//              -- then per cell the reverse predictor: dL/dW (direct part),
+//              dL/dS, and a 2-bit code per slope recording the limiter branch;
+//   2 input    per input cell: dL/dW gathered from its own predictor term
 //              and the slope adjoints of itself and its neighbours split by
 //              the recorded branches, reversed through the primitive
 //              conversion, plus the identity term lam_out.
@@ -30,6 +26,7 @@
 // whose scratch arrays would not fit.
 #include "godunov_internal.h"
 #include "godunov_math.h"
+#include "godunov_tile.h"
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -43,10 +40,9 @@ namespace adj {
 enum { LIM_MINMOD = 0, LIM_MC = 1, LIM_NONE = 2 };
 enum { RS_HLLC = 0, RS_HLL = 1 };
 
-// column tile of the cells kernel (one thread per column) and its x and y
-// face slots per plane
-constexpr int CTX = 16, CTY = 16, CT = CTX * CTY;
-constexpr int NXF = (CTX + 1) * CTY, NYF = CTX * (CTY + 1);
+// column tile of the march: its columns, then a wave of ring columns
+constexpr int CTX = 24, CTY = 8;
+using Tile = TileGeom<CTX, CTY>;
 
 struct Geo {
     int nx, ny, nz, ng, periodic;
@@ -57,7 +53,7 @@ struct Geo {
     int vin;                   // input variable stride
     int gx, gy, gz;            // input extents
     int nint;                  // interior cells
-    int ntx, nty, nseg, zlen;  // tiles and z-segments of the cells kernel
+    int ntx, nty, nseg, zlen;  // tiles and z-segments of the march
     int nitem, per_xcd;        // its work items, and items per XCD slice
     double gamma, inv_gm1, rho_floor, p_floor, lam, c;   // lam = dt/(2dx), c = dt/dx
 };
@@ -68,15 +64,12 @@ struct Geo {
 // fields of those cells lie in one 10 KB span. Records are written with
 // streaming (non-temporal) stores: the next kernel reads them long after.
 constexpr int NF = 20;
-// fields of the forward record: slopes S at d*5+q, predicted state W* at 15+q
-constexpr int F_S = 0, F_WS = 15;
-// fields of the adjoint record: dL/dS at d*5+q, direct dL/dW at 15+q
+// fields: dL/dS at d*5+q, direct dL/dW at 15+q
 constexpr int F_SB = 0, F_WD = 15;
 
 __device__ __forceinline__ int rec(int e, int f) { return ((e >> 6) * NF + f) * 64 + (e & 63); }
 
 struct Scratch {
-    double *fw;        // forward record of each extended cell
     double *ad;        // adjoint record of each extended cell
     unsigned *code;    // [E] limiter branch per slope, 2 bits at 2(d*5+q)
 };
@@ -119,16 +112,6 @@ __device__ __forceinline__ int ext(const Geo &g, int i, int j, int k)
     return ((k + 2) * g.ey + (j + 2)) * g.ex + (i + 2);
 }
 
-// position of cell (i, j, k) of the extended box in the input array
-__device__ __forceinline__ int in_index(const Geo &g, int i, int j, int k)
-{
-    if (g.periodic) {
-        i = wrap(i, g.nx); j = wrap(j, g.ny); k = wrap(k, g.nz);
-        return (k * g.ny + j) * g.nx + i;
-    }
-    return ((k + g.ng) * g.gy + (j + g.ng)) * g.gx + (i + g.ng);
-}
-
 __device__ __forceinline__ int interior_index(const Geo &g, int i, int j, int k)
 {
     return (k * g.ny + j) * g.nx + i;
@@ -146,28 +129,6 @@ __device__ __forceinline__ void to_prim(const Geo &g, const double U[5], double 
     double p = (g.gamma - 1.0) * (U[4] - kin);
     if (p < g.p_floor) p = g.p_floor;
     W[0] = rho; W[1] = u; W[2] = v; W[3] = w; W[4] = p;
-}
-
-__device__ __forceinline__ void load_prim(const Geo &g, const double *__restrict__ u, int i, int j,
-                                          int k, double W[5], double &inv_rho)
-{
-    const int p = in_index(g, i, j, k);
-    double U[5];
-    for (int q = 0; q < 5; ++q) U[q] = u[p + q * g.vin];
-    to_prim(g, U, W, inv_rho);
-}
-
-template <int LIM>
-__device__ __forceinline__ double slope(double a, double b)
-{
-    if (LIM == LIM_NONE) return 0.5 * (a + b);
-    bool same = (a > 0.0 && b > 0.0) || (a < 0.0 && b < 0.0);
-    if (!same) return 0.0;
-    if (LIM == LIM_MINMOD) return fabs(a) <= fabs(b) ? a : b;
-    double m1 = 2.0 * fabs(a), m2 = 2.0 * fabs(b), m3 = 0.5 * fabs(a + b);
-    double m = m1 <= m2 ? m1 : m2;
-    m = m <= m3 ? m : m3;
-    return a > 0.0 ? m : -m;
 }
 
 // Branch of a limited slope: 0 zero slope, 1 the a-branch, 2 the b-branch,
@@ -195,61 +156,22 @@ __device__ __forceinline__ void branch_partials(unsigned br, double &pa, double 
     pb = br == 2u ? one : (br == 3u ? 0.5 : 0.0);
 }
 
-// ------------------------------------------------------------ 1: predict
-
-template <int LIM>
-__global__ __launch_bounds__(256) void k_predict(Geo g, const double *__restrict__ u, Scratch s)
-{
-    // predicted cells lie in [lo, lo + p)^3
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= g.px * g.py * g.pz) return;
-    const int i = t % g.px + g.lo, r = t / g.px;
-    const int j = r % g.py + g.lo, k = r / g.py + g.lo;
-    if (!is_predicted(g, i, j, k)) return;
-    const int e = ext(g, i, j, k);
-    double W[5], S[3][5], inv_rho, dummy;
-    load_prim(g, u, i, j, k, W, inv_rho);
-    unsigned code = 0u;
-    for (int d = 0; d < 3; ++d) {
-        double Wm[5], Wp[5];
-        load_prim(g, u, i - (d == 0), j - (d == 1), k - (d == 2), Wm, dummy);
-        load_prim(g, u, i + (d == 0), j + (d == 1), k + (d == 2), Wp, dummy);
-        for (int q = 0; q < 5; ++q) {
-            const double a = W[q] - Wm[q], b = Wp[q] - W[q];
-            S[d][q] = slope<LIM>(a, b);
-            code |= slope_branch<LIM>(a, b) << (2 * (d * 5 + q));
-            __builtin_nontemporal_store(S[d][q], &s.fw[rec(e, F_S + d * 5 + q)]);
-        }
-    }
-    s.code[e] = code;
-    const double divu = S[0][1] + S[1][2] + S[2][3];
-    double adv[5];
-    for (int q = 0; q < 5; ++q) adv[q] = W[1] * S[0][q] + W[2] * S[1][q] + W[3] * S[2][q];
-    double Ws[5];
-    Ws[0] = W[0] - g.lam * (adv[0] + W[0] * divu);
-    Ws[1] = W[1] - g.lam * (adv[1] + S[0][4] * inv_rho);
-    Ws[2] = W[2] - g.lam * (adv[2] + S[1][4] * inv_rho);
-    Ws[3] = W[3] - g.lam * (adv[3] + S[2][4] * inv_rho);
-    Ws[4] = W[4] - g.lam * (adv[4] + g.gamma * W[4] * divu);
-    for (int q = 0; q < 5; ++q) __builtin_nontemporal_store(Ws[q], &s.fw[rec(e, F_WS + q)]);
-}
-
 // ------------------------------------------------------------ Riemann adjoints
 
 // Forward quantities of the HLLC / HLL flux in rotated form, kept for the
-// reverse sweep.
+// reverse sweep; y = 1 / sqrt(gamma p rho).
 struct Fwd {
-    double cL, cR, SL, SR, iL0, iR0, iL4, iR4;
+    double yL, yR, cL, cR, SL, SR;
     bool slL, srL;      // S_L took the left candidate, S_R the left candidate
 };
 
 __device__ __forceinline__ void speeds(double g, const double L[5], const double R[5], Fwd &f)
 {
-    f.iL0 = fast_rcp(L[0]); f.iR0 = fast_rcp(R[0]);
-    f.iL4 = fast_rcp(L[4]); f.iR4 = fast_rcp(R[4]);
     const double gl = g * L[4], gr = g * R[4];
-    f.cL = gl * fast_rsqrt(gl * L[0]);
-    f.cR = gr * fast_rsqrt(gr * R[0]);
+    f.yL = fast_rsqrt(gl * L[0]);
+    f.yR = fast_rsqrt(gr * R[0]);
+    f.cL = gl * f.yL;
+    f.cR = gr * f.yR;
     double a = L[1] - f.cL, b = R[1] - f.cR;
     f.slL = a <= b;
     f.SL = f.slL ? a : b;
@@ -258,18 +180,19 @@ __device__ __forceinline__ void speeds(double g, const double L[5], const double
     f.SR = f.srL ? c : d;
 }
 
-__device__ __forceinline__ void speeds_adjoint(const Fwd &f, double SLb, double SRb, double Lb[5],
-                                               double Rb[5])
+__device__ __forceinline__ void speeds_adjoint(double g, const Fwd &f, double SLb, double SRb,
+                                               double Lb[5], double Rb[5])
 {
-    double cLb = 0.0, cRb = 0.0;
-    if (f.slL) { Lb[1] += SLb; cLb -= SLb; } else { Rb[1] += SLb; cRb -= SLb; }
-    if (f.srL) { Lb[1] += SRb; cLb += SRb; } else { Rb[1] += SRb; cRb += SRb; }
-    // c = sqrt(g p / rho): dc = c/2 (dp/p - drho/rho)
-    const double hl = 0.5 * cLb * f.cL, hr = 0.5 * cRb * f.cR;
-    Lb[4] += hl * f.iL4;
-    Lb[0] -= hl * f.iL0;
-    Rb[4] += hr * f.iR4;
-    Rb[0] -= hr * f.iR0;
+    const double sl = f.slL ? SLb : 0.0, sr = f.srL ? SRb : 0.0;
+    Lb[1] += sl + sr;
+    Rb[1] += (SLb - sl) + (SRb - sr);
+    const double hl = 0.5 * (sr - sl), hr = 0.5 * ((SRb - sr) - (SLb - sl));
+    // c = sqrt(g p / rho): dc/dp = c / (2p) = g y / 2, dc/drho = -c / (2 rho)
+    // = -c^2 y / 2
+    Lb[4] += hl * (g * f.yL);
+    Lb[0] -= hl * (f.cL * f.cL * f.yL);
+    Rb[4] += hr * (g * f.yR);
+    Rb[0] -= hr * (f.cR * f.cR * f.yR);
 }
 
 // Adjoint of the physical flux and of the conserved vector of a rotated
@@ -311,82 +234,81 @@ __device__ __forceinline__ void phys_flux(double inv_gm1, const double W[5], dou
     U[0] = r; U[1] = r * u; U[2] = r * v; U[3] = r * w; U[4] = E;
 }
 
+// Reverse of the HLLC flux in the form the step evaluates it: the physical flux
+// of the star state of the side K the face lies on, (a S, a S^2 + p*, a S v_K,
+// a S w_K, S (E* + p*)) with m = rho_K (S_K - u_K), a = m / (S_K - S), p* =
+// p_K + m (S - u_K), E* = ((S_K - u_K) E_K - p_K u_K + p* S) / (S_K - S); S is
+// S* in the star regions and u_K in the upwind ones, where the flux no longer
+// depends on the wave speeds. One path for all regions, a third fewer
+// operations than through F_K + S_K (U*_K - U_K), and 4 of 7 reciprocals gone.
 __device__ __forceinline__ void hllc_adjoint(double g, double inv_gm1, const double L[5],
                                              const double R[5], const double Fb[5], double Lb[5],
                                              double Rb[5])
 {
     Fwd f;
     speeds(g, L, R, f);
-    const double zero[5] = { 0, 0, 0, 0, 0 };
-    if (f.SL >= 0.0) { flux_cons_adjoint(inv_gm1, L, Fb, zero, Lb); return; }
-    const double mL = L[0] * (f.SL - L[1]);
-    const double mR = R[0] * (f.SR - R[1]);
-    const double num = R[4] - L[4] + mL * L[1] - mR * R[1];
-    const double den = mL - mR;
-    const double iden = fast_rcp(den);
-    const double Sst = num * iden;
-    bool left;
-    if (Sst >= 0.0) left = true;
-    else if (f.SR > 0.0) left = false;
-    else { flux_cons_adjoint(inv_gm1, R, Fb, zero, Rb); return; }
+    const double dL = f.SL - L[1], dR = f.SR - R[1];
+    const double mL = L[0] * dL, mR = R[0] * dR;
+    const double iden = fast_rcp(mL - mR);
+    const double Sst = (R[4] - L[4] + mL * L[1] - mR * R[1]) * iden;
+    const bool supL = f.SL >= 0.0;
+    const bool left = supL || Sst >= 0.0;
+    const bool star = !supL && (left || f.SR > 0.0);
+    const double r = left ? L[0] : R[0], u = left ? L[1] : R[1], v = left ? L[2] : R[2];
+    const double w = left ? L[3] : R[3], p = left ? L[4] : R[4];
+    const double SK = left ? f.SL : f.SR, m = left ? mL : mR;
+    const double S = star ? Sst : u;
+    const double dK = SK - u, t = S - u;
+    const double id = fast_rcp(SK - S);
+    const double q2 = u * u + v * v + w * w;
+    const double EK = p * inv_gm1 + 0.5 * r * q2;
+    const double ps = p + m * t;
+    const double Es = id * (dK * EK - p * u + ps * S);
+    const double a = m * id, mass = a * S;
 
-    // the star state on the side of the contact the face lies on; values
-    // are selected (not pointers), so that everything stays in registers
-    double K[5], Kb[5] = { 0, 0, 0, 0, 0 };
-    for (int q = 0; q < 5; ++q) K[q] = left ? L[q] : R[q];
-    const double SK = left ? f.SL : f.SR, mK = left ? mL : mR;
-    const double iK0 = left ? f.iL0 : f.iR0;
-    double FK[5], UK[5];
-    phys_flux(inv_gm1, K, FK, UK);
-    const double d = SK - Sst;
-    const double id = fast_rcp(d), imK = fast_rcp(mK);
-    const double a = mK * id;
-    const double t1 = Sst - K[1], t2 = Sst + K[4] * imK;
-    const double e = UK[4] * iK0 + t1 * t2;
-    const double Us[5] = { a, a * Sst, a * K[2], a * K[3], a * e };
-
-    // F = F_K + S_K (U* - U_K)
-    double SKb = 0.0, UKb[5], Usb[5];
-    for (int q = 0; q < 5; ++q) {
-        SKb += Fb[q] * (Us[q] - UK[q]);
-        Usb[q] = SK * Fb[q];
-        UKb[q] = -SK * Fb[q];
-    }
-    // U* = a (1, S*, v, w, e)
-    double ab = Usb[0] + Usb[1] * Sst + Usb[2] * K[2] + Usb[3] * K[3] + Usb[4] * e;
-    double Sstb = a * Usb[1];
-    Kb[2] += a * Usb[2];
-    Kb[3] += a * Usb[3];
-    double eb = a * Usb[4];
-    // e = E_K / rho_K + t1 t2
-    UKb[4] += eb * iK0;
-    Kb[0] -= eb * UK[4] * iK0 * iK0;
-    Sstb += eb * (t1 + t2);
-    Kb[1] -= eb * t2;
-    Kb[4] += eb * t1 * imK;
-    double mKb = -eb * t1 * K[4] * imK * imK;
-    // a = m_K / (S_K - S*)
-    mKb += ab * id;
-    double db = -ab * a * id;
-    SKb += db;
-    Sstb -= db;
-    flux_cons_adjoint(inv_gm1, K, Fb, UKb, Kb);
-    for (int q = 0; q < 5; ++q) {
-        Lb[q] += left ? Kb[q] : 0.0;
-        Rb[q] += left ? 0.0 : Kb[q];
-    }
-
-    double SLb = 0.0, SRb = 0.0, mLb = 0.0, mRb = 0.0;
-    if (left) { SLb += SKb; mLb += mKb; } else { SRb += SKb; mRb += mKb; }
-    // S* = num / den
-    double numb = Sstb * iden, denb = -Sstb * Sst * iden;
-    Rb[4] += numb; Lb[4] -= numb;
-    mLb += numb * L[1] + denb; Lb[1] += numb * mL;
-    mRb -= numb * R[1] + denb; Rb[1] -= numb * mR;
-    // m_K = rho_K (S_K - u_K)
-    Lb[0] += mLb * (f.SL - L[1]); SLb += mLb * L[0]; Lb[1] -= mLb * L[0];
-    Rb[0] += mRb * (f.SR - R[1]); SRb += mRb * R[0]; Rb[1] -= mRb * R[0];
-    speeds_adjoint(f, SLb, SRb, Lb, Rb);
+    // the flux: mass, mass S + p*, mass v, mass w, S (E* + p*)
+    const double eb = Fb[4] * S;
+    double psb = eb + Fb[1];
+    const double massb = Fb[0] + Fb[1] * S + Fb[2] * v + Fb[3] * w;
+    double Sb = Fb[4] * (Es + ps) + Fb[1] * mass;
+    double vb = Fb[2] * mass, wb = Fb[3] * mass;
+    // E* = id N
+    const double Nb = eb * id;
+    double dKb = Nb * EK;
+    const double EKb = Nb * dK;
+    psb += Nb * S;
+    Sb += Nb * ps;
+    // mass = a S, a = m id, id = 1 / (S_K - S)
+    const double ab = massb * S;
+    Sb += massb * a;
+    const double db = -id * (eb * Es + ab * a);
+    // p* = p + m (S - u)
+    const double mb = ab * id + psb * t;
+    Sb += psb * m - db;
+    // m = r (S_K - u)
+    dKb += mb * r;
+    const double h = EKb * r;
+    const double rb = EKb * 0.5 * q2 + mb * dK;
+    double ub = h * u - Nb * p - psb * m - dKb;
+    const double pb = psb - Nb * u + EKb * inv_gm1;
+    vb += h * v;
+    wb += h * w;
+    ub += star ? 0.0 : Sb;
+    const double SKb = star ? db + dKb : 0.0;
+    // S* = num / den, num = p_R - p_L + m_L u_L - m_R u_R, den = m_L - m_R
+    const double numb = star ? Sb * iden : 0.0, denb = -numb * S;
+    const double mLb = numb * L[1] + denb, mRb = -(numb * R[1] + denb);
+    Lb[0] = mLb * dL + (left ? rb : 0.0);
+    Lb[1] = numb * mL - mLb * L[0] + (left ? ub : 0.0);
+    Lb[2] = left ? vb : 0.0;
+    Lb[3] = left ? wb : 0.0;
+    Lb[4] = (left ? pb : 0.0) - numb;
+    Rb[0] = mRb * dR + (left ? 0.0 : rb);
+    Rb[1] = (left ? 0.0 : ub) - numb * mR - mRb * R[0];
+    Rb[2] = left ? 0.0 : vb;
+    Rb[3] = left ? 0.0 : wb;
+    Rb[4] = (left ? 0.0 : pb) + numb;
+    speeds_adjoint(g, f, mLb * L[0] + (left ? SKb : 0.0), mRb * R[0] + (left ? 0.0 : SKb), Lb, Rb);
 }
 
 __device__ __forceinline__ void hll_adjoint(double g, double inv_gm1, const double L[5],
@@ -418,320 +340,460 @@ __device__ __forceinline__ void hll_adjoint(double g, double inv_gm1, const doub
     SLb -= Db;
     flux_cons_adjoint(inv_gm1, L, FLb, ULb, Lb);
     flux_cons_adjoint(inv_gm1, R, FRb, URb, Rb);
-    speeds_adjoint(f, SLb, SRb, Lb, Rb);
+    speeds_adjoint(g, f, SLb, SRb, Lb, Rb);
 }
 
-// dL/dU' of cell (i, j, k), zero for cells outside the patch interior
-// (which have no update)
-__device__ __forceinline__ void lam_at(const Geo &g, const double *__restrict__ lam_out, int i,
-                                       int j, int k, double L[5])
+// Reverse of the flux through a face, all in the rotated order of its axis: from
+// dL/dF and the face states before the floors (raised here) to their adjoints.
+template <int RS>
+__device__ __forceinline__ void face_reverse(const Geo &g, double L[5], double R[5],
+                                             const double Fb[5], double Lb[5], double Rb[5])
 {
-    const bool in = g.periodic || (i >= 0 && i < g.nx && j >= 0 && j < g.ny && k >= 0 && k < g.nz);
-    const int c = g.periodic ? ext(g, i, j, k) : (in ? interior_index(g, i, j, k) : 0);
-    for (int q = 0; q < 5; ++q) L[q] = in ? lam_out[q * g.nint + c] : 0.0;
+    const bool flL0 = L[0] < g.rho_floor, flL4 = L[4] < g.p_floor;
+    const bool flR0 = R[0] < g.rho_floor, flR4 = R[4] < g.p_floor;
+    if (flL0) L[0] = g.rho_floor;
+    if (flL4) L[4] = g.p_floor;
+    if (flR0) R[0] = g.rho_floor;
+    if (flR4) R[4] = g.p_floor;
+    for (int q = 0; q < 5; ++q) Lb[q] = Rb[q] = 0.0;
+    if (RS == RS_HLL) hll_adjoint(g.gamma, g.inv_gm1, L, R, Fb, Lb, Rb);
+    else hllc_adjoint(g.gamma, g.inv_gm1, L, R, Fb, Lb, Rb);
+    if (flL0) Lb[0] = 0.0;
+    if (flL4) Lb[4] = 0.0;
+    if (flR0) Rb[0] = 0.0;
+    if (flR4) Rb[4] = 0.0;
 }
 
-// Adjoint of the two face states WL, WR (before the floors) of the face
-// along D whose right cell is (i, j, k) and left cell (i, j, k) - e_D, whose
-// updates have adjoints lamL and lamR: dL/dF reversed through the Riemann
-// solver and the face-state floors, in unrotated variables.
-template <int RS, int D>
-__device__ __forceinline__ void face_adjoint(const Geo &g, int i, int j, int k, double WL[5],
-                                             double WR[5], const double lamL[5],
-                                             const double lamR[5],
-                                             const double *__restrict__ lam_bflux, double WLb[5],
-                                             double WRb[5])
-{
-    constexpr int nt1 = 1 + (D + 1) % 3, nt2 = 1 + (D + 2) % 3, nn = 1 + D;
-    const bool flL0 = WL[0] < g.rho_floor, flL4 = WL[4] < g.p_floor;
-    const bool flR0 = WR[0] < g.rho_floor, flR4 = WR[4] < g.p_floor;
-    if (flL0) WL[0] = g.rho_floor;
-    if (flL4) WL[4] = g.p_floor;
-    if (flR0) WR[0] = g.rho_floor;
-    if (flR4) WR[4] = g.p_floor;
+// Position of component q in the rotated order of axis D.
+template <int D>
+__device__ constexpr int rot(int q) { return q == 0 || q == 4 ? q : 1 + (q - 1 - D + 3) % 3; }
 
-    // dL/dF: the right cell's update has -c F(face), the left cell's +c F
-    double Fb[5];
-    for (int q = 0; q < 5; ++q) Fb[q] = g.c * lamR[q] - g.c * lamL[q];
+// dL/dbflux of face fi of axis D (of n_d cells), at sheet position `at`, added
+// to dL/dF in rotated order. Faces 0 and n of a periodic box are one face: both
+// sheets hold its flux.
+template <int D>
+__device__ __forceinline__ void add_bflux(const Geo &g, const double *__restrict__ lam_bflux, int fi,
+                                          int at, double Fb[5])
+{
     const int n_d = D == 0 ? g.nx : (D == 1 ? g.ny : g.nz);
-    const int fi = D == 0 ? i : (D == 1 ? j : k);
-    if (lam_bflux && (fi == 0 || fi == n_d)) {
-        const int sxs = g.nz * g.ny, sys = g.nz * g.nx, szs = g.ny * g.nx;
-        const int base = D == 0 ? 0 : (D == 1 ? 10 * sxs : 10 * sxs + 10 * sys);
-        const int size = D == 0 ? sxs : (D == 1 ? sys : szs);
-        const int slow = D == 2 ? j : k, fast = D == 0 ? j : i;
-        const int nfast = D == 0 ? g.ny : g.nx;
-        const int at = slow * nfast + fast;
-        // faces 0 and n of a periodic box are one face: both sheets hold its flux
-        if (fi == 0 || g.periodic)
-            for (int q = 0; q < 5; ++q) Fb[q] += lam_bflux[base + q * size + at];
-        if (fi == n_d || g.periodic)
-            for (int q = 0; q < 5; ++q) Fb[q] += lam_bflux[base + 5 * size + q * size + at];
-    }
-
-    // rotate, reverse the Riemann solver, rotate back
-    const double L[5] = { WL[0], WL[nn], WL[nt1], WL[nt2], WL[4] };
-    const double R[5] = { WR[0], WR[nn], WR[nt1], WR[nt2], WR[4] };
-    const double Gb[5] = { Fb[0], Fb[nn], Fb[nt1], Fb[nt2], Fb[4] };
-    double Lb[5] = { 0, 0, 0, 0, 0 }, Rb[5] = { 0, 0, 0, 0, 0 };
-    if (RS == RS_HLL) hll_adjoint(g.gamma, g.inv_gm1, L, R, Gb, Lb, Rb);
-    else hllc_adjoint(g.gamma, g.inv_gm1, L, R, Gb, Lb, Rb);
-    WLb[0] = flL0 ? 0.0 : Lb[0]; WLb[4] = flL4 ? 0.0 : Lb[4];
-    WRb[0] = flR0 ? 0.0 : Rb[0]; WRb[4] = flR4 ? 0.0 : Rb[4];
-    WLb[nn] = Lb[1]; WLb[nt1] = Lb[2]; WLb[nt2] = Lb[3];
-    WRb[nn] = Rb[1]; WRb[nt1] = Rb[2]; WRb[nt2] = Rb[3];
+    if (!lam_bflux || (fi != 0 && fi != n_d)) return;
+    const int sxs = g.nz * g.ny, sys = g.nz * g.nx, szs = g.ny * g.nx;
+    const int base = D == 0 ? 0 : (D == 1 ? 10 * sxs : 10 * sxs + 10 * sys);
+    const int size = D == 0 ? sxs : (D == 1 ? sys : szs);
+    if (fi == 0 || g.periodic)
+        for (int q = 0; q < 5; ++q) Fb[rot<D>(q)] += lam_bflux[base + q * size + at];
+    if (fi == n_d || g.periodic)
+        for (int q = 0; q < 5; ++q) Fb[rot<D>(q)] += lam_bflux[base + 5 * size + q * size + at];
 }
 
-// ------------------------------------------------------------ 2: cells
+// ------------------------------------------------------------ 1: march
 
-// LDS of the cells kernel, for the x faces of one plane of the tile (and
-// likewise for y): per cell of the row range [-1, CTX] (the tile and one
-// halo cell on each side), plus[q] = W* + S_x/2, the left state of its upper
-// face, and minus[q] = W* - S_x/2, the right state of its lower face. Each
-// face task reads the plus state of its left cell and the minus state of
-// its right cell and overwrites both with their adjoints; no other task
-// touches them, so afterwards a cell finds the adjoints of its own two face
-// states in its own slots.
-// lam holds dL/dU' of the tile and its one-deep x and y halo, at tile
-// coordinates + 1.
-constexpr int XW = CTX + 2, YW = CTY + 2;
-struct CellsSmem {
-    double xp[5][CTY][XW], xm[5][CTY][XW];
-    double yp[5][YW][CTX], ym[5][YW][CTX];
-    double lam[5][YW][XW];
+// A column of cells: its offsets within a plane of the input and of the
+// interior arrays, and how far outside the patch it lies along x and y.
+struct Column {
+    int in, inner;
+    int di, dj;
+    bool inside;
 };
 
-// A face along D exists when its index along D lies in [0, n_D] and the
-// other two coordinates of its right cell are inside the patch.
-template <int D>
-__device__ __forceinline__ bool face_exists(const Geo &g, int i, int j, int k)
+__device__ __forceinline__ Column make_column(const Geo &g, int i, int j)
 {
-    const int c3[3] = { i, j, k }, n3[3] = { g.nx, g.ny, g.nz };
-    bool ok = c3[D] >= 0 && c3[D] <= n3[D];
-    for (int o = 0; o < 3; ++o)
-        if (o != D && (c3[o] < 0 || c3[o] >= n3[o])) ok = false;
-    return ok;
-}
-
-// whether cell (i, j, k) has a slot in the scratch records
-__device__ __forceinline__ bool in_scratch(const Geo &g, int i, int j, int k)
-{
-    return g.periodic || (i >= -2 && i < g.nx + 2 && j >= -2 && j < g.ny + 2 && k >= -2 &&
-                          k < g.nz + 2);
-}
-
-// W* +- S_D/2 of cell (i, j, k) (zero outside the scratch box)
-template <int D>
-__device__ __forceinline__ void face_states(const Geo &g, const Scratch &s, int i, int j, int k,
-                                            double P[5], double M[5])
-{
-    if (!in_scratch(g, i, j, k)) {
-        for (int q = 0; q < 5; ++q) { P[q] = 0.0; M[q] = 0.0; }
-        return;
+    Column c;
+    if (g.periodic) {
+        c.in = c.inner = wrap(j, g.ny) * g.nx + wrap(i, g.nx);
+        c.di = c.dj = 0;
+        c.inside = true;
+        return c;
     }
-    const int e = ext(g, i, j, k);
-    for (int q = 0; q < 5; ++q) {
-        const double w = s.fw[rec(e, F_WS + q)], h = 0.5 * s.fw[rec(e, F_S + D * 5 + q)];
-        P[q] = w + h;
-        M[q] = w - h;
-    }
+    c.di = depth_out(i, g.nx);
+    c.dj = depth_out(j, g.ny);
+    c.inside = c.di == 0 && c.dj == 0;
+    // columns more than two cells out are never read (they may lie outside the
+    // array)
+    c.in = c.di <= 2 && c.dj <= 2 ? (j + g.ng) * g.gx + (i + g.ng) : 0;
+    c.inner = c.inside ? j * g.nx + i : 0;
+    return c;
 }
 
-// The x (D = 0) or y (D = 1) face tasks of a plane, on the staged states.
-template <int RS, int D>
-__device__ __forceinline__ void plane_faces(const Geo &g, int i0, int j0, int k,
-                                            const double *__restrict__ lam_bflux, CellsSmem &sm)
+// whether the step reads the column's cell `dk` planes outside the patch
+__device__ __forceinline__ bool reads(const Column &c, int dk)
 {
-    constexpr int SX = CTX + (D == 0), NS = D == 0 ? NXF : NYF;
-    // NS exceeds the thread count by a few tasks; the y pass hands its extra
-    // tasks to the second wave, so that no wave does two extra rounds
-    const int first = D == 0 ? threadIdx.x : (threadIdx.x + CT - 64) % CT;
-    for (int t = first; t < NS; t += CT) {
-        // slot (sx, sy): the face whose right cell is (i0 + sx, j0 + sy, k)
-        const int sx = t % SX, sy = t / SX;
-        const int i = i0 + sx, j = j0 + sy;
-        if (!face_exists<D>(g, i, j, k)) {
-            for (int q = 0; q < 5; ++q) {
-                if (D == 0) { sm.xp[q][sy][sx] = 0.0; sm.xm[q][sy][sx + 1] = 0.0; }
-                else { sm.yp[q][sy][sx] = 0.0; sm.ym[q][sy + 1][sx] = 0.0; }
-            }
-            continue;
-        }
-        // the left cell sits at x index sx - 1 of the staged row, i.e. slot sx
-        double WL[5], WR[5], WLb[5], WRb[5], lamL[5], lamR[5];
-        for (int q = 0; q < 5; ++q) {
-            WL[q] = D == 0 ? sm.xp[q][sy][sx] : sm.yp[q][sy][sx];
-            WR[q] = D == 0 ? sm.xm[q][sy][sx + 1] : sm.ym[q][sy + 1][sx];
-            lamL[q] = D == 0 ? sm.lam[q][sy + 1][sx] : sm.lam[q][sy][sx + 1];
-            lamR[q] = sm.lam[q][sy + 1][sx + 1];
-        }
-        face_adjoint<RS, D>(g, i, j, k, WL, WR, lamL, lamR, lam_bflux, WLb, WRb);
-        for (int q = 0; q < 5; ++q) {
-            if (D == 0) { sm.xp[q][sy][sx] = WLb[q]; sm.xm[q][sy][sx + 1] = WRb[q]; }
-            else { sm.yp[q][sy][sx] = WLb[q]; sm.ym[q][sy + 1][sx] = WRb[q]; }
-        }
-    }
+    const int nout = (c.di > 0) + (c.dj > 0) + (dk > 0), sum = c.di + c.dj + dk;
+    return nout == 0 || (nout == 1 && sum <= 2) || (nout == 2 && c.di <= 1 && c.dj <= 1 && dk <= 1);
 }
 
-template <int RS>
-__global__ __launch_bounds__(CT) void k_cells(Geo g, const double *__restrict__ u,
-                                              const double *__restrict__ lam_out,
-                                              const double *__restrict__ lam_bflux, Scratch s)
+struct MarchSmem {
+    double w[2][5][CTY + 4][CTX + 4];    // primitives of planes k and k-1, two-deep halo
+    // one slot per x and y face of planes k and k-1 (TileGeom::xface / yface, y
+    // faces in rotated order): the face's right state, then its adjoint
+    double f[2][5][Tile::NF];
+    double lam[5][CTY + 2][CTX + 2];     // dL/dU' of plane k and its ring
+};
+
+// The march of the step (godunov_tile) with reversed faces. Per plane k:
+//   I   slopes, predictor and face states of plane k; the z face below it,
+//       which completes the face-state adjoints of plane k-1; the reverse
+//       predictor of plane k-1 and its record;
+//   II  the plane's x and y faces; plane k+1 staged, plane k+2 and dL/dU' of
+//       plane k+1 loaded.
+// Two waves per SIMD: the reverse solves need the registers, and the LDS holds
+// two workgroups per CU then, so planes and faces have two buffers and no third
+// barrier. Bound by the latency of the reverse solves. Slopes are formed twice
+// and the reverse predictor goes axis by axis, so that nothing of a plane's
+// slopes is held across the z face: held, 72 registers spilled and the kernel
+// took 343 us on the 128^3 box, so 268. Before, one kernel wrote slopes and
+// predicted states (20 doubles a cell, 116 us) and another read them back (285
+// us): an adjoint step 0.56 -> 0.42 ms, a 112 x 84 x 60 ghosted patch with MC
+// limiter and flux adjoints 0.266 -> 0.168 ms.
+template <int LIM, int RS>
+__global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_march(
+    Geo g, const double *__restrict__ u, const double *__restrict__ lam_out,
+    const double *__restrict__ lam_bflux, Scratch s)
 {
-    __shared__ CellsSmem sm;
+    __shared__ MarchSmem sm;
     // workgroups are dealt to the eight XCDs in turn: give each XCD a
     // contiguous range of work items, so that neighbouring tiles share its L2
-    const int b = (blockIdx.x & 7) * g.per_xcd + (blockIdx.x >> 3);
-    if (b >= g.nitem) return;
-    const int bx = b % g.ntx, br = b / g.ntx;
-    const int by = br % g.nty, bz = br / g.nty;
+    const int item = (blockIdx.x & 7) * g.per_xcd + (blockIdx.x >> 3);
+    if (item >= g.nitem) return;
+    const int bx = item % g.ntx, br = item / g.ntx;
     // tiles and z-segments cover the predicted range [lo, lo + p)^3
-    const int i0 = bx * CTX + g.lo, j0 = by * CTY + g.lo;
-    const int kb = bz * g.zlen + g.lo, ke = min(kb + g.zlen, g.lo + g.pz);
-    const int tx = threadIdx.x % CTX, ty = threadIdx.x / CTX;
-    const int i = i0 + tx, j = j0 + ty;
-    const bool col = i < g.lo + g.px && j < g.lo + g.py;
+    const int x0 = bx * CTX + g.lo, y0 = (br % g.nty) * CTY + g.lo;
+    const int kb = (br / g.nty) * g.zlen + g.lo, ke = min(kb + g.zlen, g.lo + g.pz);
+    const int ax = min(CTX, g.lo + g.px - x0), ay = min(CTY, g.lo + g.py - y0);
+    const int tid = threadIdx.x;
 
-    // dL/dU' of the column's cell in the current plane, carried up the march
-    double lamk[5];
-    lam_at(g, lam_out, i, j, kb, lamk);
-    // right-state adjoint of the z face below the first plane
-    double zlo[5] = { 0, 0, 0, 0, 0 };
-    if (face_exists<2>(g, i, j, kb)) {
-        double P[5], M[5], WL[5], WR[5], t[5], lamb[5];
-        face_states<2>(g, s, i, j, kb - 1, WL, M);
-        face_states<2>(g, s, i, j, kb, P, WR);
-        lam_at(g, lam_out, i, j, kb - 1, lamb);
-        face_adjoint<RS, 2>(g, i, j, kb, WL, WR, lamb, lamk, lam_bflux, t, zlo);
-    }
-    for (int k = kb; k < ke; ++k) {
-        // stage the x and y face states of the plane: every thread its own
-        // cell, the first wave the 64 halo cells
-        {
-            double P[5], M[5];
-            face_states<0>(g, s, i, j, k, P, M);
-            for (int q = 0; q < 5; ++q) { sm.xp[q][ty][tx + 1] = P[q]; sm.xm[q][ty][tx + 1] = M[q]; }
-            face_states<1>(g, s, i, j, k, P, M);
-            for (int q = 0; q < 5; ++q) { sm.yp[q][ty + 1][tx] = P[q]; sm.ym[q][ty + 1][tx] = M[q]; }
-            for (int q = 0; q < 5; ++q) sm.lam[q][ty + 1][tx + 1] = lamk[q];
-            if (threadIdx.x < 2 * (CTX + CTY)) {
-                const int h = threadIdx.x;
-                double L[5];
-                if (h < 2 * CTY) {
-                    // x halo: column -1 (plus state) or column CTX (minus state)
-                    const int r = h % CTY, right = h / CTY;
-                    const int hx = right ? CTX : -1;
-                    face_states<0>(g, s, i0 + hx, j0 + r, k, P, M);
-                    lam_at(g, lam_out, i0 + hx, j0 + r, k, L);
+    auto depth = [&](int k) { return g.periodic ? 0 : depth_out(k, g.nz); };
+    auto load_u = [&](const Column &c, int k, double U[5]) {
+        const double *p = u + (g.periodic ? wrap(k, g.nz) : k + g.ng) * (g.gx * g.gy);
+        const bool ok = reads(c, depth(k));
+        for (int q = 0; q < 5; ++q) U[q] = ok ? p[q * g.vin + c.in] : (q == 0 || q == 4 ? 1.0 : 0.0);
+    };
+    auto load_lam = [&](const Column &c, int k, double L[5]) {
+        const int kk = g.periodic ? wrap(k, g.nz) : k;
+        const bool ok = c.inside && kk >= 0 && kk < g.nz;
+        const double *p = lam_out + kk * (g.nx * g.ny);
+        for (int q = 0; q < 5; ++q) L[q] = ok ? p[q * g.nint + c.inner] : 0.0;
+    };
+
+    if (__builtin_amdgcn_readfirstlane(tid >> 6) < Tile::NINT / 64) {
+        // ---- the tile's columns
+        const int ci = tid % CTX, cj = tid / CTX;
+        const bool own = ci < ax && cj < ay;
+        const int i = x0 + ci, j = y0 + cj, lx = ci + 2, ly = cj + 2;
+        const Column c = make_column(g, i, j);
+        const int xlo = Tile::xface(ci, cj), xhi = Tile::xface(ci + 1, cj);
+        const int ylo = Tile::yface(ci, cj), yhi = Tile::yface(ci, cj + 1);
+        // whether the column's upper x and y faces and its z faces exist (at
+        // the planes, or below the planes, that do)
+        const bool in_i = g.periodic || c.di == 0, in_j = g.periodic || c.dj == 0;
+        const bool has_x = own && in_j && i + 1 >= 0 && i + 1 <= g.nx;
+        const bool has_y = own && in_i && j + 1 >= 0 && j + 1 <= g.ny;
+        const bool has_z = own && in_i && in_j;
+
+        // planes k-2 and k+1 of the column; the upper z state of plane k-1 and
+        // the adjoint of its lower z face's right state; the upper x and y
+        // states, then (after the solves) their adjoints; dL/dU' of plane k
+        double Wmm[5], Wp[5], zprev[5], zlo[5], up1[5], up2[5], lam0[5];
+        for (int q = 0; q < 5; ++q) zprev[q] = zlo[q] = up1[q] = up2[q] = Wmm[q] = Wp[q] = lam0[q] = 0.0;
+        double ir;
+        if (own) {
+            double Ua[5], Ub[5], Uc[5];
+            load_u(c, kb - 2, Ua);
+            load_u(c, kb - 1, Ub);
+            load_u(c, kb, Uc);
+            load_lam(c, kb - 1, lam0);
+            to_prim(g, Uc, Wp, ir);
+            to_prim(g, Ub, Uc, ir);
+            to_prim(g, Ua, Ub, ir);
+            for (int q = 0; q < 5; ++q) {
+                sm.w[0][q][ly][lx] = Uc[q];
+                sm.w[1][q][ly][lx] = Ub[q];       // plane kb-2: the z slopes of kb-1
+            }
+        }
+        __syncthreads();
+        int b = 0;
+        for (int k = kb - 1;; ++k, b ^= 1) {
+            const bool inner = k >= kb && k < ke;
+            // ---- I
+            // dL/dF of the z face below the plane, from dL/dU' of plane k-1
+            // (still in LDS) and of plane k
+            double Fz[5], nx1[5], nx2[5], zm[5], zp[5];
+            for (int q = 0; q < 5; ++q) Fz[q] = zm[q] = zp[q] = nx1[q] = nx2[q] = 0.0;
+            if (own) {
+                for (int q = 0; q < 5; ++q) {
+                    Fz[rot<2>(q)] = g.c * lam0[q] - g.c * sm.lam[q][cj + 1][ci + 1];
+                    sm.lam[q][cj + 1][ci + 1] = lam0[q];
+                }
+            }
+            if (own && (g.periodic || c.di + c.dj + depth(k) <= 1)) {
+                double W[5], Sx[5], Sy[5], Sz[5], Ws[5];
+                for (int q = 0; q < 5; ++q) {
+                    const double w = W[q] = sm.w[b][q][ly][lx];
+                    Sx[q] = limited_slope<LIM>(w - sm.w[b][q][ly][lx - 1], sm.w[b][q][ly][lx + 1] - w);
+                    Sy[q] = limited_slope<LIM>(w - sm.w[b][q][ly - 1][lx], sm.w[b][q][ly + 1][lx] - w);
+                    Sz[q] = limited_slope<LIM>(w - sm.w[b ^ 1][q][ly][lx], Wp[q] - w);
+                }
+                predictor(W, fast_rcp(W[0]), Sx, Sy, Sz, g.lam, g.gamma, Ws);
+                for (int q = 0; q < 5; ++q) {
+                    zm[q] = Ws[q] - 0.5 * Sz[q];
+                    zp[q] = Ws[q] + 0.5 * Sz[q];
+                    nx1[q] = Ws[q] + 0.5 * Sx[q];
+                    nx2[yslot(q)] = Ws[q] + 0.5 * Sy[q];
+                }
+                if (inner) {
                     for (int q = 0; q < 5; ++q) {
-                        if (right) sm.xm[q][r][CTX + 1] = M[q];
-                        else sm.xp[q][r][0] = P[q];
-                        sm.lam[q][r + 1][hx + 1] = L[q];
-                    }
-                } else {
-                    // y halo: row -1 (plus state) or row CTY (minus state)
-                    const int c = (h - 2 * CTY) % CTX, top = (h - 2 * CTY) / CTX;
-                    const int hy = top ? CTY : -1;
-                    face_states<1>(g, s, i0 + c, j0 + hy, k, P, M);
-                    lam_at(g, lam_out, i0 + c, j0 + hy, k, L);
-                    for (int q = 0; q < 5; ++q) {
-                        if (top) sm.ym[q][CTY + 1][c] = M[q];
-                        else sm.yp[q][0][c] = P[q];
-                        sm.lam[q][hy + 1][c + 1] = L[q];
+                        sm.f[b][q][xlo] = Ws[q] - 0.5 * Sx[q];
+                        sm.f[b][yslot(q)][ylo] = Ws[q] - 0.5 * Sy[q];
                     }
                 }
             }
-        }
-        // the z face above the cell, in registers
-        double zl[5] = { 0, 0, 0, 0, 0 }, zr[5] = { 0, 0, 0, 0, 0 }, lamk1[5];
-        lam_at(g, lam_out, i, j, k + 1, lamk1);
-        if (face_exists<2>(g, i, j, k + 1)) {
-            double P[5], M[5], WL[5], WR[5];
-            face_states<2>(g, s, i, j, k, WL, M);
-            face_states<2>(g, s, i, j, k + 1, P, WR);
-            face_adjoint<RS, 2>(g, i, j, k + 1, WL, WR, lamk, lamk1, lam_bflux, zl, zr);
-        }
-        for (int q = 0; q < 5; ++q) lamk[q] = lamk1[q];
-        __syncthreads();
-        plane_faces<RS, 0>(g, i0, j0, k, lam_bflux, sm);
-        plane_faces<RS, 1>(g, i0, j0, k, lam_bflux, sm);
-        __syncthreads();
-
-        // the adjoints of the cell's face states: the left state of its upper
-        // face is W* + S/2, the right state of its lower face is W* - S/2
-        double Wsb[5] = { 0, 0, 0, 0, 0 }, Sb[3][5];
-        for (int q = 0; q < 5; ++q) {
-            const double vl = sm.xp[q][ty][tx + 1], vr = sm.xm[q][ty][tx + 1];
-            Wsb[q] += vl;
-            Wsb[q] += vr;
-            Sb[0][q] = 0.5 * vl - 0.5 * vr;
-        }
-        for (int q = 0; q < 5; ++q) {
-            const double vl = sm.yp[q][ty + 1][tx], vr = sm.ym[q][ty + 1][tx];
-            Wsb[q] += vl;
-            Wsb[q] += vr;
-            Sb[1][q] = 0.5 * vl - 0.5 * vr;
-        }
-        for (int q = 0; q < 5; ++q) {
-            Wsb[q] += zl[q];
-            Wsb[q] += zlo[q];
-            Sb[2][q] = 0.5 * zl[q] - 0.5 * zlo[q];
-            zlo[q] = zr[q];
-        }
-        __syncthreads();
-        if (!col || !is_predicted(g, i, j, k)) continue;
-
-        // reverse of the predictor
-        const int e = ext(g, i, j, k);
-        double W[5], S[3][5], inv_rho;
-        load_prim(g, u, i, j, k, W, inv_rho);
-        for (int d = 0; d < 3; ++d)
-            for (int q = 0; q < 5; ++q) S[d][q] = s.fw[rec(e, F_S + d * 5 + q)];
-        const double lam = g.lam, gm = g.gamma;
-        const double rho = W[0], p = W[4], vel[3] = { W[1], W[2], W[3] };
-        const double divu = S[0][1] + S[1][2] + S[2][3];
-        double Wb[5] = { 0, 0, 0, 0, 0 }, velb[3] = { 0, 0, 0 }, divub = 0.0;
-        // rho* = rho - lam (sum_d u_d S_d,rho + rho divu)
-        Wb[0] += Wsb[0] * (1.0 - lam * divu);
-        divub -= lam * Wsb[0] * rho;
-        for (int d = 0; d < 3; ++d) {
-            velb[d] -= lam * Wsb[0] * S[d][0];
-            Sb[d][0] -= lam * Wsb[0] * vel[d];
-        }
-        // u_m* = u_m - lam (sum_d u_d S_d,m + S_m,p / rho)
-        for (int m = 0; m < 3; ++m) {
-            const double bm = Wsb[1 + m];
-            velb[m] += bm;
-            for (int d = 0; d < 3; ++d) {
-                velb[d] -= lam * bm * S[d][1 + m];
-                Sb[d][1 + m] -= lam * bm * vel[d];
+            // the z face below the plane
+            double zl[5], zr[5];
+            for (int q = 0; q < 5; ++q) zl[q] = zr[q] = 0.0;
+            __builtin_amdgcn_sched_barrier(0);
+            if (has_z && k >= kb && (g.periodic || (k >= 0 && k <= g.nz))) {
+                double L[5], R[5], Lb[5], Rb[5];
+                for (int q = 0; q < 5; ++q) {
+                    L[rot<2>(q)] = zprev[q];
+                    R[rot<2>(q)] = zm[q];
+                }
+                add_bflux<2>(g, lam_bflux, k, j * g.nx + i, Fz);
+                face_reverse<RS>(g, L, R, Fz, Lb, Rb);
+                for (int q = 0; q < 5; ++q) {
+                    zl[q] = Lb[rot<2>(q)];
+                    zr[q] = Rb[rot<2>(q)];
+                }
             }
-            Sb[m][4] -= lam * bm * inv_rho;
-            Wb[0] += lam * bm * S[m][4] * inv_rho * inv_rho;
+            __builtin_amdgcn_sched_barrier(0);
+            if (own && k > kb && (g.periodic || c.di + c.dj + depth(k - 1) <= 1)) {
+                // the adjoints of plane k-1's face states: the left state of an
+                // upper face is W* + S/2, the right state of a lower one W* - S/2
+                const int e = ext(g, i, j, k - 1);
+                double Wsb[5], W[5];
+                for (int q = 0; q < 5; ++q) {
+                    Wsb[q] = ((up1[q] + sm.f[b ^ 1][q][xlo]) +
+                              (up2[yslot(q)] + sm.f[b ^ 1][yslot(q)][ylo])) + (zl[q] + zlo[q]);
+                    W[q] = sm.w[b ^ 1][q][ly][lx];
+                }
+                // reverse of the predictor, axis by axis:
+                //   rho* = rho - lam (sum_d u_d S_d,rho + rho divu)
+                //   u_m* = u_m - lam (sum_d u_d S_d,m + S_m,p / rho)
+                //   p*   = p - lam (sum_d u_d S_d,p + gamma p divu)
+                const double inv_rho = fast_rcp(W[0]), lam = g.lam;
+                const double divub = -lam * (Wsb[0] * W[0] + g.gamma * Wsb[4] * W[4]);
+                double Wb0 = Wsb[0], Wb4 = Wsb[4];
+                unsigned code = 0u;
+                for (int d = 0; d < 3; ++d) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    double S[5], Sb[5], dot = 0.0;
+                    for (int q = 0; q < 5; ++q) {
+                        const double w = W[q];
+                        const double a = w - (d == 0 ? sm.w[b ^ 1][q][ly][lx - 1]
+                                                     : (d == 1 ? sm.w[b ^ 1][q][ly - 1][lx] : Wmm[q]));
+                        const double h = (d == 0 ? sm.w[b ^ 1][q][ly][lx + 1]
+                                                 : (d == 1 ? sm.w[b ^ 1][q][ly + 1][lx]
+                                                           : sm.w[b][q][ly][lx])) - w;
+                        S[q] = limited_slope<LIM>(a, h);
+                        code |= slope_branch<LIM>(a, h) << (2 * (d * 5 + q));
+                        const double vl = d == 0 ? up1[q] : (d == 1 ? up2[yslot(q)] : zl[q]);
+                        const double vr = d == 0 ? sm.f[b ^ 1][q][xlo]
+                                                 : (d == 1 ? sm.f[b ^ 1][yslot(q)][ylo] : zlo[q]);
+                        Sb[q] = (0.5 * vl - 0.5 * vr) - lam * Wsb[q] * W[1 + d];
+                        dot += Wsb[q] * S[q];
+                    }
+                    Sb[4] -= lam * Wsb[1 + d] * inv_rho;
+                    Sb[1 + d] += divub;
+                    Wb0 += lam * (Wsb[1 + d] * S[4] * inv_rho * inv_rho - Wsb[0] * S[1 + d]);
+                    Wb4 -= lam * g.gamma * Wsb[4] * S[1 + d];
+                    for (int q = 0; q < 5; ++q)
+                        __builtin_nontemporal_store(Sb[q], &s.ad[rec(e, F_SB + d * 5 + q)]);
+                    __builtin_nontemporal_store(Wsb[1 + d] - lam * dot, &s.ad[rec(e, F_WD + 1 + d)]);
+                }
+                __builtin_nontemporal_store(Wb0, &s.ad[rec(e, F_WD)]);
+                __builtin_nontemporal_store(Wb4, &s.ad[rec(e, F_WD + 4)]);
+                s.code[e] = code;
+            }
+            for (int q = 0; q < 5; ++q) {
+                up1[q] = nx1[q];
+                up2[q] = nx2[q];
+            }
+            for (int q = 0; q < 5; ++q) {
+                zlo[q] = zr[q];
+                zprev[q] = zp[q];
+            }
+            if (k == ke) break;
+            __syncthreads();
+
+            // ---- II
+            double Un[5], lamn[5];
+            if (own) {
+                load_u(c, k + 2, Un);
+                load_lam(c, k + 1, lamn);
+            }
+            if (own && inner) {
+                // a face between cells that are not both there has no adjoint
+                const bool at_k = g.periodic || (k >= 0 && k < g.nz);
+                double R[5], Fb[5], Lb[5], Rb[5];
+                for (int q = 0; q < 5; ++q) Lb[q] = Rb[q] = 0.0;
+                if (has_x && at_k) {
+                    for (int q = 0; q < 5; ++q) {
+                        R[q] = sm.f[b][q][xhi];
+                        Fb[q] = g.c * sm.lam[q][cj + 1][ci + 2] - g.c * lam0[q];
+                    }
+                    add_bflux<0>(g, lam_bflux, i + 1, k * g.ny + j, Fb);
+                    face_reverse<RS>(g, up1, R, Fb, Lb, Rb);
+                }
+                for (int q = 0; q < 5; ++q) {
+                    up1[q] = Lb[q];
+                    sm.f[b][q][xhi] = Rb[q];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                for (int q = 0; q < 5; ++q) Lb[q] = Rb[q] = 0.0;
+                if (has_y && at_k) {
+                    for (int q = 0; q < 5; ++q) {
+                        R[q] = sm.f[b][q][yhi];
+                        Fb[yslot(q)] = g.c * sm.lam[q][cj + 2][ci + 1] - g.c * lam0[q];
+                    }
+                    add_bflux<1>(g, lam_bflux, j + 1, k * g.nx + i, Fb);
+                    face_reverse<RS>(g, up2, R, Fb, Lb, Rb);
+                }
+                for (int q = 0; q < 5; ++q) {
+                    up2[q] = Lb[q];
+                    sm.f[b][q][yhi] = Rb[q];
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (own) {
+                // the column moves up
+                for (int q = 0; q < 5; ++q) {
+                    Wmm[q] = sm.w[b ^ 1][q][ly][lx];
+                    sm.w[b ^ 1][q][ly][lx] = Wp[q];
+                    lam0[q] = lamn[q];
+                }
+                to_prim(g, Un, Wp, ir);
+            }
+            __syncthreads();
         }
-        // p* = p - lam (sum_d u_d S_d,p + gamma p divu)
-        Wb[4] += Wsb[4] * (1.0 - lam * gm * divu);
-        divub -= lam * Wsb[4] * gm * p;
-        for (int d = 0; d < 3; ++d) {
-            velb[d] -= lam * Wsb[4] * S[d][4];
-            Sb[d][4] -= lam * Wsb[4] * vel[d];
+    } else {
+        // ---- a ring column: the state its face with the tile needs (the left
+        // and bottom columns hold the face's left state and reverse it), dL/dU'
+        // of its cell, and the primitives of its cell and the halo cell behind
+        // it, the first four lanes of a corner cell too
+        const int r = tid - Tile::NINT;
+        const bool own = r < 2 * (ax + ay);
+        const bool ring_x = r >= 2 * ax;
+        const int e = ring_x ? r - 2 * ax : r;
+        const bool far = e >= (ring_x ? ay : ax);             // right or top
+        const int at = far ? e - (ring_x ? ay : ax) : e;
+        const int ci = ring_x ? (far ? ax : -1) : at, cj = ring_x ? at : (far ? ay : -1);
+        const int hi = ring_x ? (far ? ax + 1 : -2) : at, hj = ring_x ? at : (far ? ay + 1 : -2);
+        const int ki = (r & 1) ? ax : -1, kj = (r & 2) ? ay : -1;
+        const bool corner = r < 4;
+        const int i = x0 + ci, j = y0 + cj, lx = ci + 2, ly = cj + 2;
+        const Column c = make_column(g, i, j);
+        const Column ch = make_column(g, x0 + hi, y0 + hj), ck = make_column(g, x0 + ki, y0 + kj);
+        const int face = ring_x ? Tile::xface(ci + !far, cj) : Tile::yface(ci, cj + !far);
+        // the face's index along its axis, and whether it exists
+        const int fi = (ring_x ? i : j) + !far;
+        const bool has = own && fi >= 0 && fi <= (ring_x ? g.nx : g.ny) &&
+                         (g.periodic || (ring_x ? c.dj : c.di) == 0);
+        const double side = far ? -0.5 : 0.5;
+
+        double Wm[5], Wp[5], up1[5], lam0[5], ir;
+        for (int q = 0; q < 5; ++q) Wm[q] = Wp[q] = up1[q] = lam0[q] = 0.0;
+        if (own) {
+            double Ub[5], Uc[5];
+            load_u(c, kb - 1, Ub);
+            load_u(c, kb, Uc);
+            load_lam(c, kb - 1, lam0);
+            to_prim(g, Uc, Wp, ir);
+            to_prim(g, Ub, Uc, ir);
+            for (int q = 0; q < 5; ++q) sm.w[0][q][ly][lx] = Uc[q];
         }
-        Sb[0][1] += divub;
-        Sb[1][2] += divub;
-        Sb[2][3] += divub;
-        for (int d = 0; d < 3; ++d) Wb[1 + d] += velb[d];
-        for (int q = 0; q < 5; ++q) __builtin_nontemporal_store(Wb[q], &s.ad[rec(e, F_WD + q)]);
-        for (int d = 0; d < 3; ++d)
-            for (int q = 0; q < 5; ++q)
-                __builtin_nontemporal_store(Sb[d][q], &s.ad[rec(e, F_SB + d * 5 + q)]);
+        __syncthreads();
+        int b = 0;
+        for (int k = kb - 1;; ++k, b ^= 1) {
+            const bool inner = k >= kb && k < ke;
+            const bool at_k = g.periodic || (k >= 0 && k < g.nz);
+            // ---- I
+            if (own && inner) {
+                if (has && at_k) {
+                    double W[5], Sx[5], Sy[5], Sz[5], Ws[5];
+                    for (int q = 0; q < 5; ++q) {
+                        const double w = W[q] = sm.w[b][q][ly][lx];
+                        Sx[q] = limited_slope<LIM>(w - sm.w[b][q][ly][lx - 1],
+                                                   sm.w[b][q][ly][lx + 1] - w);
+                        Sy[q] = limited_slope<LIM>(w - sm.w[b][q][ly - 1][lx],
+                                                   sm.w[b][q][ly + 1][lx] - w);
+                        Sz[q] = limited_slope<LIM>(w - Wm[q], Wp[q] - w);
+                    }
+                    predictor(W, fast_rcp(W[0]), Sx, Sy, Sz, g.lam, g.gamma, Ws);
+                    double st[5];
+                    for (int q = 0; q < 5; ++q) st[q] = Ws[q] + side * (ring_x ? Sx[q] : Sy[q]);
+                    for (int q = 0; q < 5; ++q) up1[q] = st[q];
+                    if (!ring_x)
+                        for (int q = 0; q < 5; ++q) up1[yslot(q)] = st[q];
+                    if (far)
+                        for (int q = 0; q < 5; ++q) sm.f[b][q][face] = up1[q];
+                }
+                for (int q = 0; q < 5; ++q) sm.lam[q][cj + 1][ci + 1] = lam0[q];
+            }
+            if (k == ke) break;
+            __syncthreads();
+
+            // ---- II
+            double Un[5], Hn[5], Kn[5], lamn[5];
+            if (own) {
+                load_u(c, k + 2, Un);
+                load_lam(c, k + 1, lamn);
+                load_u(ch, k + 1, Hn);
+                if (corner) load_u(ck, k + 1, Kn);
+            }
+            if (own && inner && !far) {
+                double Lb[5], Rb[5];
+                for (int q = 0; q < 5; ++q) Rb[q] = 0.0;
+                if (has && at_k) {
+                    double R[5], d[5], Fb[5];
+                    for (int q = 0; q < 5; ++q) {
+                        R[q] = sm.f[b][q][face];
+                        d[q] = g.c * sm.lam[q][cj + 1 + !ring_x][ci + 1 + ring_x] - g.c * lam0[q];
+                    }
+                    for (int q = 0; q < 5; ++q) Fb[q] = d[q];
+                    if (ring_x) {
+                        add_bflux<0>(g, lam_bflux, fi, k * g.ny + j, Fb);
+                    } else {
+                        for (int q = 0; q < 5; ++q) Fb[yslot(q)] = d[q];
+                        add_bflux<1>(g, lam_bflux, fi, k * g.nx + i, Fb);
+                    }
+                    face_reverse<RS>(g, up1, R, Fb, Lb, Rb);
+                }
+                for (int q = 0; q < 5; ++q) sm.f[b][q][face] = Rb[q];
+            }
+            if (own) {
+                double Wh[5];
+                for (int q = 0; q < 5; ++q) {
+                    Wm[q] = sm.w[b][q][ly][lx];
+                    sm.w[b ^ 1][q][ly][lx] = Wp[q];
+                    lam0[q] = lamn[q];
+                }
+                to_prim(g, Un, Wp, ir);
+                to_prim(g, Hn, Wh, ir);
+                for (int q = 0; q < 5; ++q) sm.w[b ^ 1][q][hj + 2][hi + 2] = Wh[q];
+                if (corner) {
+                    to_prim(g, Kn, Wh, ir);
+                    for (int q = 0; q < 5; ++q) sm.w[b ^ 1][q][kj + 2][ki + 2] = Wh[q];
+                }
+            }
+            __syncthreads();
+        }
     }
 }
 
-// ------------------------------------------------------------ 3: input
+// ------------------------------------------------------------ 2: input
 
 // dL/dW of extended cell (i, j, k): its predictor term and the slope splits
 // of itself (a - b) and of its neighbours along each axis, from the branches
-// recorded by the predict kernel.
+// recorded by the march.
 template <int LIM>
 __device__ __forceinline__ void gather_wbar(const Geo &g, const Scratch &s, int i, int j, int k,
                                             double Wb[5])
@@ -834,8 +896,8 @@ size_t adjoint_scratch_bytes(const PatchDesc &P)
     const int pad = P.periodic ? 0 : 4;
     const int64_t E = (int64_t)(P.nx + pad) * (P.ny + pad) * (P.nz + pad);
     const int64_t Ep = (E + 63) / 64 * 64;
-    // two records of 20 doubles and one branch word per extended cell
-    return (size_t)(2 * adj::NF * Ep) * sizeof(double) + (size_t)Ep * sizeof(unsigned);
+    // a record of 20 doubles and one branch word per extended cell
+    return (size_t)(adj::NF * Ep) * sizeof(double) + (size_t)Ep * sizeof(unsigned);
 }
 
 bool adjoint_fits_32bit(const PatchDesc &P)
@@ -850,7 +912,7 @@ bool adjoint_fits_32bit(const PatchDesc &P)
 template <int LIM, int RS>
 static int run_adjoint(const PatchDesc &P, const double *u_in, const double *lam_out,
                        const double *lam_bflux, double *lam_in, const Scalars &sc, double dt,
-                       double *scratch, hipStream_t st)
+                       double *scratch, int num_cus, hipStream_t st)
 {
     adj::Geo g{};
     g.nx = P.nx; g.ny = P.ny; g.nz = P.nz; g.ng = P.ng; g.periodic = P.periodic;
@@ -868,10 +930,11 @@ static int run_adjoint(const PatchDesc &P, const double *u_in, const double *lam
     g.nint = P.nx * P.ny * P.nz;
     g.ntx = (g.px + adj::CTX - 1) / adj::CTX;
     g.nty = (g.py + adj::CTY - 1) / adj::CTY;
-    // z-segments: about 1024 work items, at least 4 planes each
+    // z-segments: as many as the chip holds workgroups (two per CU), at least 4
+    // planes each (a segment predicts the planes below and above it again)
     {
         const int tiles = g.ntx * g.nty;
-        int nseg = (1024 + tiles - 1) / tiles;
+        int nseg = std::max(1, 2 * num_cus / tiles);
         nseg = std::max(1, std::min(nseg, g.pz / 4));
         g.zlen = (g.pz + nseg - 1) / nseg;
         g.nseg = (g.pz + g.zlen - 1) / g.zlen;
@@ -884,14 +947,10 @@ static int run_adjoint(const PatchDesc &P, const double *u_in, const double *lam
     g.c = dt / P.dx;
     adj::Scratch s{};
     const size_t Ep = ((size_t)g.E + 63) / 64 * 64;
-    s.fw = scratch;
-    s.ad = scratch + adj::NF * Ep;
-    s.code = reinterpret_cast<unsigned *>(scratch + 2 * adj::NF * Ep);
-    const int npred = g.px * g.py * g.pz;
-    hipLaunchKernelGGL(adj::k_predict<LIM>, dim3((npred + 255) / 256), dim3(256), 0, st, g, u_in,
-                       s);
-    hipLaunchKernelGGL(adj::k_cells<RS>, dim3(8 * g.per_xcd), dim3(adj::CT), 0, st, g, u_in,
-                       lam_out, lam_bflux, s);
+    s.ad = scratch;
+    s.code = reinterpret_cast<unsigned *>(scratch + adj::NF * Ep);
+    hipLaunchKernelGGL((adj::k_march<LIM, RS>), dim3(8 * g.per_xcd), dim3(adj::Tile::NT), 0, st, g,
+                       u_in, lam_out, lam_bflux, s);
     hipLaunchKernelGGL(adj::k_input<LIM>, dim3((g.gx + 63) / 64, (g.gy + 3) / 4, g.gz), dim3(256),
                        0, st, g, u_in, lam_out, lam_in, s);
     return (int)hipGetLastError();
@@ -899,16 +958,16 @@ static int run_adjoint(const PatchDesc &P, const double *u_in, const double *lam
 
 int launch_adjoint(int limiter, int riemann, const PatchDesc &P, const double *u_in,
                    const double *lam_out, const double *lam_bflux, double *lam_in,
-                   const Scalars &sc, double dt, double *scratch, hipStream_t s)
+                   const Scalars &sc, double dt, double *scratch, int num_cus, hipStream_t s)
 {
     if (riemann == 1) {
-        if (limiter == 1) return run_adjoint<1, 1>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, s);
-        if (limiter == 2) return run_adjoint<2, 1>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, s);
-        return run_adjoint<0, 1>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, s);
+        if (limiter == 1) return run_adjoint<1, 1>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, num_cus, s);
+        if (limiter == 2) return run_adjoint<2, 1>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, num_cus, s);
+        return run_adjoint<0, 1>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, num_cus, s);
     }
-    if (limiter == 1) return run_adjoint<1, 0>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, s);
-    if (limiter == 2) return run_adjoint<2, 0>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, s);
-    return run_adjoint<0, 0>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, s);
+    if (limiter == 1) return run_adjoint<1, 0>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, num_cus, s);
+    if (limiter == 2) return run_adjoint<2, 0>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, num_cus, s);
+    return run_adjoint<0, 0>(P, u_in, lam_out, lam_bflux, lam_in, sc, dt, scratch, num_cus, s);
 }
 
 }  // namespace gd

@@ -858,7 +858,7 @@ int godunov_step_adjoint(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int n
     gd::Scalars sc{ gamma, opts->rho_floor, opts->p_floor };
     int e = gd::launch_adjoint(opts->limiter, opts->riemann, P, (const double *)u_in,
                                (const double *)lam_out, (const double *)lam_bflux, (double *)lam_in,
-                               sc, dt, (double *)ctx->adj.p, s);
+                               sc, dt, (double *)ctx->adj.p, ctx->num_cus, s);
     if (e) return hip_fail(ctx, e, "godunov_step_adjoint launch");
     return GD_OK;
 }

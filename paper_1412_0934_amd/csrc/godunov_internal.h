@@ -100,7 +100,8 @@ bool adjoint_fits_32bit(const PatchDesc &P);
 
 int launch_adjoint(int limiter, int riemann, const PatchDesc &P, const double *u_in,
                    const double *lam_out, const double *lam_bflux, double *lam_in,
-                   const Scalars &sc, double dt, double *scratch, hipStream_t s);
+                   const Scalars &sc, double dt, double *scratch, int num_cus,
+                   hipStream_t s);
 
 // Workgroups of the step kernel of a scheme and tile shape that one CU holds
 // at once (the batched and single-patch kernels have the same resources).
