@@ -653,7 +653,6 @@ int step_impl(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int nz, int ng,
         gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.u32 + 3 };
         int e = gd::launch_ppm_tile(opts->dtype, opts->limiter, opts->riemann, P, u_in, u_out, bflux,
                                     dt_dev, sc, ctx->d_u64, 2 * ctx->num_cus, co, s);
-        if (!e && dt_next) e = gd::launch_cfl_finalize(cfl, dt_next, co.smax_bits, s);
         if (e) return hip_fail(ctx, e, "PPM step launch");
         return GD_OK;
     }
@@ -735,7 +734,6 @@ int step_batched_impl(gd_ctx *ctx, const gd_opts *opts, int npatch, const gd_pat
         int e = gd::launch_ppm_batched(opts->dtype, opts->limiter, opts->riemann, c.d_patches,
                                        c.d_items, c.nitems, u_in_base, u_out_base, bflux_base, dt_dev,
                                        sc, ctx->d_u64, slot.u32, ctx->num_cus, co, s);
-        if (!e && dt_next) e = gd::launch_cfl_finalize(cfl, dt_next, co.smax_bits, s);
         if (e) return hip_fail(ctx, e, "PPM batched step launch");
         return GD_OK;
     }

@@ -251,18 +251,21 @@ __device__ __forceinline__ void hllc_rotated(const T L[5], const T R[5], const P
 }
 
 // Order of the sum of squares of a single-precision HLL flux: the compiler's,
-// or one of the two fused orders of the PLM tile march (its x and y faces, its
-// z faces), which the march names to keep its bits.
-enum { SQ_ANY = 0, SQ_XY = 1, SQ_Z = 2 };
+// or one of the two fused orders of the tile marches (their x and y faces, their
+// z faces), which a march names to keep its bits; the PPM march also names the
+// product that its energy fuses.
+enum { SQ_ANY = 0, SQ_XY = 1, SQ_Z = 2, SQ_PPM = 4 };
 
 template <int SQ, typename T>
 __device__ __forceinline__ void euler_flux_rotated(const T W[5], const Phys<T> &ph, T F[5], T U[5])
 {
     T q2;
-    if constexpr (SQ == SQ_XY) q2 = fma(W[3], W[3], fma(W[1], W[1], W[2] * W[2]));
-    else if constexpr (SQ == SQ_Z) q2 = fma(W[3], W[3], fma(W[2], W[2], W[1] * W[1]));
+    if constexpr ((SQ & 3) == SQ_XY) q2 = fma(W[3], W[3], fma(W[1], W[1], W[2] * W[2]));
+    else if constexpr ((SQ & 3) == SQ_Z) q2 = fma(W[3], W[3], fma(W[2], W[2], W[1] * W[1]));
     else q2 = W[1] * W[1] + W[2] * W[2] + W[3] * W[3];
-    T E = W[4] * ph.inv_gm1 + T(0.5) * W[0] * q2;
+    T E;
+    if constexpr (SQ & SQ_PPM) E = fma(W[4], ph.inv_gm1, T(0.5) * W[0] * q2);
+    else E = W[4] * ph.inv_gm1 + T(0.5) * W[0] * q2;
     T mass = W[0] * W[1];
     F[0] = mass; F[1] = mass * W[1] + W[4]; F[2] = mass * W[2]; F[3] = mass * W[3];
     F[4] = W[1] * (E + W[4]);

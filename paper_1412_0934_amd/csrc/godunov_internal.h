@@ -63,6 +63,16 @@ struct CflOut {
 // (4.7 us); a large grid hides it, and its counts would queue on one address.
 constexpr int CFL_COUNT_BLOCKS = 512;
 
+// The CFL output as a launch of `blocks` workgroups takes it.
+inline CflOut cfl_counted(CflOut co, int64_t blocks)
+{
+    if (blocks > CFL_COUNT_BLOCKS) co.done = nullptr;
+    return co;
+}
+
+// After that launch: the one-thread launch, where one is needed.
+int cfl_finalized(const CflOut &co, hipStream_t s);
+
 // Launchers. Return 0 or a hipError_t value.
 // launch_step: z-ranges of zlen planes, shorter (down to one) where the
 // patch would otherwise give fewer than min_blocks workgroups.
@@ -208,8 +218,7 @@ int launch_ppm(int dtype, int limiter, int riemann, const PatchDesc &P, const vo
 
 // One PPM step (limiters 3 to 6) of a single patch in one launch: the tile
 // march of the PLM step with the parabola, no face-state scratch; with
-// co.dt_next the CFL signal of the new state is reduced into co.smax_bits
-// (launch_cfl_finalize turns it into dt).
+// co.dt_next also the time step of the new state.
 constexpr int PPM_FUSED_TX = 24, PPM_FUSED_TY = 8;
 int launch_ppm_tile(int dtype, int limiter, int riemann, const PatchDesc &P, const void *u_in,
                     void *u_out, void *bflux, const double *dt_dev, const Scalars &sc,
@@ -223,7 +232,5 @@ int launch_ppm_batched(int dtype, int limiter, int riemann, const PatchDesc *d_p
                        void *bflux, const double *dt_dev, const Scalars &sc,
                        unsigned long long *hits, unsigned *d_queue, int num_cus, const CflOut &co,
                        hipStream_t s);
-// dt = cfl / (the maximum folded into smax_bits), which is cleared for the next use
-int launch_cfl_finalize(double cfl, double *dt_out, unsigned long long *smax_bits, hipStream_t s);
 
 }  // namespace gd

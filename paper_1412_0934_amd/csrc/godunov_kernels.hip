@@ -240,21 +240,6 @@ __global__ __launch_bounds__(256) void cfl_single_kernel(PatchDesc P, const T *_
 
 // ------------------------------------------------------------ launchers
 
-// The CFL output of a launch of `blocks` workgroups: with its completion
-// counter or without.
-static CflOut counted(CflOut co, int64_t blocks)
-{
-    if (blocks > CFL_COUNT_BLOCKS) co.done = nullptr;
-    return co;
-}
-
-static void finalize(const CflOut &co, hipStream_t s)
-{
-    if (co.dt_next && !co.done)
-        hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(64), 0, s, co.cfl, co.dt_next,
-                           co.smax_bits);
-}
-
 template <typename T, int LIM, int RS, int TX, int TY>
 static int launch_step_t(const PatchDesc &P, const void *u_in, void *u_out, void *bflux,
                          const double *dt_dev, const Scalars &sc, unsigned long long *hits,
@@ -272,12 +257,11 @@ static int launch_step_t(const PatchDesc &P, const void *u_in, void *u_out, void
     const int nseg = (P.nz + zlen - 1) / zlen;
     const int64_t nblocks = (int64_t)ntx * nty * nseg;
     if (nblocks <= 0 || nblocks > 0x7fffffff) return (int)hipErrorInvalidValue;
-    const CflOut co = counted(want, nblocks);
+    const CflOut co = cfl_counted(want, nblocks);
     hipLaunchKernelGGL((step_kernel<T, LIM, RS, TX, TY>), dim3((unsigned)nblocks),
                        dim3(TileGeom<TX, TY>::NT), 0, s, P, (const T *)u_in, (T *)u_out, (T *)bflux,
                        dt_dev, sc, hits, ntx, nty, zlen, co);
-    finalize(co, s);
-    return (int)hipGetLastError();
+    return cfl_finalized(co, s);
 }
 
 template <typename T, int LIM, int RS, int TX, int TY>
@@ -286,12 +270,11 @@ static int launch_batched_t(const PatchDesc *d_patches, const WorkItem *d_items,
                             const Scalars &sc, unsigned long long *hits, unsigned *d_queue,
                             int grid, const CflOut &want, hipStream_t s)
 {
-    const CflOut co = counted(want, grid);
+    const CflOut co = cfl_counted(want, grid);
     hipLaunchKernelGGL((step_batched_kernel<T, LIM, RS, TX, TY>), dim3(grid),
                        dim3(TileGeom<TX, TY>::NT), 0, s, d_patches, d_items, nitems,
                        (const T *)u_in, (T *)u_out, (T *)bflux, dt_dev, sc, hits, d_queue, co);
-    finalize(co, s);
-    return (int)hipGetLastError();
+    return cfl_finalized(co, s);
 }
 
 template <typename T, int LIM, int RS>
@@ -315,12 +298,11 @@ static int launch_batched_pair_t(const PatchDesc *d_patches, const WorkItem *d_i
                                  const Scalars &sc, unsigned long long *hits, unsigned *d_queue,
                                  int grid, const CflOut &want, hipStream_t s)
 {
-    const CflOut co = counted(want, grid);
+    const CflOut co = cfl_counted(want, grid);
     hipLaunchKernelGGL((step_batched_pair_kernel<T, LIM, RS, TXB, TYB>), dim3(grid),
                        dim3(pair_threads(TXB, TYB)), 0, s, d_patches, d_items, nitems,
                        (const T *)u_in, (T *)u_out, (T *)bflux, dt_dev, sc, hits, d_queue, co);
-    finalize(co, s);
-    return (int)hipGetLastError();
+    return cfl_finalized(co, s);
 }
 
 template <typename T, int LIM, int RS>
@@ -377,15 +359,14 @@ int launch_cfl(int dtype, const PatchDesc *d_patches, const CflItem *d_items, in
                const void *u, const Scalars &sc, double cfl, double *dt_out,
                unsigned long long *smax_bits, unsigned *done, int grid, hipStream_t s)
 {
-    const CflOut co = counted(CflOut{ cfl, dt_out, smax_bits, done }, grid);
+    const CflOut co = cfl_counted(CflOut{ cfl, dt_out, smax_bits, done }, grid);
     if (dtype == 1)
         hipLaunchKernelGGL(cfl_kernel<float>, dim3(grid), dim3(256), 0, s, d_patches, d_items,
                            nitems, (const float *)u, sc, co);
     else
         hipLaunchKernelGGL(cfl_kernel<double>, dim3(grid), dim3(256), 0, s, d_patches, d_items,
                            nitems, (const double *)u, sc, co);
-    finalize(co, s);
-    return (int)hipGetLastError();
+    return cfl_finalized(co, s);
 }
 
 int launch_cfl_single(int dtype, const PatchDesc &P, const void *u, const Scalars &sc, double cfl,
@@ -396,15 +377,14 @@ int launch_cfl_single(int dtype, const PatchDesc &P, const void *u, const Scalar
     int64_t blocks = (ncell + 255) / 256;
     if (blocks > 2048) blocks = 2048;
     if (blocks < 1) blocks = 1;
-    const CflOut co = counted(CflOut{ cfl, dt_out, smax_bits, done }, blocks);
+    const CflOut co = cfl_counted(CflOut{ cfl, dt_out, smax_bits, done }, blocks);
     if (dtype == 1)
         hipLaunchKernelGGL(cfl_single_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, s, P,
                            (const float *)u, sc, co);
     else
         hipLaunchKernelGGL(cfl_single_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, s, P,
                            (const double *)u, sc, co);
-    finalize(co, s);
-    return (int)hipGetLastError();
+    return cfl_finalized(co, s);
 }
 
 template <typename T, int LIM, int RS>
@@ -436,9 +416,11 @@ static int occupancy_t(int shape, int device)
     return n;
 }
 
-int launch_cfl_finalize(double cfl, double *dt_out, unsigned long long *smax_bits, hipStream_t s)
+int cfl_finalized(const CflOut &co, hipStream_t s)
 {
-    hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(64), 0, s, cfl, dt_out, smax_bits);
+    if (co.dt_next && !co.done)
+        hipLaunchKernelGGL(cfl_finalize_kernel, dim3(1), dim3(64), 0, s, co.cfl, co.dt_next,
+                           co.smax_bits);
     return (int)hipGetLastError();
 }
 

@@ -1,0 +1,121 @@
+"""The marching kernels at the sizes where their tiles and z-ranges end: extents
+one below, at and one above the 24 x 8 column tile and its multiples, one plane
+and one plane more than a z-range, each against the oracle; and the time step
+stored by the step's last workgroup, on both sides of the grid size from which
+a launch of its own stores it. FP64 to 1e-12 as everywhere (rounding of a few
+hundred operations on values of order one), time steps to 1e-14 (a maximum of
+the same sums, one square root and one division)."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import mhd
+from helpers import bflux_err, parity_err, say
+from paper_1412_0934_amd import inputs
+
+pytestmark = pytest.mark.gpu
+G = 5.0 / 3.0
+SHAPES = [(23, 7, 1), (24, 8, 2), (25, 9, 33), (49, 17, 5)]
+
+
+@pytest.fixture(scope="module")
+def gd():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1412_0934_amd import godunov
+    return godunov
+
+
+def dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def host(t):
+    import torch
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("periodic", [False, True])
+@pytest.mark.parametrize("lim,rs", [("minmod", "hllc"), ("mc", "hll"), ("ppm", "hllc"),
+                                    ("ppm_ct", "hll"), ("ppm_ct_unlimited", "hllc")])
+def test_step(gd, shape, periodic, lim, rs):
+    nx, ny, nz = shape
+    if periodic:
+        nz += 1         # the one-launch PPM march takes periodic extents of 2 and more
+    ng = 0 if periodic else 3
+    u = inputs.random_patch(nx, ny, nz, ng=ng, seed=nx + 7 * ny + 31 * nz, generic=True)
+    dx = 1 / 64
+    kw = dict(periodic=True) if periodic else dict(ng=3)
+    dt = oracle.cfl_dt(u, G, dx, 0.4, **kw)
+    ref, bref, _ = oracle.step(u, G, dx, dt, limiter=lim, riemann=rs, **kw)
+    say("tile edges", shape, "periodic" if periodic else "ghosted", lim, rs)
+    out, b = gd.step(dev(u), G, dx, dt, limiter=lim, riemann=rs, **kw)
+    assert parity_err(host(out), ref) <= 1e-12
+    assert bflux_err(host(b), bref, nx, ny, nz) <= 1e-12
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("lim", ["minmod", "mc"])
+def test_mhd_step(gd, shape, lim):
+    nx, ny, nz = shape
+    u = inputs.mhd_random_box(nx, ny, nz, seed=nx + 10 * ny + 100 * nz)
+    dx = 1.0 / max(shape)
+    dt, ch = mhd.cfl(u, G, dx)
+    ref, _ = mhd.step(u, G, dx, dt, ch, alpha=0.1, limiter=lim)
+    say("tile edges mhd", shape, lim)
+    got = host(gd.step_mhd(dev(u), G, dx, dt, ch, alpha=0.1, limiter=lim))
+    assert parity_err(got, ref, 9) <= 1e-12
+
+
+def _adjoint(gd, u, shape, dx, lim, rs, **kw):
+    nx, ny, nz = shape
+    dt = 0.5 * oracle.cfl_dt(u, G, dx, **kw)
+    rng = np.random.default_rng(8)
+    lo = rng.standard_normal((5, nz, ny, nx))
+    lb = rng.standard_normal(oracle.bflux_size(nx, ny, nz))
+    ref = oracle.step_adjoint(u, lo, G, dx, dt, lam_bflux=lb, limiter=lim, riemann=rs, **kw)
+    say("tile edges adjoint", shape, kw, lim, rs)
+    got = host(gd.step_adjoint(dev(u), dev(lo), G, dx, dt, lam_bflux=dev(lb), limiter=lim,
+                               riemann=rs, **kw))
+    assert float(np.abs(got - ref).max() / np.abs(ref).max()) <= 1e-12
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("lim,rs", [("minmod", "hllc"), ("mc", "hll")])
+def test_adjoint(gd, shape, lim, rs):
+    nx, ny, nz = shape
+    u = inputs.random_patch(nx, ny, nz, seed=nx + 7 * ny + 31 * nz, generic=True)
+    _adjoint(gd, u, shape, 1 / 64, lim, rs)
+
+
+@pytest.mark.parametrize("n", [24, 25])
+def test_periodic_adjoint(gd, n):
+    # the turbulent box, as in the other periodic adjoint tests: a shocked patch
+    # closed periodically has slopes that are rounding noise, where a limiter's
+    # branch is decided by that noise and both sides are valid subgradients
+    _adjoint(gd, inputs.turbulent_box(n, mach=1.0), (n, n, n), 1 / n, "minmod", "hllc",
+             periodic=True)
+
+
+@pytest.mark.parametrize("nz", [512, 513])
+def test_time_step_of_the_last_workgroup(gd, nz):
+    """A 16 x 8 column stepped in z-ranges of one plane: nz workgroups."""
+    import torch
+    u = inputs.random_patch(16, 8, nz, seed=nz, generic=True)
+    dx = 1 / 64
+    dt = oracle.cfl_dt(u, G, dx)
+    say("time step of the last workgroup", nz)
+    gd.set_config(torch.float64, shape_single="16x8", zlen_single=1)
+    try:
+        for cfl in (0.5, 0.3):          # the counter and the maximum are left clear
+            nxt = torch.zeros(1, dtype=torch.float64, device="cuda")
+            out, _ = gd.step(dev(u), G, dx, dt, cfl=cfl, dt_next=nxt)
+            want = oracle.cfl_dt(host(out), G, dx, cfl, periodic=True)
+            assert abs(float(host(nxt)[0]) - want) <= 1e-14 * want
+            assert np.array_equal(host(nxt), host(gd.cfl_dt(out, G, dx, cfl, periodic=True)))
+    finally:
+        gd.set_config(torch.float64)
