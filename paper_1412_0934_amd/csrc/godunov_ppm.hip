@@ -1236,14 +1236,6 @@ ppm_ring_traced(const double (&w)[5][NY][NX], int ly, int lx, const double W[5],
     floored(fma(-lam, t[4], v[4] + (ring_lo ? tl[4] : tu[4])), ph.p_floor, hits);
 }
 
-// An index that is used in a rare branch only: computed there, and not kept in
-// a register by the whole march.
-__device__ __forceinline__ int rarely(int i)
-{
-    asm volatile("" : "+v"(i));
-    return i;
-}
-
 // The same step in double precision (the single-precision tile above keeps its
 // arithmetic bit for bit, which these forms would not: the time step of a
 // single-precision state is a double that callers compare far below a single
@@ -1293,8 +1285,8 @@ __device__ void ppm_march(const PatchDesc &P, const double *__restrict__ u_in_ba
     constexpr uint32_t ES = sizeof(double);
     static_assert(ppm_halo_cells<TX, TY>() <= Geo::NT, "one halo cell per thread at most");
     static_assert(Geo::NINT % 64 == 0, "interior columns fill whole waves");
-    const int tid = threadIdx.x;
-    const bool tile_wave = __builtin_amdgcn_readfirstlane(tid) < Geo::NINT;
+    const int tid = threadIdx.x, first = __builtin_amdgcn_readfirstlane(tid);
+    const bool tile_wave = first < Geo::NINT;
     const int ax = min(TX, P.nx - x0);
     const int ay = min(TY, P.ny - y0);
     const InputView view = make_view(P);
@@ -1329,7 +1321,7 @@ __device__ void ppm_march(const PatchDesc &P, const double *__restrict__ u_in_ba
     int hi = 0, hj = 0;
     const int nhalo = 4 * ax + 4 * ay + 12;
     const bool halo = tid < nhalo, near = tid < 2 * (ax + ay);
-    const bool halo_wave = __builtin_amdgcn_readfirstlane(tid) < nhalo;
+    const bool halo_wave = first < nhalo;
     if (halo) {
         const int h = tid;
         if (h < 4 * ay + 4 * ax) {

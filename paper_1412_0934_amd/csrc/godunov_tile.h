@@ -170,6 +170,14 @@ __device__ __forceinline__ void cfl_finish(double v, const CflOut &co)
 }
 
 
+// An index that is used in a rare branch only: computed there, and not kept in
+// a register by the whole march.
+__device__ __forceinline__ int rarely(int i)
+{
+    asm volatile("" : "+v"(i));
+    return i;
+}
+
 // ------------------------------------------------------------ the tile march
 
 template <typename T, int TX, int TY>
@@ -195,21 +203,27 @@ enum { ROLE_NONE = -1, ROLE_INT = 0, ROLE_BOTTOM = 1, ROLE_TOP = 2, ROLE_LEFT = 
 // states, and an epilogue plane z1 that only produces the z- face states):
 //   I   the x-y flux divergence of plane k-1; slopes, predictor and face
 //       states of plane k; the z face below the plane, which completes and
-//       stores plane k-1;
+//       stores plane k-1; the loads of the column's plane k+2 and of the halo's
+//       plane k+1;
 //   II  the plane's x and y faces (interior columns their upper ones, the
-//       ring columns to the left and below the tile's first ones); the
-//       column's plane k+2 from its loads, plane k+1 staged in LDS.
-// Two barriers a plane. The march is bound by latency, not by issue (a 2%
-// gain from 15% fewer vector instructions): what counts is how much work
-// stands between barriers, and registers and LDS for three workgroups per CU.
-// Against both states of every face passed through LDS to a thread picked for
-// the face, with four barriers a plane: 256^3 FP64 box with 24x8 tiles and
-// z-ranges of 32 planes 0.713 -> 0.641 ms, 250 x 190 x 141 FP32 with 24x8 / 16
-// 0.181 -> 0.165 ms, the 4096-patch batch in 16x8 tiles 1.210 -> 1.151 ms. Vector
-// instructions issue in 63% of the cycles (11.4 per cell), and 65 LDS
-// accesses per column and plane stand where 98 did. Loading U(k-1) before the
-// slopes instead of where it is used spills 14 registers; a fifth wave per
-// SIMD in FP32 spills 10 and is 4% (batch: 20%) slower.
+//       ring columns to the left and below the tile's first ones); plane k+1
+//       staged in LDS, the column's plane k+2 converted.
+// Two barriers a plane. Interior columns fill whole waves and the ring columns
+// the rest, so the branch between the two is scalar, and both run unmasked:
+// lanes without a column compute on the tile's first one, and neither write nor
+// count. What a masked branch may or may not set occupies its registers
+// throughout the branch, and the registers are what bounds the march: they set
+// the waves per SIMD (three in FP64, four to five in FP32), a spilled prefetch
+// costs a wait for each value, and vector instructions alone are cheap (a 2%
+// gain from 15% fewer). The loads are issued where registers are free, behind
+// the z face, with the faces of phase II before their use; U(k-1) before the
+// slopes.
+// Measured, against both states of every face passed through LDS to a thread
+// picked for the face, with four barriers a plane, and then against masked roles
+// with loads a plane ahead: 4096 patches of 8^3 to 32^3 FP64 2.03 -> 1.10 -> 0.97
+// ms (the first with its tile choice), 250 x 190 x 141 FP32 0.336 -> 0.176 ->
+// 0.172 ms, 256^3 FP64 box 1.04 -> 0.640 -> 0.653 ms; two-level step of a 128^3
+// box and 1024 small patches 0.761 -> 0.592 -> 0.573 ms.
 // STREAM_OUT: write the new state with streaming (non-temporal) stores. The
 // batched launches do: there the outputs of many small patches would
 // otherwise evict from the L2 the inputs that neighbouring tiles still read
@@ -225,18 +239,24 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
 {
 #pragma clang fp contract(off)
     using Geo = TileGeom<TX, TY, NT>;
-    const int tid = threadIdx.x;
+    static_assert(Geo::NINT % 64 == 0, "interior columns fill whole waves");
+    const int tid = threadIdx.x, first = __builtin_amdgcn_readfirstlane(tid);
     const int ax = min(TX, P.nx - x0);
     const int ay = min(TY, P.ny - y0);
     const InputView view = make_view(P);
     const T *__restrict__ uin = u_in_base + P.in_off;
 
     // ---- role of this thread: an interior column, a ring column, or none
+    // (which computes on the tile's first column, and neither writes nor counts)
+    const bool tile_wave = first < Geo::NINT;
+    const bool live = tile_wave ? first / TX < ay : first - Geo::NINT < 2 * (ax + ay);
     int ci = 0, cj = 0, role = ROLE_NONE;
     if (tid < Geo::NINT) {
-        ci = tid % TX;
-        cj = tid / TX;
-        if (ci < ax && cj < ay) role = ROLE_INT;
+        if (tid % TX < ax && tid / TX < ay) {
+            ci = tid % TX;
+            cj = tid / TX;
+            role = ROLE_INT;
+        }
     } else {
         int r = tid - Geo::NINT;
         if (r < ax) { ci = r; cj = -1; role = ROLE_BOTTOM; }
@@ -245,7 +265,6 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
         else if (r < 2 * ax + 2 * ay) { ci = ax; cj = r - 2 * ax - ay; role = ROLE_RIGHT; }
     }
     const bool owner = role != ROLE_NONE;
-    const bool interior = role == ROLE_INT;
     // a ring column has one face with the tile: an x face for the left and
     // right columns, a y face for the bottom and top rows; the left and bottom
     // columns hold its left (lower) state and solve it
@@ -254,14 +273,13 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
     const int gi = x0 + ci, gj = y0 + cj;     // patch coordinates of the owned column
     const uint32_t col = (uint32_t)view.column(gi, gj) * (uint32_t)sizeof(T);
     // the face solved first (interior: the upper x face)
-    const int face1 = interior ? Geo::xface(ci + 1, cj)
-                               : (ring_x ? Geo::xface(ci + ring_lo, cj) : Geo::yface(ci, cj + ring_lo));
-    const bool solves = interior || ring_lo;
+    const int face1 = tile_wave ? Geo::xface(ci + 1, cj)
+                                : (ring_x ? Geo::xface(ci + ring_lo, cj) : Geo::yface(ci, cj + ring_lo));
 
     // ---- depth-2 halo and depth-1 corner cells of a plane, one per thread
     int hi = 0, hj = 0;
     const int nhalo = 2 * ax + 2 * ay + 4;
-    const bool halo = tid < nhalo;
+    const bool halo = tid < nhalo, halo_wave = first < nhalo;
     if (halo) {
         int h = tid;
         if (h < ax) { hi = h; hj = -2; }
@@ -287,64 +305,49 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
     const uint32_t ocol = (uint32_t)(gj * P.nx + gi) * (uint32_t)sizeof(T);
 
     // ---- registers of the owned column
-    T Wm[5], W0[5], Wp[5], inv0 = T(1), invp = T(1);
+    T Wm[5], W0[5], Wp[5], inv0, invp;
     T zprev[5], acc[5];
     T up1[5], up2[5];       // upper-face states, then the fluxes solved from them
-#pragma unroll
-    for (int q = 0; q < 5; ++q) {
-        Wm[q] = W0[q] = Wp[q] = T(0);
-        zprev[q] = acc[q] = up1[q] = up2[q] = T(0);
-    }
-
-    // Column loads run one plane ahead of their use: the raw conserved state
-    // of plane k+2 (Upf) and of the halo of plane k+1 (Hpf) are in flight
-    // while plane k is computed. The last plane a column reads is z1+1 for an
-    // interior column and z1 for a ring column.
-    const int last_plane = interior ? z1 + 1 : z1;
-    T Upf[5], Hpf[5];
-#pragma unroll
-    for (int q = 0; q < 5; ++q) Upf[q] = Hpf[q] = T(0);
-
-    // prologue: planes z0-2 (interior only), z0-1 and z0, and the loads of
-    // plane z0+1
-    if (owner) {
-        T Ua[5], Ub[5], Uc[5], inv;
-        if (interior) load5_plane(uin + view.plane(z0 - 2), view.vstride, col, Ua);
-        load5_plane(uin + view.plane(z0 - 1), view.vstride, col, Ub);
-        load5_plane(uin + view.plane(z0), view.vstride, col, Uc);
-        if (halo) load5_plane(uin + view.plane(z0), view.vstride, hcol, Hpf);
-        if (z0 + 1 <= last_plane) load5_plane(uin + view.plane(z0 + 1), view.vstride, col, Upf);
-        if (interior) prim_from_cons(Ua, Wm, inv, ph, hits);
-        prim_from_cons(Ub, W0, inv0, ph, hits);
-        prim_from_cons(Uc, Wp, invp, ph, hits);
-    } else if (halo) {
-        load5_plane(uin + view.plane(z0), view.vstride, hcol, Hpf);
-    }
-
+    int col_hits = 0, halo_hits = 0;
     const int lx = ci + 2, ly = cj + 2;
     const T half = T(0.5);
-    if (owner) {
+
+    // prologue: planes z0-2 (used by interior columns only), z0-1 and z0
+    {
+        T Ua[5], Ub[5], Uc[5], inv;
+        load5_plane(uin + view.plane(z0 - 2), view.vstride, col, Ua);
+        load5_plane(uin + view.plane(z0 - 1), view.vstride, col, Ub);
+        load5_plane(uin + view.plane(z0), view.vstride, col, Uc);
+        int below = 0;
+        prim_from_cons(Ua, Wm, inv, ph, below);
+        if (tile_wave) col_hits += below;
+        prim_from_cons(Ub, W0, inv0, ph, col_hits);
+        prim_from_cons(Uc, Wp, invp, ph, col_hits);
 #pragma unroll
-        for (int q = 0; q < 5; ++q) sm.w[q][ly][lx] = W0[q];
+        for (int q = 0; q < 5; ++q) {
+            if (owner) sm.w[q][ly][lx] = W0[q];
+            zprev[q] = acc[q] = up1[q] = up2[q] = T(0);
+        }
     }
     __syncthreads();
     int b = 0;
+#pragma unroll 1
     for (int k = z0 - 1;; ++k, b ^= 1) {
         const bool pre = k < z0;
         const bool post = k == z1;
         T(&f)[5][Geo::NF] = sm.f[b];
 
         // ---- I
-        if (interior) {
-            if (k > z0) {
+        if (live) {
+            if (tile_wave && k > z0) {
                 const T(&g)[5][Geo::NF] = sm.f[b ^ 1];
 #pragma unroll
                 for (int q = 0; q < 5; ++q)
                     acc[q] = ((up1[q] - g[q][Geo::xface(ci, cj)]) +
                               (up2[yslot(q)] - g[yslot(q)][Geo::yface(ci, cj)])) + acc[q];
             }
-        }
-        if (interior || (owner && !pre && !post)) {
+            T Uold[5];
+            load5_plane(uin + view.plane(max(k - 1, z0 - 1)), view.vstride, col, Uold);
             T Sx[5], Sy[5], Sz[5], Ws[5];
 #pragma unroll
             for (int q = 0; q < 5; ++q) {
@@ -354,7 +357,7 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
                 Sz[q] = limited_slope<LIM>(c - Wm[q], Wp[q] - c);
             }
             predictor(W0, inv0, Sx, Sy, Sz, lam, ph.gamma, Ws);
-            if (interior) {
+            if (tile_wave) {
                 T zm[5], zpn[5], dx[5], dy[5];
 #pragma unroll
                 for (int q = 0; q < 5; ++q) {
@@ -362,7 +365,7 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
                     zpn[q] = fma(half, Sz[q], Ws[q]);
                     dx[q] = fma(-half, Sx[q], Ws[q]);
                     up1[q] = fma(half, Sx[q], Ws[q]);
-                    dy[q] = fma(-half, Sy[q], Ws[q]);
+                    dy[yslot(q)] = fma(-half, Sy[q], Ws[q]);
                     up2[yslot(q)] = fma(half, Sy[q], Ws[q]);
                 }
                 // the lowest of the six densities and of the six pressures: a
@@ -373,11 +376,11 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
                 if (__builtin_expect(rmin < ph.rho_floor || pmin < ph.p_floor, 0)) {
                     // the prologue and epilogue planes use (and count) one state
                     int none = 0;
-                    int &xy = pre || post ? none : hits;
-                    zm[0] = floored(zm[0], ph.rho_floor, pre ? none : hits);
-                    zm[4] = floored(zm[4], ph.p_floor, pre ? none : hits);
-                    zpn[0] = floored(zpn[0], ph.rho_floor, post ? none : hits);
-                    zpn[4] = floored(zpn[4], ph.p_floor, post ? none : hits);
+                    int &xy = pre || post ? none : col_hits;
+                    zm[0] = floored(zm[0], ph.rho_floor, pre ? none : col_hits);
+                    zm[4] = floored(zm[4], ph.p_floor, pre ? none : col_hits);
+                    zpn[0] = floored(zpn[0], ph.rho_floor, post ? none : col_hits);
+                    zpn[4] = floored(zpn[4], ph.p_floor, post ? none : col_hits);
                     dx[0] = floored(dx[0], ph.rho_floor, xy);
                     dx[4] = floored(dx[4], ph.p_floor, xy);
                     up1[0] = floored(up1[0], ph.rho_floor, xy);
@@ -387,34 +390,39 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
                     up2[0] = floored(up2[0], ph.rho_floor, xy);
                     up2[4] = floored(up2[4], ph.p_floor, xy);
                 }
+                if (owner) {
 #pragma unroll
-                for (int q = 0; q < 5; ++q) {
-                    f[q][Geo::xface(ci, cj)] = dx[q];
-                    f[yslot(q)][Geo::yface(ci, cj)] = dy[q];
+                    for (int q = 0; q < 5; ++q) {
+                        f[q][Geo::xface(ci, cj)] = dx[q];
+                        f[q][Geo::yface(ci, cj)] = dy[q];
+                    }
                 }
                 if (!pre) {
                     // the z face below the plane; completes plane k-1
                     T F[5];
                     face_flux<RS, 2, SQ_Z>(zprev, zm, ph, F);
-                    if (want_flux && (k == 0 || k == P.nz)) {
+                    if (want_flux && owner && (k == 0 || k == P.nz)) {
                         T *sheet = bf + 10 * sxs + 10 * sys + (k == 0 ? 0 : 5 * szs);
+                        const int at = rarely(gj) * P.nx + rarely(gi);
 #pragma unroll
-                        for (int q = 0; q < 5; ++q) sheet[q * szs + (int64_t)gj * P.nx + gi] = F[q];
+                        for (int q = 0; q < 5; ++q) sheet[q * szs + at] = F[q];
                     }
                     if (k > z0) {
                         // U' = U - dt/dx (acc + F_z(k-1/2)), acc = div_xy(k-1) - F_z(k-3/2)
-                        T Uold[5], Un[5];
-                        load5_plane(uin + view.plane(k - 1), view.vstride, col, Uold);
+                        T Un[5];
                         T *o = out + (int64_t)(k - 1) * P.nx * P.ny;
 #pragma unroll
-                        for (int q = 0; q < 5; ++q) {
-                            Un[q] = fma(-dtdx, acc[q] + F[q], Uold[q]);
-                            T *dst = reinterpret_cast<T *>(
-                                reinterpret_cast<char *>(o + q * ostride) + ocol);
-                            if constexpr (STREAM_OUT) __builtin_nontemporal_store(Un[q], dst);
-                            else *dst = Un[q];
+                        for (int q = 0; q < 5; ++q) Un[q] = fma(-dtdx, acc[q] + F[q], Uold[q]);
+                        if (owner) {
+#pragma unroll
+                            for (int q = 0; q < 5; ++q) {
+                                T *dst = reinterpret_cast<T *>(
+                                    reinterpret_cast<char *>(o + q * ostride) + ocol);
+                                if constexpr (STREAM_OUT) __builtin_nontemporal_store(Un[q], dst);
+                                else *dst = Un[q];
+                            }
                         }
-                        if (want_cfl) {
+                        if (want_cfl && owner) {
                             // signal speed of the new state, exactly as cfl_dt computes it
                             int unused = 0;
                             smax = fmax(smax, cell_signal(Un, ph, unused) * inv_dx);
@@ -425,60 +433,77 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
                 }
 #pragma unroll
                 for (int q = 0; q < 5; ++q) zprev[q] = zpn[q];
-            } else {
+            } else if (!pre && !post) {
                 // a ring column: the one state its face with the tile needs,
                 // direction and side selected per lane
                 T st[5];
 #pragma unroll
                 for (int q = 0; q < 5; ++q)
                     st[q] = fma(ring_lo ? half : -half, ring_x ? Sx[q] : Sy[q], Ws[q]);
-                st[0] = floored(st[0], ph.rho_floor, hits);
-                st[4] = floored(st[4], ph.p_floor, hits);
+                st[0] = floored(st[0], ph.rho_floor, col_hits);
+                st[4] = floored(st[4], ph.p_floor, col_hits);
+                const T y[5] = { st[0], st[2], st[3], st[1], st[4] };
 #pragma unroll
-                for (int q = 0; q < 5; ++q) up1[q] = ring_x ? st[q] : st[q == 1 ? 2 : (q == 2 ? 3 : (q == 3 ? 1 : q))];
-                if (!ring_lo) {
+                for (int q = 0; q < 5; ++q) up1[q] = ring_x ? st[q] : y[q];
+                if (owner && !ring_lo) {
 #pragma unroll
                     for (int q = 0; q < 5; ++q) f[q][face1] = up1[q];
                 }
             }
         }
         if (post) break;
+        __builtin_amdgcn_sched_barrier(0);
+        T Upf[5], Hpf[5];
+        load5_plane(uin + view.plane(k + 2), view.vstride, col, Upf);
+        load5_plane(uin + view.plane(k + 1), view.vstride, hcol, Hpf);
         __syncthreads();
 
         // ---- II
-        if (!pre && solves) {
+        if (!pre && live) {
             T R[5], G[5];
 #pragma unroll
             for (int q = 0; q < 5; ++q) R[q] = f[q][face1];
             riemann<RS, SQ_XY>(up1, R, ph, G);
 #pragma unroll
-            for (int q = 0; q < 5; ++q) f[q][face1] = up1[q] = G[q];
-            if (want_flux) {
-                // the face's index along its axis: gi+1 (an interior column's
-                // upper face, or the left ring's), gj+1 for the bottom ring
-                if (interior || ring_x) {
-                    if (gi + 1 == (interior ? P.nx : 0)) {
-                        T *sheet = bf + (interior ? 5 * sxs : 0);
+            for (int q = 0; q < 5; ++q) up1[q] = G[q];
+            if (tile_wave ? owner : ring_lo) {
 #pragma unroll
-                        for (int q = 0; q < 5; ++q) sheet[q * sxs + (int64_t)k * P.ny + gj] = G[q];
+                for (int q = 0; q < 5; ++q) f[q][face1] = G[q];
+                if (want_flux) {
+                    // the face's index along its axis: gi+1 (an interior
+                    // column's upper face, or the left ring's), gj+1 for the
+                    // bottom ring
+                    if (tile_wave || ring_x) {
+                        if (gi + 1 == (tile_wave ? P.nx : 0)) {
+                            T *sheet = bf + (tile_wave ? 5 * sxs : 0);
+                            const int at = k * P.ny + rarely(gj);
+#pragma unroll
+                            for (int q = 0; q < 5; ++q) sheet[q * sxs + at] = G[q];
+                        }
+                    } else if (gj + 1 == 0) {
+                        T *sheet = bf + 10 * sxs;
+                        const int at = k * P.nx + rarely(gi);
+#pragma unroll
+                        for (int q = 0; q < 5; ++q) sheet[q * sys + at] = G[yslot(q)];
                     }
-                } else if (gj + 1 == 0) {
-                    T *sheet = bf + 10 * sxs;
-#pragma unroll
-                    for (int q = 0; q < 5; ++q) sheet[q * sys + (int64_t)k * P.nx + gi] = G[yslot(q)];
                 }
             }
-            if (interior) {
+            if (tile_wave) {
                 const int face2 = Geo::yface(ci, cj + 1);
 #pragma unroll
                 for (int q = 0; q < 5; ++q) R[q] = f[q][face2];
                 riemann<RS, SQ_XY>(up2, R, ph, G);
 #pragma unroll
-                for (int q = 0; q < 5; ++q) f[q][face2] = up2[q] = G[q];
-                if (want_flux && gj + 1 == P.ny) {
-                    T *sheet = bf + 10 * sxs + 5 * sys;
+                for (int q = 0; q < 5; ++q) up2[q] = G[q];
+                if (owner) {
 #pragma unroll
-                    for (int q = 0; q < 5; ++q) sheet[q * sys + (int64_t)k * P.nx + gi] = G[yslot(q)];
+                    for (int q = 0; q < 5; ++q) f[q][face2] = G[q];
+                    if (want_flux && gj + 1 == P.ny) {
+                        T *sheet = bf + 10 * sxs + 5 * sys;
+                        const int at = k * P.nx + rarely(gi);
+#pragma unroll
+                        for (int q = 0; q < 5; ++q) sheet[q * sys + at] = G[yslot(q)];
+                    }
                 }
             }
         }
@@ -492,20 +517,24 @@ __device__ void godunov_tile(const PatchDesc &P, const T *__restrict__ u_in_base
         if (owner) {
 #pragma unroll
             for (int q = 0; q < 5; ++q) sm.w[q][ly][lx] = W0[q];
-            if (k + 2 <= last_plane) {
-                prim_from_cons_march(Upf, Wp, invp, ph, hits);
-                if (k + 3 <= last_plane) load5_plane(uin + view.plane(k + 3), view.vstride, col, Upf);
-            }
         }
-        if (halo && k + 1 < z1) {
+        if (live) {
+            int own = 0;
+            prim_from_cons_march(Upf, Wp, invp, ph, own);
+            // (a ring column uses planes up to z1, an interior one z1+1)
+            if (tile_wave || k + 2 <= z1) col_hits += own;
+        }
+        if (halo_wave && k + 1 < z1) {
             T Wh[5], invh;
-            prim_from_cons_march(Hpf, Wh, invh, ph, hits);
+            prim_from_cons_march(Hpf, Wh, invh, ph, halo_hits);
+            if (halo) {
 #pragma unroll
-            for (int q = 0; q < 5; ++q) sm.w[q][hj + 2][hi + 2] = Wh[q];
-            if (k + 2 < z1) load5_plane(uin + view.plane(k + 2), view.vstride, hcol, Hpf);
+                for (int q = 0; q < 5; ++q) sm.w[q][hj + 2][hi + 2] = Wh[q];
+            }
         }
         __syncthreads();
     }
+    hits += (owner ? col_hits : 0) + (halo ? halo_hits : 0);
 }
 
 __device__ __forceinline__ void flush_hits(int hits, unsigned long long *counter)
