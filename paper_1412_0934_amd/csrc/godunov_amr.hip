@@ -17,8 +17,8 @@
 //            the four fine boundary fluxes;
 //   average  one thread per covered coarse cell: the mean of its eight
 //            children, summed as a fixed pairwise tree.
-// The work is a few percent of the step's and bound by latency and HBM
-// gathers, so the kernels stay plain: no LDS staging, 32-bit indexing.
+// The work is bound by latency and HBM gathers, so the kernels stay plain: no
+// LDS staging, 32-bit indexing, pairs of neighbouring values in one access.
 #include "godunov_cell.h"
 #include "godunov_internal.h"
 
@@ -36,12 +36,43 @@ constexpr int SEAM_BLOCK = 128;
 // positions lie in [-2, 2 nc + 1) of a fine extent 2 nc >= 2)
 __device__ __forceinline__ int wrap(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
+// Two neighbouring values (i, i + 1) of a row in one access. PAIR: i is even
+// and the array starts on a multiple of two values, so the pair is aligned;
+// every patch extent is even, so that holds for all patches of a plan whose
+// offsets are even. Else two accesses.
+template <typename T>
+struct alignas(2 * sizeof(T)) Pair {
+    T a, b;
+};
+
+template <bool PAIR, typename T>
+__device__ __forceinline__ Pair<T> load_pair(const T *__restrict__ p)
+{
+    if constexpr (PAIR) return *reinterpret_cast<const Pair<T> *>(p);
+    else return { p[0], p[1] };
+}
+
+template <bool PAIR, typename T>
+__device__ __forceinline__ void store_pair(T *__restrict__ p, T a, T b)
+{
+    if constexpr (PAIR) {
+        *reinterpret_cast<Pair<T> *>(p) = { a, b };
+    } else {
+        p[0] = a;
+        p[1] = b;
+    }
+}
+
 // One thread per cell of the one-coarse-cell shell around a patch (its two
 // fine ghost layers are exactly the eight children of each shell cell):
 // the eight children come from the fine patch covering the shell cell, or
 // from the limited linear prolongation of the coarse cell, whose slopes are
-// computed once for all eight.
-template <typename T>
+// computed once for all eight. Shell cells in the order of AmrFillItem.
+// Bound by memory instructions and the chain of table look-ups before them:
+// pairs in place of single values, every load of a cell before its first store,
+// and no threads for the footprint inside the shell took the fill of 1024 small
+// patches (2.9 M ghost cells) from 107 to 82 us.
+template <typename T, bool PAIR>
 __global__ __launch_bounds__(FILL_BLOCK) void fill_kernel(AmrTables t, const T *__restrict__ coarse,
                                                           T *__restrict__ fine)
 {
@@ -49,9 +80,25 @@ __global__ __launch_bounds__(FILL_BLOCK) void fill_kernel(AmrTables t, const T *
     const AmrPatch P = t.patches[it.patch];
     const int sx = P.n[0] / 2 + 2, sy = P.n[1] / 2 + 2, sz = P.n[2] / 2 + 2;
     const int idx = it.start + (int)threadIdx.x;
-    if (idx >= sx * sy * sz) return;
-    const int ci = idx % sx, cj = (idx / sx) % sy, ck = idx / (sx * sy);
-    if (ci >= 1 && ci < sx - 1 && cj >= 1 && cj < sy - 1 && ck >= 1 && ck < sz - 1) return;
+    if (idx >= amr_shell_cells(P)) return;
+    int ci, cj, ck;
+    if (idx < 2 * sx * sy) {
+        const bool top = idx >= sx * sy;
+        const int e = idx - (top ? sx * sy : 0);
+        ci = e % sx;
+        cj = e / sx;
+        ck = top ? sz - 1 : 0;
+    } else {
+        const int per = 2 * (sx + sy - 2), r = idx - 2 * sx * sy, e = r % per;
+        ck = 1 + r / per;
+        if (e < 2 * sx) {
+            ci = e < sx ? e : e - sx;
+            cj = e < sx ? 0 : sy - 1;
+        } else {
+            ci = (e & 1) ? sx - 1 : 0;
+            cj = 1 + (e - 2 * sx) / 2;
+        }
+    }
     const int nx = t.nc[0], ny = t.nc[1], nz = t.nc[2];
     // the shell cell, periodic over the coarse box
     const int cx = wrap(P.lo[0] + ci - 1, nx), cy = wrap(P.lo[1] + cj - 1, ny);
@@ -69,16 +116,24 @@ __global__ __launch_bounds__(FILL_BLOCK) void fill_kernel(AmrTables t, const T *
         const int li = 2 * (cx - Q.lo[0]) + 2, lj = 2 * (cy - Q.lo[1]) + 2, lk = 2 * (cz - Q.lo[2]) + 2;
         const T *src = fine + Q.in_off + ((int64_t)lk * qy + lj) * qx + li;
         const int64_t vs = (int64_t)qx * qy * (Q.n[2] + 4);
+        // all loads in flight before the first store: interior cells are only
+        // read and ghost cells only written, which the compiler cannot know
+        Pair<T> v[5][2][2];
 #pragma unroll
         for (int c = 0; c < 5; ++c)
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
                 for (int j = 0; j < 2; ++j)
+                    v[c][k][j] = load_pair<PAIR>(src + c * vs + ((int64_t)k * qy + j) * qx);
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        dst[c * dvs + ((int64_t)k * gy + j) * gx + i] =
-                            src[c * vs + ((int64_t)k * qy + j) * qx + i];
+        for (int c = 0; c < 5; ++c)
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    store_pair<PAIR>(dst + c * dvs + ((int64_t)k * gy + j) * gx, v[c][k][j].a,
+                                     v[c][k][j].b);
         return;
     }
     // limited linear prolongation: per variable the minmod slope along each
@@ -91,22 +146,33 @@ __global__ __launch_bounds__(FILL_BLOCK) void fill_kernel(AmrTables t, const T *
     const int ym = cy > 0 ? -ox : (ny - 1) * ox, yp = cy < ny - 1 ? ox : (1 - ny) * ox;
     const int zm = cz > 0 ? -oy : (nz - 1) * oy, zp = cz < nz - 1 ? oy : (1 - nz) * oy;
     const T *c0 = coarse + cidx;
+    T u[5][7];
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
-        const T *u = c0 + c * vs;
-        const T uc = u[0];
-        const T Sx = limited_slope<LIM_MINMOD>(uc - u[xm], u[xp] - uc);
-        const T Sy = limited_slope<LIM_MINMOD>(uc - u[ym], u[yp] - uc);
-        const T Sz = limited_slope<LIM_MINMOD>(uc - u[zm], u[zp] - uc);
+        const T *p = c0 + c * vs;
+        u[c][0] = p[0];
+        u[c][1] = p[xm]; u[c][2] = p[xp];
+        u[c][3] = p[ym]; u[c][4] = p[yp];
+        u[c][5] = p[zm]; u[c][6] = p[zp];
+    }
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+        const T uc = u[c][0];
+        const T Sx = limited_slope<LIM_MINMOD>(uc - u[c][1], u[c][2] - uc);
+        const T Sy = limited_slope<LIM_MINMOD>(uc - u[c][3], u[c][4] - uc);
+        const T Sz = limited_slope<LIM_MINMOD>(uc - u[c][5], u[c][6] - uc);
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < 2; ++j) {
+                T v[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     const T tx = i ? Sx : -Sx, ty = j ? Sy : -Sy, tz = k ? Sz : -Sz;
-                    dst[c * dvs + ((int64_t)k * gy + j) * gx + i] = uc + T(0.25) * ((tx + ty) + tz);
+                    v[i] = uc + T(0.25) * ((tx + ty) + tz);
                 }
+                store_pair<PAIR>(dst + c * dvs + ((int64_t)k * gy + j) * gx, v[0], v[1]);
+            }
     }
 }
 
@@ -200,7 +266,7 @@ __global__ __launch_bounds__(SEAM_BLOCK) void face_state_kernel(AmrTables t,
 // order (coarse flux from the staged face states, applied component by
 // component in the rotated frame); the rest: averaging down of one covered
 // cell.
-template <typename T, int RS>
+template <typename T, int RS, bool PAIR>
 __global__ __launch_bounds__(SEAM_BLOCK) void seam_kernel(AmrTables t, T *__restrict__ coarse_new,
                                                           const T *__restrict__ fine_out,
                                                           const T *__restrict__ fine_flux,
@@ -229,7 +295,8 @@ __global__ __launch_bounds__(SEAM_BLOCK) void seam_kernel(AmrTables t, T *__rest
             for (int k = 0; k < 5; ++k) {
                 const int q = rotated_var(k, d);
                 const T *v = fine_flux + fc.fine + (int64_t)q * fc.vstride;
-                T Ff = ((v[0] + v[1]) + (v[fc.row] + v[fc.row + 1])) * T(0.25);
+                const Pair<T> v0 = load_pair<PAIR>(v), v1 = load_pair<PAIR>(v + fc.row);
+                T Ff = ((v0.a + v0.b) + (v1.a + v1.b)) * T(0.25);
                 U[q * n] += upper_side ? c * (Ff - G[k]) : c * (G[k] - Ff);
             }
         }
@@ -244,13 +311,34 @@ __global__ __launch_bounds__(SEAM_BLOCK) void seam_kernel(AmrTables t, T *__rest
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
         const T *v = ch + q * vs;
-        T z0 = (v[0] + v[1]) + (v[sy] + v[sy + 1]);
-        T z1 = (v[sz] + v[sz + 1]) + (v[sz + sy] + v[sz + sy + 1]);
+        const Pair<T> a0 = load_pair<PAIR>(v), a1 = load_pair<PAIR>(v + sy);
+        const Pair<T> b0 = load_pair<PAIR>(v + sz), b1 = load_pair<PAIR>(v + sz + sy);
+        T z0 = (a0.a + a0.b) + (a1.a + a1.b);
+        T z1 = (b0.a + b0.b) + (b1.a + b1.b);
         coarse_new[cv.coarse + q * n] = (z0 + z1) * T(0.125);
     }
 }
 
 __global__ void set_scalar_kernel(double *dst, double v) { *dst = v; }
+
+// Whether an array starts on a multiple of two values.
+template <typename T>
+bool on_pair(const void *p)
+{
+    return (uintptr_t)p % (2 * sizeof(T)) == 0;
+}
+
+template <typename T>
+int launch_fill_t(const AmrTables &t, const void *coarse, void *fine, hipStream_t s)
+{
+    if (t.even_in && on_pair<T>(fine))
+        hipLaunchKernelGGL((fill_kernel<T, true>), dim3(t.nfill), dim3(FILL_BLOCK), 0, s, t,
+                           (const T *)coarse, (T *)fine);
+    else
+        hipLaunchKernelGGL((fill_kernel<T, false>), dim3(t.nfill), dim3(FILL_BLOCK), 0, s, t,
+                           (const T *)coarse, (T *)fine);
+    return (int)hipGetLastError();
+}
 
 template <typename T, int LIM, int RS>
 int launch_seam_t(const AmrTables &t, const void *coarse_old, void *coarse_new, const void *fine_out,
@@ -265,9 +353,15 @@ int launch_seam_t(const AmrTables &t, const void *coarse_old, void *coarse_new, 
     }
     const int total = t.ncells + t.ncover;
     if (total == 0) return 0;
-    hipLaunchKernelGGL((seam_kernel<T, RS>), dim3((total + SEAM_BLOCK - 1) / SEAM_BLOCK),
-                       dim3(SEAM_BLOCK), 0, s, t, (T *)coarse_new, (const T *)fine_out,
-                       (const T *)fine_flux, sc, dx, dt, dt_dev);
+    const dim3 grid((total + SEAM_BLOCK - 1) / SEAM_BLOCK);
+    if (t.even_out && on_pair<T>(fine_out) && on_pair<T>(fine_flux))
+        hipLaunchKernelGGL((seam_kernel<T, RS, true>), grid, dim3(SEAM_BLOCK), 0, s, t,
+                           (T *)coarse_new, (const T *)fine_out, (const T *)fine_flux, sc, dx, dt,
+                           dt_dev);
+    else
+        hipLaunchKernelGGL((seam_kernel<T, RS, false>), grid, dim3(SEAM_BLOCK), 0, s, t,
+                           (T *)coarse_new, (const T *)fine_out, (const T *)fine_flux, sc, dx, dt,
+                           dt_dev);
     return (int)hipGetLastError();
 }
 
@@ -293,13 +387,8 @@ int launch_seam_d(int limiter, int riemann, const AmrTables &t, const void *co, 
 int launch_amr_fill(int dtype, const AmrTables &t, const void *coarse, void *fine, hipStream_t s)
 {
     if (t.nfill == 0) return 0;
-    if (dtype == 1)
-        hipLaunchKernelGGL(fill_kernel<float>, dim3(t.nfill), dim3(FILL_BLOCK), 0, s, t,
-                           (const float *)coarse, (float *)fine);
-    else
-        hipLaunchKernelGGL(fill_kernel<double>, dim3(t.nfill), dim3(FILL_BLOCK), 0, s, t,
-                           (const double *)coarse, (double *)fine);
-    return (int)hipGetLastError();
+    return dtype == 1 ? launch_fill_t<float>(t, coarse, fine, s)
+                      : launch_fill_t<double>(t, coarse, fine, s);
 }
 
 int launch_amr_seam(int dtype, int limiter, int riemann, const AmrTables &t, const void *coarse_old,

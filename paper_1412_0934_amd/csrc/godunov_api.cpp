@@ -1242,11 +1242,14 @@ int gd_amr_create(gd_ctx *ctx, int ncx, int ncy, int ncz, double dx_coarse, int 
         fl_end = std::max<int64_t>(fl_end, P.flux_off + flux_elems(P.n[0], P.n[1], P.n[2]));
     }
 
-    // ghost fill: 256-cell pieces of each patch's one-coarse-cell shell box
+    // ghost fill: 256-cell pieces of each patch's one-coarse-cell shell
     std::vector<gd::AmrFillItem> fill;
+    int64_t odd_in = 0, odd_out = 0;
     for (int p = 0; p < npatch; ++p) {
-        const int box = (dp[p].n[0] / 2 + 2) * (dp[p].n[1] / 2 + 2) * (dp[p].n[2] / 2 + 2);
-        for (int s0 = 0; s0 < box; s0 += 256) fill.push_back(gd::AmrFillItem{ p, s0 });
+        const int shell = gd::amr_shell_cells(dp[p]);
+        for (int s0 = 0; s0 < shell; s0 += 256) fill.push_back(gd::AmrFillItem{ p, s0 });
+        odd_in |= dp[p].in_off & 1;
+        odd_out |= (dp[p].out_off | dp[p].flux_off) & 1;
     }
     // interface faces, per patch, axis, side and footprint cell; grouped by
     // the uncovered cell they correct, in that order
@@ -1358,6 +1361,8 @@ int gd_amr_create(gd_ctx *ctx, int ncx, int ncy, int ncz, double dx_coarse, int 
     t.ncells = (int32_t)cells.size();
     t.ncover = (int32_t)cover.size();
     t.nfaces = (int32_t)faces.size();
+    t.even_in = !odd_in;
+    t.even_out = !odd_out;
     t.owner = (const int32_t *)(base + o_owner);
     t.patches = (const gd::AmrPatch *)(base + o_patch);
     t.fill = (const gd::AmrFillItem *)(base + o_fill);

@@ -150,11 +150,18 @@ struct AmrPatch {
     int64_t in_off, out_off, flux_off;
 };
 
-// 256 consecutive cells of the box of coarse cells around one patch (the
-// patch's footprint and a one-cell shell), for the ghost fill.
+// 256 consecutive cells of the one-coarse-cell shell around one patch, for the
+// ghost fill. The shell's order: the planes below and above the footprint, then
+// plane by plane the rows before and behind it and the cells at its two sides.
 struct AmrFillItem {
     int32_t patch, start;
 };
+
+__host__ __device__ inline int amr_shell_cells(const AmrPatch &P)
+{
+    const int sx = P.n[0] / 2 + 2, sy = P.n[1] / 2 + 2, sz = P.n[2] / 2 + 2;
+    return 2 * sx * sy + 2 * (sx + sy - 2) * (sz - 2);
+}
 
 // One coarse-fine face. right: coarse cell on the + side of the face;
 // dside = 2 d + side, side 1 when the uncovered cell is on the + side;
@@ -177,6 +184,7 @@ struct AmrCover {
 struct AmrTables {
     int32_t nc[3];
     int32_t nfill, ncells, ncover, nfaces;
+    int32_t even_in, even_out;      // all input, all output and flux offsets are even
     const int32_t *owner;           // coarse cell -> covering patch or -1
     const AmrPatch *patches;
     const AmrFillItem *fill;

@@ -119,3 +119,34 @@ def test_time_step_of_the_last_workgroup(gd, nz):
             assert np.array_equal(host(nxt), host(gd.cfl_dt(out, G, dx, cfl, periodic=True)))
     finally:
         gd.set_config(torch.float64)
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("shift,skip", [(1, 0), (0, 1), (1, 1)])
+def test_amr_seams_off_the_pair_grid(gd, dtype, shift, skip):
+    """The seams' paired accesses need even offsets and aligned buffers. Offsets
+    moved by one (shift), buffers that start one value late (skip), and both:
+    the same bits as with neither."""
+    import torch
+    dt_ = getattr(torch, dtype)
+    h = inputs.amr_hierarchy(gamma=G)
+    f = h.fine
+    dt = oracle.cfl_dt(h.coarse, G, h.dx_coarse / 2, 0.3, periodic=True)
+    say("amr seams off the pair grid", dtype, shift, skip)
+
+    def run(shift, skip):
+        t = gd.amr_patch_table(h.lo, h.n, f.u_in_off + shift, f.u_out_off + shift, f.flux_off + shift)
+        plan = gd.AmrPlan((h.nc,) * 3, h.dx_coarse, t)
+
+        def buf(n, fill=-7.0):
+            return torch.full((n + shift + skip,), fill, dtype=dt_, device="cuda")[skip:]
+
+        ci = dev(h.coarse).to(dt_)
+        fi, fo, ff = buf(f.u_in.size), buf(f.u_out_size), buf(f.flux_size)
+        fi[shift:] = dev(np.nan_to_num(f.u_in, nan=-7.0)).to(dt_)
+        co = torch.empty_like(ci)
+        plan.step(ci, fi, G, dt, coarse_out=co, fine_out=fo, fine_flux=ff)
+        return [host(co)] + [host(b[shift:]) for b in (fi, fo, ff)]
+
+    for got, want in zip(run(shift, skip), run(0, 0)):
+        assert np.array_equal(got, want)
