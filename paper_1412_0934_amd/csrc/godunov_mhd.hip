@@ -731,8 +731,9 @@ __device__ __forceinline__ void load9(const T *__restrict__ p, int n, uint32_t a
 // waves, halo loads held by every thread and the slopes kept from the half step
 // to the face states, 70 registers spilled, the prefetched plane among them
 // (its whole latency then stood between two barriers), and a step took
-// 0.635 ms. 128^3 box, dt and ch on the device: 0.333 ms a step against 0.593 ms
-// for the two launches over 54 staged values per cell.
+// 0.635 ms; with the interior lanes masked one by one, 16 spilled and 0.332 ms.
+// 128^3 box, dt and ch on the device: 0.304 ms a step against 0.591 ms for the
+// two launches over 54 staged values per cell.
 template <typename T, int LIM, int TX, int TY>
 __global__ __launch_bounds__(tile_threads(TX, TY))
 __attribute__((amdgpu_waves_per_eu(2))) void k_step(
@@ -769,10 +770,14 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_step(
     // has no z face, no update and no second face, and stages the halo instead,
     // so neither side pays registers for what the other one holds.
     if (uniform(tid >> 6) < Geo::NINT / 64) {
-        const int ci = tid % TX, cj = tid / TX;
-        const bool own = ci < ax && cj < ay;
+        // lanes outside a clipped tile compute on its first column, and neither
+        // write nor reduce: what a masked branch may or may not set would keep
+        // its registers throughout the branch
+        const bool own = tid % TX < ax && tid / TX < ay;
+        const bool live = uniform(tid) / TX < ay;
+        const int ci = own ? tid % TX : 0, cj = own ? tid / TX : 0;
         const int lx = ci + 2, ly = cj + 2;
-        const uint32_t col = own ? place(ci, cj) : 0;
+        const uint32_t col = place(ci, cj);
         const int xlo = Geo::xface(ci, cj), xhi = Geo::xface(ci + 1, cj);
         const int ylo = Geo::yface(ci, cj), yhi = Geo::yface(ci, cj + 1);
         // planes k-1 and k+1 of the column (plane k is in LDS); zprev the upper
@@ -783,7 +788,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_step(
             Wm[q] = Wp[q] = zprev[q] = acc[q] = up1[q] = T(0);
             up2[q] = T(0);
         }
-        if (own) {
+        {
             T Ua[NV], Ub[NV], Uc[NV];
             load9(plane(z0 - 2), P.n, col, Ua);
             load9(plane(z0 - 1), P.n, col, Ub);
@@ -791,8 +796,10 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_step(
             to_prim<false>(P, Ua, Wm);
             to_prim<false>(P, Uc, Wp);
             to_prim<false>(P, Ub, Uc);
+            if (own) {
 #pragma unroll
-            for (int q = 0; q < NV; ++q) sm.w[q][ly][lx] = Uc[q];
+                for (int q = 0; q < NV; ++q) sm.w[q][ly][lx] = Uc[q];
+            }
         }
         __syncthreads();
         for (int k = z0 - 1;; ++k) {
@@ -811,7 +818,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_step(
                 }
             };
             // ---- the x-y flux divergence of plane k-1; the half step of plane k
-            if (own) {
+            if (live) {
                 if (k > z0) {
 #pragma unroll
                     for (int q = 0; q < NV; ++q)
@@ -836,7 +843,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_step(
                 }
             }
             __syncthreads();
-            if (own) {
+            if (live) {
                 T up[NV], dn[NV];
                 slopes(2);
                 face_values(P, W0, S, up, dn);
@@ -860,11 +867,15 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_step(
                         for (int q = 0; q < NV; ++q) {
                             U[q] = U[q] - P.c * (acc[q] + F[slot<2>(q)]);
                             if (q == 8) U[q] *= P.damp;
-                            __builtin_nontemporal_store(
-                                U[q], reinterpret_cast<T *>(
-                                          reinterpret_cast<char *>(o + (size_t)q * P.n) + col));
                         }
-                        if (speed_acc) {
+                        if (own) {
+#pragma unroll
+                            for (int q = 0; q < NV; ++q)
+                                __builtin_nontemporal_store(
+                                    U[q], reinterpret_cast<T *>(
+                                              reinterpret_cast<char *>(o + (size_t)q * P.n) + col));
+                        }
+                        if (speed_acc && own) {
                             T W[NV];
                             to_prim<true>(P, U, W);
                             double sum = 0.0;
@@ -887,15 +898,19 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_step(
                 slopes(0);
                 face_values(P, W0, S, up1, dn);
                 half_step(P, dn, dU, dn);
+                if (own) {
 #pragma unroll
-                for (int q = 0; q < NV; ++q) sm.f[q][xlo] = dn[q];
+                    for (int q = 0; q < NV; ++q) sm.f[q][xlo] = dn[q];
+                }
                 half_step(P, up1, dU, up1);
                 __builtin_amdgcn_sched_barrier(0);
                 slopes(1);
                 face_values(P, W0, S, up, dn);
                 half_step(P, dn, dU, dn);
+                if (own) {
 #pragma unroll
-                for (int q = 0; q < NV; ++q) sm.f[slot<1>(q)][ylo] = dn[q];
+                    for (int q = 0; q < NV; ++q) sm.f[slot<1>(q)][ylo] = dn[q];
+                }
                 half_step(P, up, dU, up);
 #pragma unroll
                 for (int q = 0; q < NV; ++q) up2[slot<1>(q)] = up[q];
@@ -906,30 +921,32 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_step(
             // ---- the load of plane k+2, in flight through the solves of the
             // cell's upper x and y faces; the column moves up
             T Un[NV], R[NV];
-            const bool more = own && k + 2 <= z1 + 1;
-            if (more) load9(plane(k + 2), P.n, col, Un);
-            if (own && !pre) {
+            load9(plane(k + 2), P.n, col, Un);
+            if (live && !pre) {
 #pragma unroll
                 for (int q = 0; q < NV; ++q) R[q] = sm.f[q][xhi];
                 glm_hlld(P, up1, R, up1);
+                if (own) {
 #pragma unroll
-                for (int q = 0; q < NV; ++q) sm.f[q][xhi] = up1[q];
+                    for (int q = 0; q < NV; ++q) sm.f[q][xhi] = up1[q];
+                }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int q = 0; q < NV; ++q) R[q] = sm.f[q][yhi];
                 glm_hlld(P, up2, R, up2);
+                if (own) {
 #pragma unroll
-                for (int q = 0; q < NV; ++q) sm.f[q][yhi] = up2[q];
+                    for (int q = 0; q < NV; ++q) sm.f[q][yhi] = up2[q];
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < NV; ++q) Wm[q] = sm.w[q][ly][lx];
             if (own) {
 #pragma unroll
-                for (int q = 0; q < NV; ++q) {
-                    Wm[q] = sm.w[q][ly][lx];
-                    sm.w[q][ly][lx] = Wp[q];
-                }
-                if (more) to_prim<false>(P, Un, Wp);
+                for (int q = 0; q < NV; ++q) sm.w[q][ly][lx] = Wp[q];
             }
+            to_prim<false>(P, Un, Wp);
             __syncthreads();
         }
     } else {
