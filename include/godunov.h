@@ -355,10 +355,11 @@ int godunov_step_batched_streamed(gd_ctx *ctx, const gd_opts *opts, int npatch,
  *
  * dt and ch come from the host values, or from device scalars when dt_dev /
  * ch_dev are not NULL (as written by cfl_dt_mhd). u_out must not overlap
- * u_in (GD_E_ARG). The library keeps a device scratch of 54 values per cell,
- * grown on first use (the growth synchronises the device; GD_E_NOMEM if it
- * fails). Boxes with 9 nx ny nz >= 2^31 return GD_E_UNSUPPORTED. Every
- * element of u_out is written once (deterministic). */
+ * u_in (GD_E_ARG). In single precision the library keeps a device scratch of 54
+ * values per cell, grown on first use (the growth synchronises the device;
+ * GD_E_NOMEM if it fails); double precision needs none. Boxes with
+ * 9 nx ny nz >= 2^31 return GD_E_UNSUPPORTED. Every element of u_out is written
+ * once (deterministic). */
 int godunov_step_mhd(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int nz, const void *u_in,
                      void *u_out, double gamma, double dx, double dt, const double *dt_dev,
                      double ch, const double *ch_dev, double alpha, void *hip_stream);

@@ -443,8 +443,11 @@ struct MarchSmem {
 // slopes is held across the z face: held, 72 registers spilled and the kernel
 // took 343 us on the 128^3 box, so 268. Before, one kernel wrote slopes and
 // predicted states (20 doubles a cell, 116 us) and another read them back (285
-// us): an adjoint step 0.56 -> 0.42 ms, a 112 x 84 x 60 ghosted patch with MC
-// limiter and flux adjoints 0.266 -> 0.168 ms.
+// us): an adjoint step 0.56 -> 0.42 ms. Tile waves run unmasked (masked lane by
+// lane, 26 registers of the minmod and 64 of the MC variant spilled, now 8 and
+// 35): a 112 x 84 x 60 ghosted patch with MC limiter and flux adjoints
+// 0.267 -> 0.174 -> 0.155 ms, ten steps of a 128^3 box and their adjoint
+// 7.74 -> 5.63 -> 5.35 ms.
 template <int LIM, int RS>
 __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_march(
     Geo g, const double *__restrict__ u, const double *__restrict__ lam_out,
@@ -477,8 +480,12 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
 
     if (__builtin_amdgcn_readfirstlane(tid >> 6) < Tile::NINT / 64) {
         // ---- the tile's columns
-        const int ci = tid % CTX, cj = tid / CTX;
-        const bool own = ci < ax && cj < ay;
+        // lanes outside a clipped tile compute on its first column, and do not
+        // write: what a masked branch may or may not set would keep its
+        // registers throughout the branch
+        const bool own = tid % CTX < ax && tid / CTX < ay;
+        const bool live = __builtin_amdgcn_readfirstlane(tid) / CTX < ay;
+        const int ci = own ? tid % CTX : 0, cj = own ? tid / CTX : 0;
         const int i = x0 + ci, j = y0 + cj, lx = ci + 2, ly = cj + 2;
         const Column c = make_column(g, i, j);
         const int xlo = Tile::xface(ci, cj), xhi = Tile::xface(ci + 1, cj);
@@ -486,9 +493,9 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
         // whether the column's upper x and y faces and its z faces exist (at
         // the planes, or below the planes, that do)
         const bool in_i = g.periodic || c.di == 0, in_j = g.periodic || c.dj == 0;
-        const bool has_x = own && in_j && i + 1 >= 0 && i + 1 <= g.nx;
-        const bool has_y = own && in_i && j + 1 >= 0 && j + 1 <= g.ny;
-        const bool has_z = own && in_i && in_j;
+        const bool has_x = in_j && i + 1 >= 0 && i + 1 <= g.nx;
+        const bool has_y = in_i && j + 1 >= 0 && j + 1 <= g.ny;
+        const bool has_z = in_i && in_j;
 
         // planes k-2 and k+1 of the column; the upper z state of plane k-1 and
         // the adjoint of its lower z face's right state; the upper x and y
@@ -496,7 +503,7 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
         double Wmm[5], Wp[5], zprev[5], zlo[5], up1[5], up2[5], lam0[5];
         for (int q = 0; q < 5; ++q) zprev[q] = zlo[q] = up1[q] = up2[q] = Wmm[q] = Wp[q] = lam0[q] = 0.0;
         double ir;
-        if (own) {
+        {
             double Ua[5], Ub[5], Uc[5];
             load_u(c, kb - 2, Ua);
             load_u(c, kb - 1, Ub);
@@ -505,9 +512,11 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
             to_prim(g, Uc, Wp, ir);
             to_prim(g, Ub, Uc, ir);
             to_prim(g, Ua, Ub, ir);
-            for (int q = 0; q < 5; ++q) {
-                sm.w[0][q][ly][lx] = Uc[q];
-                sm.w[1][q][ly][lx] = Ub[q];       // plane kb-2: the z slopes of kb-1
+            if (own) {
+                for (int q = 0; q < 5; ++q) {
+                    sm.w[0][q][ly][lx] = Uc[q];
+                    sm.w[1][q][ly][lx] = Ub[q];   // plane kb-2: the z slopes of kb-1
+                }
             }
         }
         __syncthreads();
@@ -519,13 +528,12 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
             // (still in LDS) and of plane k
             double Fz[5], nx1[5], nx2[5], zm[5], zp[5];
             for (int q = 0; q < 5; ++q) Fz[q] = zm[q] = zp[q] = nx1[q] = nx2[q] = 0.0;
+            for (int q = 0; q < 5; ++q)
+                Fz[rot<2>(q)] = g.c * lam0[q] - g.c * sm.lam[q][cj + 1][ci + 1];
             if (own) {
-                for (int q = 0; q < 5; ++q) {
-                    Fz[rot<2>(q)] = g.c * lam0[q] - g.c * sm.lam[q][cj + 1][ci + 1];
-                    sm.lam[q][cj + 1][ci + 1] = lam0[q];
-                }
+                for (int q = 0; q < 5; ++q) sm.lam[q][cj + 1][ci + 1] = lam0[q];
             }
-            if (own && (g.periodic || c.di + c.dj + depth(k) <= 1)) {
+            if (live && (g.periodic || c.di + c.dj + depth(k) <= 1)) {
                 double W[5], Sx[5], Sy[5], Sz[5], Ws[5];
                 for (int q = 0; q < 5; ++q) {
                     const double w = W[q] = sm.w[b][q][ly][lx];
@@ -540,7 +548,7 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
                     nx1[q] = Ws[q] + 0.5 * Sx[q];
                     nx2[yslot(q)] = Ws[q] + 0.5 * Sy[q];
                 }
-                if (inner) {
+                if (own && inner) {
                     for (int q = 0; q < 5; ++q) {
                         sm.f[b][q][xlo] = Ws[q] - 0.5 * Sx[q];
                         sm.f[b][yslot(q)][ylo] = Ws[q] - 0.5 * Sy[q];
@@ -551,7 +559,7 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
             double zl[5], zr[5];
             for (int q = 0; q < 5; ++q) zl[q] = zr[q] = 0.0;
             __builtin_amdgcn_sched_barrier(0);
-            if (has_z && k >= kb && (g.periodic || (k >= 0 && k <= g.nz))) {
+            if (live && has_z && k >= kb && (g.periodic || (k >= 0 && k <= g.nz))) {
                 double L[5], R[5], Lb[5], Rb[5];
                 for (int q = 0; q < 5; ++q) {
                     L[rot<2>(q)] = zprev[q];
@@ -565,7 +573,7 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (own && k > kb && (g.periodic || c.di + c.dj + depth(k - 1) <= 1)) {
+            if (live && k > kb && (g.periodic || c.di + c.dj + depth(k - 1) <= 1)) {
                 // the adjoints of plane k-1's face states: the left state of an
                 // upper face is W* + S/2, the right state of a lower one W* - S/2
                 const int e = ext(g, i, j, k - 1);
@@ -605,13 +613,18 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
                     Sb[1 + d] += divub;
                     Wb0 += lam * (Wsb[1 + d] * S[4] * inv_rho * inv_rho - Wsb[0] * S[1 + d]);
                     Wb4 -= lam * g.gamma * Wsb[4] * S[1 + d];
-                    for (int q = 0; q < 5; ++q)
-                        __builtin_nontemporal_store(Sb[q], &s.ad[rec(e, F_SB + d * 5 + q)]);
-                    __builtin_nontemporal_store(Wsb[1 + d] - lam * dot, &s.ad[rec(e, F_WD + 1 + d)]);
+                    const double wd = Wsb[1 + d] - lam * dot;
+                    if (own) {
+                        for (int q = 0; q < 5; ++q)
+                            __builtin_nontemporal_store(Sb[q], &s.ad[rec(e, F_SB + d * 5 + q)]);
+                        __builtin_nontemporal_store(wd, &s.ad[rec(e, F_WD + 1 + d)]);
+                    }
                 }
-                __builtin_nontemporal_store(Wb0, &s.ad[rec(e, F_WD)]);
-                __builtin_nontemporal_store(Wb4, &s.ad[rec(e, F_WD + 4)]);
-                s.code[e] = code;
+                if (own) {
+                    __builtin_nontemporal_store(Wb0, &s.ad[rec(e, F_WD)]);
+                    __builtin_nontemporal_store(Wb4, &s.ad[rec(e, F_WD + 4)]);
+                    s.code[e] = code;
+                }
             }
             for (int q = 0; q < 5; ++q) {
                 up1[q] = nx1[q];
@@ -626,11 +639,9 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
 
             // ---- II
             double Un[5], lamn[5];
-            if (own) {
-                load_u(c, k + 2, Un);
-                load_lam(c, k + 1, lamn);
-            }
-            if (own && inner) {
+            load_u(c, k + 2, Un);
+            load_lam(c, k + 1, lamn);
+            if (live && inner) {
                 // a face between cells that are not both there has no adjoint
                 const bool at_k = g.periodic || (k >= 0 && k < g.nz);
                 double R[5], Fb[5], Lb[5], Rb[5];
@@ -643,9 +654,9 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
                     add_bflux<0>(g, lam_bflux, i + 1, k * g.ny + j, Fb);
                     face_reverse<RS>(g, up1, R, Fb, Lb, Rb);
                 }
-                for (int q = 0; q < 5; ++q) {
-                    up1[q] = Lb[q];
-                    sm.f[b][q][xhi] = Rb[q];
+                for (int q = 0; q < 5; ++q) up1[q] = Lb[q];
+                if (own) {
+                    for (int q = 0; q < 5; ++q) sm.f[b][q][xhi] = Rb[q];
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 for (int q = 0; q < 5; ++q) Lb[q] = Rb[q] = 0.0;
@@ -657,21 +668,21 @@ __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) v
                     add_bflux<1>(g, lam_bflux, j + 1, k * g.nx + i, Fb);
                     face_reverse<RS>(g, up2, R, Fb, Lb, Rb);
                 }
-                for (int q = 0; q < 5; ++q) {
-                    up2[q] = Lb[q];
-                    sm.f[b][q][yhi] = Rb[q];
+                for (int q = 0; q < 5; ++q) up2[q] = Lb[q];
+                if (own) {
+                    for (int q = 0; q < 5; ++q) sm.f[b][q][yhi] = Rb[q];
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (own) {
-                // the column moves up
-                for (int q = 0; q < 5; ++q) {
-                    Wmm[q] = sm.w[b ^ 1][q][ly][lx];
-                    sm.w[b ^ 1][q][ly][lx] = Wp[q];
-                    lam0[q] = lamn[q];
-                }
-                to_prim(g, Un, Wp, ir);
+            // the column moves up
+            for (int q = 0; q < 5; ++q) {
+                Wmm[q] = sm.w[b ^ 1][q][ly][lx];
+                lam0[q] = lamn[q];
             }
+            if (own) {
+                for (int q = 0; q < 5; ++q) sm.w[b ^ 1][q][ly][lx] = Wp[q];
+            }
+            to_prim(g, Un, Wp, ir);
             __syncthreads();
         }
     } else {
