@@ -342,10 +342,10 @@ int resident_blocks(gd_ctx *ctx, int dtype, int limiter, int riemann, int shape)
 // 0.7 of a full one's time and all of it, and long ranges lose about 1% per 1.5
 // planes because neighbouring tiles drift apart and re-read their halos. The
 // cost formed from these picks, among 16x8 and 24x8 tiles and every z-range up
-// to 64 planes, a configuration within 6% of the best of twenty measured ones
-// on each of twenty-two boxes of 64^3 to 256^3 in both precisions, in the mean
-// no slower than it (256^3 FP64: 0.64 ms, where 16x16 tiles with ranges of 32
-// take 0.88; 250 x 190 x 141 FP32 0.14 against 0.29; 128^3 FP64 0.079 against
+// to 64 planes, a configuration within 4% of the best of twenty measured ones
+// on each of twenty-two boxes of 64^3 to 256^3 in both precisions but one (8%),
+// in the mean no slower than it (256^3 FP64: 0.64 ms, where 16x16 tiles with ranges of 32
+// take 0.88; 250 x 190 x 141 FP32 0.13 against 0.29; 128^3 FP64 0.077 against
 // 0.11). 8x8, 32x8 and 16x16 tiles were the best on none: their rings or their
 // LDS leave fewer columns on a CU.
 void choose_single(gd_ctx *ctx, int dtype, int limiter, int riemann, int nx, int ny, int nz,
@@ -391,10 +391,11 @@ void choose_single(gd_ctx *ctx, int dtype, int limiter, int riemann, int nx, int
 // 1.06, over the workgroups the chip holds at once, and a twentieth of the
 // longest item for the tail. Over thirteen batches in both precisions (64 to
 // 4096 patches of 4 to 40 cells, cubic and not) the choice is 2% from the best
-// of all shapes and policies in the mean, 7% at most; one fixed choice is up to
-// 40% off (4096 cubic patches of 8 to 32 cells, FP64: 1.11 ms in the pair with
-// whole patches, 1.23 with ranges of 8; 500 uneven patches of 6 to 40: 0.224 ms
-// in 24x8 tiles with ranges of 8, 0.273 with whole patches).
+// of all shapes and policies in the mean, 8% at most; one fixed choice is up to
+// 40% off (when the weights were fitted, 4096 cubic patches of 8 to 32 cells,
+// FP64: 1.11 ms in the pair with whole patches, 1.23 with ranges of 8; 500 uneven
+// patches of 6 to 40: 0.224 ms in 24x8 tiles with ranges of 8, 0.273 with whole
+// patches; with the march as it is now the chosen ones take 0.98 and 0.208).
 void choose_batched(gd_ctx *ctx, int dtype, int npatch, const gd_patch *patches, int *shape,
                     int *zpolicy)
 {
