@@ -150,3 +150,42 @@ def test_amr_seams_off_the_pair_grid(gd, dtype, shift, skip):
 
     for got, want in zip(run(shift, skip), run(0, 0)):
         assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+@pytest.mark.parametrize("lim,rs", [("minmod", "hll"), ("mc", "hllc"), ("none", "hll")])
+def test_the_librarys_own_tiles_give_the_bits_of_any(gd, dtype, lim, rs):
+    """Tiles and z-ranges chosen by size against fixed ones: patches and boxes
+    of odd sizes and of one cell, and a batch of them."""
+    import torch
+    dt_ = getattr(torch, dtype)
+    sizes = [(1, 1, 1), (7, 3, 61), (23, 40, 2), (65, 9, 17), (50, 51, 52)]
+    states = [inputs.random_patch(*s, seed=300 + p, generic=True) for p, s in enumerate(sizes)]
+    batch = inputs.pack_batch(states, 2, 1 / 64, order_seed=6)
+    table = gd.patch_table(batch.dims, 2, batch.u_in_off, batch.u_out_off, batch.flux_off,
+                           batch.dx, 1e-3)
+    say("own tiles", dtype, lim, rs)
+
+    def run():
+        got = []
+        for u in states:
+            d = dev(u).to(dt_)
+            got += [host(t) for t in gd.step(d, G, 1 / 64, 1e-3, limiter=lim, riemann=rs)]
+            box = d[:, 2:-2, 2:-2, 2:-2].contiguous()
+            got += [host(t) for t in gd.step(box, G, 1 / 64, 1e-3, periodic=True, limiter=lim,
+                                             riemann=rs)]
+        out = torch.zeros(batch.u_out_size, dtype=dt_, device="cuda")
+        flux = torch.zeros(batch.flux_size, dtype=dt_, device="cuda")
+        gd.step_batched(dev(batch.u_in).to(dt_), table, G, out=out, bflux=flux, limiter=lim,
+                        riemann=rs)
+        return got + [host(out), host(flux)]
+
+    own = run()
+    try:
+        gd.set_config(dt_, shape_single="8x8", zlen_single=5, shape_batched="16x8",
+                      zpolicy_batched=0)
+        fixed = run()
+    finally:
+        gd.set_config(dt_)
+    for a, b in zip(own, fixed):
+        assert np.array_equal(a, b)
