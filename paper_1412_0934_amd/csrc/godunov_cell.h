@@ -161,9 +161,12 @@ __device__ __forceinline__ void face_state(const T Ws[5], const T S[5], T half_s
 // a, normal velocity S*, pressure p* = p_K + m_K (S* - u_K) and energy
 // E* = ((S_K - u_K) E_K - p_K u_K + p* S*) / (S_K - S*), and the flux is the
 // physical flux of that state: (a S*, a S*^2 + p*, a S* v_K, a S* w_K,
-// S* (E* + p*)). In the upwind regions S* is replaced by u_K, which turns the
-// star state into K itself: one select, and 16 fewer FP64 operations per face
-// than F_K + S_K (U*_K - U_K).
+// S* (E* + p*)), 14 fewer FP64 operations per face than F_K + S_K (U*_K - U_K).
+// In the upwind regions S*, a and E* are replaced by u_K, rho_K and E_K, which
+// turns the star state into K itself. The replacement of S* alone would do so in
+// exact arithmetic, but the quotients by S_K - u_K carry the error of the
+// reciprocal (4e-15 against one rounding), and where the sound speed is lost in
+// u_K (Mach numbers of 1e16: a gas at its pressure floor) they are 0/0.
 // Regions, in order: S_L >= 0 -> F(L); S* >= 0 -> L star; S_R > 0 -> R star;
 // else F(R).
 template <typename T>
@@ -198,8 +201,8 @@ __device__ __forceinline__ void hllc_rotated(const T L[5], const T R[5], const P
         const T inv_d = fast_rcp(SK - S);
         const T ps = fma(mK, S - uK, pK);
         const T EK = fma(T(0.5) * rK, fma(wK, wK, fma(vK, vK, uK * uK)), pK * ph.inv_gm1);
-        const T Es = inv_d * fma(ps, S, fma(dK, EK, -(pK * uK)));
-        const T mass = mK * inv_d * S;
+        const T Es = star ? inv_d * fma(ps, S, fma(dK, EK, -(pK * uK))) : EK;
+        const T mass = (star ? mK * inv_d : rK) * S;
         F[0] = mass;
         F[1] = fma(mass, S, ps);
         F[2] = mass * vK;
