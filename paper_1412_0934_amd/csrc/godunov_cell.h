@@ -253,10 +253,12 @@ __device__ __forceinline__ void hllc_rotated(const T L[5], const T R[5], const P
     }
 }
 
-// Order of the sum of squares of a single-precision HLL flux: the compiler's,
-// or one of the two fused orders of the tile marches (their x and y faces, their
-// z faces), which a march names to keep its bits; the PPM march also names the
-// product that its energy fuses.
+// Order of the sum of squares of an HLL flux: the natural one, or one of the two
+// fused orders of the tile marches (their x and y faces, their z faces), which a
+// march names to keep its bits; the PPM march also names the product that its
+// energy fuses in single precision. Two tiles solve the face between them in code
+// of their own (the tile's columns, the ring's), so what the fluxes fuse must not
+// be the compiler's choice in each place: in double precision it is written out.
 enum { SQ_ANY = 0, SQ_XY = 1, SQ_Z = 2, SQ_PPM = 4 };
 
 template <int SQ, typename T>
@@ -265,33 +267,57 @@ __device__ __forceinline__ void euler_flux_rotated(const T W[5], const Phys<T> &
     T q2;
     if constexpr ((SQ & 3) == SQ_XY) q2 = fma(W[3], W[3], fma(W[1], W[1], W[2] * W[2]));
     else if constexpr ((SQ & 3) == SQ_Z) q2 = fma(W[3], W[3], fma(W[2], W[2], W[1] * W[1]));
+    else if constexpr (sizeof(T) == 8) q2 = fma(W[3], W[3], fma(W[2], W[2], W[1] * W[1]));
     else q2 = W[1] * W[1] + W[2] * W[2] + W[3] * W[3];
     T E;
-    if constexpr (SQ & SQ_PPM) E = fma(W[4], ph.inv_gm1, T(0.5) * W[0] * q2);
+    if constexpr (sizeof(T) == 8) E = fma(T(0.5) * W[0], q2, W[4] * ph.inv_gm1);
+    else if constexpr (SQ & SQ_PPM) E = fma(W[4], ph.inv_gm1, T(0.5) * W[0] * q2);
     else E = W[4] * ph.inv_gm1 + T(0.5) * W[0] * q2;
     T mass = W[0] * W[1];
-    F[0] = mass; F[1] = mass * W[1] + W[4]; F[2] = mass * W[2]; F[3] = mass * W[3];
-    F[4] = W[1] * (E + W[4]);
+    F[0] = mass; F[2] = mass * W[2]; F[3] = mass * W[3];
+    if constexpr (sizeof(T) == 8) {
+#pragma clang fp contract(off)
+        F[1] = fma(mass, W[1], W[4]);
+        F[4] = W[1] * (E + W[4]);
+    } else {
+        F[1] = mass * W[1] + W[4];
+        F[4] = W[1] * (E + W[4]);
+    }
     U[0] = W[0]; U[1] = mass; U[2] = W[0] * W[2]; U[3] = W[0] * W[3]; U[4] = E;
 }
 
 template <int SQ, typename T>
 __device__ __forceinline__ void hll_rotated(const T L[5], const T R[5], const Phys<T> &ph, T F[5])
 {
-    const T g = ph.gamma;
-    T gpL = g * L[4], gpR = g * R[4];
-    T cL = gpL * fast_rsqrt(gpL * L[0]);
-    T cR = gpR * fast_rsqrt(gpR * R[0]);
-    T SL = fmin(L[1] - cL, R[1] - cR);
-    T SR = fmax(L[1] + cL, R[1] + cR);
     T FL[5], FR[5], UL[5], UR[5];
     euler_flux_rotated<SQ>(L, ph, FL, UL);
     euler_flux_rotated<SQ>(R, ph, FR, UR);
-    T inv = fast_rcp(SR - SL);
+    if constexpr (sizeof(T) == 8) {
+#pragma clang fp contract(off)
+        const T gpL = ph.gamma * L[4], gpR = ph.gamma * R[4];
+        const T cL = gpL * fast_rsqrt(gpL * L[0]);
+        const T cR = gpR * fast_rsqrt(gpR * R[0]);
+        const T SL = fmin(L[1] - cL, R[1] - cR);
+        const T SR = fmax(L[1] + cL, R[1] + cR);
+        const T inv = fast_rcp(SR - SL);
 #pragma unroll
-    for (int q = 0; q < 5; ++q) {
-        T Fm = (SR * FL[q] - SL * FR[q] + SL * SR * (UR[q] - UL[q])) * inv;
-        F[q] = SL >= T(0) ? FL[q] : (SR <= T(0) ? FR[q] : Fm);
+        for (int q = 0; q < 5; ++q) {
+            const T Fm = fma(SL * SR, UR[q] - UL[q], fma(SR, FL[q], -(SL * FR[q]))) * inv;
+            F[q] = SL >= T(0) ? FL[q] : (SR <= T(0) ? FR[q] : Fm);
+        }
+    } else {
+        const T g = ph.gamma;
+        T gpL = g * L[4], gpR = g * R[4];
+        T cL = gpL * fast_rsqrt(gpL * L[0]);
+        T cR = gpR * fast_rsqrt(gpR * R[0]);
+        T SL = fmin(L[1] - cL, R[1] - cR);
+        T SR = fmax(L[1] + cL, R[1] + cR);
+        T inv = fast_rcp(SR - SL);
+#pragma unroll
+        for (int q = 0; q < 5; ++q) {
+            T Fm = (SR * FL[q] - SL * FR[q] + SL * SR * (UR[q] - UL[q])) * inv;
+            F[q] = SL >= T(0) ? FL[q] : (SR <= T(0) ? FR[q] : Fm);
+        }
     }
 }
 
