@@ -625,14 +625,16 @@ __device__ __forceinline__ void glm_hlld(const Par<T> &P, const T L[NV], const T
     const T yO = left ? R[6] : L[6], zO = left ? R[7] : L[7];
     const T SO = left ? SR : SL, dO = left ? dR : dL;
 
-    // single-star states of both sides; outside the fan K* is K
+    // single-star states of both sides; outside the fan K* is K, selected value by
+    // value: the quotients by S_K - u_K give it in exact arithmetic only, and are
+    // 0/0 where the fast speed is lost in u_K
     const T SMK = sup ? uK : SM;
     pS = sup ? pTK : pS;
     const T isd = fast_rcp(SK - SMK);
-    const T rs = dK * isd;
+    const T rs = sup ? rK : dK * isd;
     const T ddK = dK * (SK - uK);
     const T denK = fma(dK, SK - SMK, -Bn2);
-    const bool badK = fabs(denK) <= T(1e-12) * (ddK + Bn2);
+    const bool badK = sup || fabs(denK) <= T(1e-12) * (ddK + Bn2);
     const T idK = fast_rcp(denK);
     const T tK = badK ? T(0) : Bn * (SMK - uK) * idK;
     const T fK = badK ? T(1) : (ddK - Bn2) * idK;
@@ -650,7 +652,7 @@ __device__ __forceinline__ void glm_hlld(const Par<T> &P, const T L[NV], const T
     const T EK = fma(half, fma(rK, fma(wK, wK, fma(vK, vK, uK * uK)), B2K), pK * P.inv_gm1);
     const T uB = fma(wK, zK, fma(vK, yK, uK * Bn));
     const T uBs = fma(ws, zs, fma(vs, ys, SMK * Bn));
-    T E = isd * fma(Bn, uB - uBs, fma(pS, SMK, fma(SK - uK, EK, -(pTK * uK))));
+    T E = sup ? EK : isd * fma(Bn, uB - uBs, fma(pS, SMK, fma(SK - uK, EK, -(pTK * uK))));
 
     // between the Alfven waves: the double-star state
     const T iq = fast_rsqrt(rs), sqK = rs * iq, sqO = hw_sqrt(rO);

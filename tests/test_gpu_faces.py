@@ -67,3 +67,76 @@ def test_supersonic_face_has_the_upwind_flux(gd, lim, axis, cold):
         for side in (0, 1):
             got = sheet(host(b), axis, side, n)
             assert (np.abs(got - F[:, None]) <= 2 * np.spacing(np.abs(F))[:, None]).all(), (U, got, F)
+
+
+def rotate(v, axis, fields=((1, 2, 3),)):
+    """Variables of data along x turned to an axis (cyclically)."""
+    v = np.array(v)
+    for f in fields:
+        v[[f[(c + axis) % 3] for c in range(3)]] = v[list(f)]
+    return v
+
+
+def along(profile, axis, shape=(4, 4)):
+    """A profile [var][i] as a box [var][z][y][x] that varies along one axis only."""
+    nvar, n = profile.shape
+    dims = [shape[1], shape[0]]
+    dims.insert(2 - axis, n)                    # z, y, x
+    one = [1, 1, 1]
+    one[2 - axis] = n
+    return np.ascontiguousarray(np.broadcast_to(profile.reshape([nvar] + one), [nvar] + dims))
+
+
+def mhd_blocks(sign, cold, seed, n=32):
+    """n MHD states in blocks of two cells, the flow faster than any wave along the
+    axis and the field along it uniform: (U, F), [9][2n] each. Cold: a weak field
+    too, so that the fast speed lies below the last place of the velocity."""
+    rng = np.random.default_rng(seed)
+    rho = 2.0 ** rng.integers(-2, 3, n)
+    u = sign * rng.integers(256, 512, n) / 8.0
+    v, w = np.zeros(n), np.zeros(n)
+    p = np.zeros(n) if cold else rho * rng.integers(16, 64, n) / 4.0
+    weak = 2.0 ** -60 if cold else 1.0
+    Bx = np.full(n, weak)
+    By, Bz = (weak * rng.integers(-16, 16, n) / 8.0 for _ in range(2))
+    psi = np.zeros(n)
+    B2 = Bx * Bx + By * By + Bz * Bz
+    E = 2.0 * p + 0.5 * rho * u * u + 0.5 * B2
+    pT = p + 0.5 * B2
+    U = np.stack([rho, rho * u, rho * v, rho * w, E, Bx, By, Bz, psi])
+    F = np.stack([rho * u, rho * u * u + pT - Bx * Bx, -Bx * By, -Bx * Bz,
+                  (E + pT) * u - Bx * (u * Bx), 0.0 * u, u * By, u * Bz, CH * CH * Bx])
+    return np.repeat(U, 2, axis=1), np.repeat(F, 2, axis=1)
+
+
+CH = 64.0
+
+
+@pytest.mark.parametrize("lim", ["minmod", "mc"])
+@pytest.mark.parametrize("axis,sign", [(0, 1), (1, -1), (2, 1), (2, -1)])
+@pytest.mark.parametrize("cold", [False, True])
+def test_mhd_super_fast_face_has_the_upwind_flux(gd, lim, axis, sign, cold):
+    """U' = U - c (F_i - F_{i-1}) with c large, so that the fluxes show. Each flux may
+    take two roundings; a cell's sum passes through the transverse flux T that
+    stands on both of its sides, which rounds |F_i - F_{i-1}| + |T| twice, and U'
+    once; twice that is allowed."""
+    U, F = mhd_blocks(sign, cold, seed=23 + axis)
+    c, dx = 64.0, 1 / 16
+    dF = F - np.roll(F, 1, axis=1) if sign > 0 else np.roll(F, -1, axis=1) - F
+    fields = ((1, 2, 3), (5, 6, 7))
+    want = U - c * dF
+    rho, u, (Bx, By, Bz) = U[0], U[1] / U[0], U[5:8]
+    B2, big = Bx * Bx + By * By + Bz * Bz, np.maximum(np.abs(By), np.abs(Bz))
+    pT = 0.5 * (U[4] - 0.5 * rho * u * u - 0.5 * B2) + 0.5 * B2
+    T = np.stack([0 * u, big * np.abs(Bx), pT + B2, pT + B2, big * np.abs(u * Bx), np.abs(u) * big,
+                  0 * u, 0 * u, CH * CH * big])
+    off = np.spacing(np.abs(F))
+    off += np.roll(off, sign, axis=1)
+    tol = 2 * (c * (off + np.spacing(np.abs(dF) + T)) + np.spacing(np.abs(want)))
+    say("super-fast faces", lim, axis, sign, "cold" if cold else "warm")
+    out = gd.step_mhd(dev(along(rotate(U, axis, fields), axis)), G, dx, c * dx, CH, alpha=0.0,
+                      limiter=lim, rho_floor=P_FLOOR, p_floor=P_FLOOR)
+    err = np.abs(host(out) - along(rotate(want, axis, fields), axis))
+    tol = along(rotate(tol, axis, fields), axis)
+    say("worst error in tolerances", float((err / tol).max()))
+    assert (err <= tol).all()
