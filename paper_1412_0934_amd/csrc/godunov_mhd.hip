@@ -80,25 +80,61 @@ __device__ __forceinline__ T hw_sqrt(T x)
     return x > T(0) ? x * fast_rsqrt(x) : T(0);
 }
 
+// The helpers below are inlined in several places whose results have to agree:
+// the tile's columns and the ring's predict the same cells, the step and
+// cfl_dt_mhd reduce the same speeds. In double precision their products and sums
+// are therefore fused as written, by fma() and not by the compiler's choice,
+// which shared a product among six face states in one loop and fused it into each
+// in the other. In single precision, whose step has one copy of each, the
+// expressions are left to the compiler.
+
+// sum of three products
+__device__ __forceinline__ double dot3(const double *x, const double *y)
+{
+#pragma clang fp contract(off)
+    return fma(x[2], y[2], fma(x[1], y[1], x[0] * y[0]));
+}
+
 // Divisions and square roots: EXACT = IEEE-rounded (the signal speeds behind
 // dt and ch), else the refined hardware estimates (the step's arithmetic).
 template <bool EXACT, typename T>
 __device__ __forceinline__ void to_prim(const Par<T> &P, const T U[NV], T W[NV])
 {
-    T rho = U[0] < P.rho_floor ? P.rho_floor : U[0];
-    T u, v, w;
-    if constexpr (EXACT) {
-        u = U[1] / rho; v = U[2] / rho; w = U[3] / rho;
+    if constexpr (sizeof(T) == 8) {
+#pragma clang fp contract(off)
+        const T rho = U[0] < P.rho_floor ? P.rho_floor : U[0];
+        if constexpr (EXACT) {
+            W[1] = U[1] / rho; W[2] = U[2] / rho; W[3] = U[3] / rho;
+        } else {
+            const T ir = fast_rcp(rho);
+            W[1] = U[1] * ir; W[2] = U[2] * ir; W[3] = U[3] * ir;
+        }
+        const T p = P.gm1 * fma(T(-0.5), dot3(U + 5, U + 5), fma(T(-0.5), dot3(U + 1, W + 1), U[4]));
+        W[0] = rho;
+        W[4] = p < P.p_floor ? P.p_floor : p;
     } else {
-        const T ir = fast_rcp(rho);
-        u = U[1] * ir; v = U[2] * ir; w = U[3] * ir;
+        T rho = U[0] < P.rho_floor ? P.rho_floor : U[0];
+        T u, v, w;
+        if constexpr (EXACT) {
+            u = U[1] / rho; v = U[2] / rho; w = U[3] / rho;
+        } else {
+            const T ir = fast_rcp(rho);
+            u = U[1] * ir; v = U[2] * ir; w = U[3] * ir;
+        }
+        T kin = T(0.5) * (U[1] * u + U[2] * v + U[3] * w);
+        T mag = T(0.5) * (U[5] * U[5] + U[6] * U[6] + U[7] * U[7]);
+        T p = P.gm1 * (U[4] - kin - mag);
+        if (p < P.p_floor) p = P.p_floor;
+        W[0] = rho; W[1] = u; W[2] = v; W[3] = w; W[4] = p;
     }
-    T kin = T(0.5) * (U[1] * u + U[2] * v + U[3] * w);
-    T mag = T(0.5) * (U[5] * U[5] + U[6] * U[6] + U[7] * U[7]);
-    T p = P.gm1 * (U[4] - kin - mag);
-    if (p < P.p_floor) p = P.p_floor;
-    W[0] = rho; W[1] = u; W[2] = v; W[3] = w; W[4] = p;
     W[5] = U[5]; W[6] = U[6]; W[7] = U[7]; W[8] = U[8];
+}
+
+// total energy of a primitive state in double precision
+__device__ __forceinline__ double energy(const Par<double> &P, const double W[NV])
+{
+#pragma clang fp contract(off)
+    return fma(0.5, dot3(W + 5, W + 5), fma(0.5 * W[0], dot3(W + 1, W + 1), W[4] * P.inv_gm1));
 }
 
 template <typename T>
@@ -106,9 +142,15 @@ __device__ __forceinline__ void to_cons(const Par<T> &P, const T W[NV], T U[NV])
 {
     const T rho = W[0];
     U[0] = rho;
-    U[1] = rho * W[1]; U[2] = rho * W[2]; U[3] = rho * W[3];
-    U[4] = W[4] * P.inv_gm1 + T(0.5) * rho * (W[1] * W[1] + W[2] * W[2] + W[3] * W[3]) +
-           T(0.5) * (W[5] * W[5] + W[6] * W[6] + W[7] * W[7]);
+    if constexpr (sizeof(T) == 8) {
+#pragma clang fp contract(off)
+        U[1] = rho * W[1]; U[2] = rho * W[2]; U[3] = rho * W[3];
+        U[4] = energy(P, W);
+    } else {
+        U[1] = rho * W[1]; U[2] = rho * W[2]; U[3] = rho * W[3];
+        U[4] = W[4] * P.inv_gm1 + T(0.5) * rho * (W[1] * W[1] + W[2] * W[2] + W[3] * W[3]) +
+               T(0.5) * (W[5] * W[5] + W[6] * W[6] + W[7] * W[7]);
+    }
     U[5] = W[5]; U[6] = W[6]; U[7] = W[7]; U[8] = W[8];
 }
 
@@ -118,6 +160,15 @@ template <bool EXACT, typename T>
 __device__ __forceinline__ T fast_speed(const Par<T> &P, const T W[NV], T bn)
 {
     const T ir = EXACT ? T(1) / W[0] : fast_rcp(W[0]);
+    if constexpr (sizeof(T) == 8) {
+#pragma clang fp contract(off)
+        const T a2 = P.gamma * W[4] * ir;
+        const T s = fma(dot3(W + 5, W + 5), ir, a2);
+        const T disc = fma(s, s, T(-4) * a2 * (bn * bn * ir));
+        const T r = disc < T(0) ? T(0) : disc;
+        if constexpr (EXACT) return sqrt(T(0.5) * (s + sqrt(r)));
+        else return hw_sqrt(T(0.5) * (s + hw_sqrt(r)));
+    }
     const T a2 = P.gamma * W[4] * ir;
     const T b2 = (W[5] * W[5] + W[6] * W[6] + W[7] * W[7]) * ir;
     const T s = a2 + b2;
@@ -133,6 +184,19 @@ __device__ __forceinline__ void phys_flux(const Par<T> &P, const T W[NV], T F[NV
 {
     const T rho = W[0], p = W[4];
     const T un = W[1 + D], Bn = W[5 + D];
+    if constexpr (sizeof(T) == 8) {
+#pragma clang fp contract(off)
+        const T pT = fma(T(0.5), dot3(W + 5, W + 5), p), m = rho * un;
+        F[0] = m;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            F[1 + k] = fma(m, W[1 + k], k == D ? fma(-Bn, Bn, pT) : -(Bn * W[5 + k]));
+            F[5 + k] = k == D ? W[8] : fma(un, W[5 + k], -(W[1 + k] * Bn));
+        }
+        F[4] = fma(energy(P, W) + pT, un, -(Bn * dot3(W + 1, W + 5)));
+        F[8] = P.ch2 * Bn;
+        return;
+    }
     const T B2 = W[5] * W[5] + W[6] * W[6] + W[7] * W[7];
     const T pT = p + T(0.5) * B2;
     const T uB = W[1] * W[5] + W[2] * W[6] + W[3] * W[7];
@@ -698,7 +762,7 @@ __device__ __forceinline__ void half_step(const Par<T> &P, const T W[NV], const 
     T U[NV], V[NV];
     to_cons(P, W, U);
 #pragma unroll
-    for (int q = 0; q < NV; ++q) U[q] += P.h * dU[q];
+    for (int q = 0; q < NV; ++q) U[q] = fma(P.h, dU[q], U[q]);
     to_prim<false>(P, U, V);
 #pragma unroll
     for (int q = 0; q < NV; ++q) Wn[q] = V[q];
@@ -734,7 +798,7 @@ __device__ __forceinline__ void load9(const T *__restrict__ p, int n, uint32_t a
 // to the face states, 70 registers spilled, the prefetched plane among them
 // (its whole latency then stood between two barriers), and a step took
 // 0.635 ms; with the interior lanes masked one by one, 16 spilled and 0.332 ms.
-// 128^3 box, dt and ch on the device: 0.304 ms a step against 0.591 ms for the
+// 128^3 box, dt and ch on the device: 0.305 ms a step against 0.591 ms for the
 // two launches over 54 staged values per cell.
 template <typename T, int LIM, int TX, int TY>
 __global__ __launch_bounds__(tile_threads(TX, TY))
@@ -867,7 +931,7 @@ __attribute__((amdgpu_waves_per_eu(2))) void k_step(
                         T *o = out + (size_t)(k - 1) * (P.nx * P.ny);
 #pragma unroll
                         for (int q = 0; q < NV; ++q) {
-                            U[q] = U[q] - P.c * (acc[q] + F[slot<2>(q)]);
+                            U[q] = fma(-P.c, acc[q] + F[slot<2>(q)], U[q]);
                             if (q == 8) U[q] *= P.damp;
                         }
                         if (own) {

@@ -53,3 +53,14 @@ def test_step(gd, axis, rs, dtype):
         say("transverse-uniform", axis, rs, dtype, lim)
         out, _ = gd.step(u, G, 1 / 64, 1e-3, periodic=True, limiter=lim, riemann=rs)
         assert_uniform(out, axis)
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("lim", ["minmod", "mc", "none"])
+@pytest.mark.parametrize("dtype", ["float64", "float32"])
+def test_mhd_step(gd, axis, lim, dtype):
+    import torch
+    line = inputs.mhd_random_box(N[axis], 1, 1, seed=40 + axis)[:, 0, 0, :]
+    u = along(line, axis, ((1, 2, 3), (5, 6, 7))).to(getattr(torch, dtype))
+    say("mhd transverse-uniform", axis, lim, dtype)
+    assert_uniform(gd.step_mhd(u, G, 1 / 64, 1e-3, 3.0, alpha=0.1, limiter=lim), axis)
