@@ -238,9 +238,12 @@ __device__ __forceinline__ void phys_flux(double inv_gm1, const double W[5], dou
 // of the star state of the side K the face lies on, (a S, a S^2 + p*, a S v_K,
 // a S w_K, S (E* + p*)) with m = rho_K (S_K - u_K), a = m / (S_K - S), p* =
 // p_K + m (S - u_K), E* = ((S_K - u_K) E_K - p_K u_K + p* S) / (S_K - S); S is
-// S* in the star regions and u_K in the upwind ones, where the flux no longer
-// depends on the wave speeds. One path for all regions, a third fewer
-// operations than through F_K + S_K (U*_K - U_K), and 4 of 7 reciprocals gone.
+// S* in the star regions and u_K in the upwind ones, where the flux is that of K
+// and no longer depends on the wave speeds: a is rho_K there, E* is E_K, and 1 /
+// (S_K - S) and m stand for nothing and are zero (the quotients would give the
+// same in exact arithmetic only, and 0/0 where the sound speed is lost in u_K).
+// One path for all regions, a third fewer operations than through
+// F_K + S_K (U*_K - U_K), and 4 of 7 reciprocals gone.
 __device__ __forceinline__ void hllc_adjoint(double g, double inv_gm1, const double L[5],
                                              const double R[5], const double Fb[5], double Lb[5],
                                              double Rb[5])
@@ -256,15 +259,15 @@ __device__ __forceinline__ void hllc_adjoint(double g, double inv_gm1, const dou
     const bool star = !supL && (left || f.SR > 0.0);
     const double r = left ? L[0] : R[0], u = left ? L[1] : R[1], v = left ? L[2] : R[2];
     const double w = left ? L[3] : R[3], p = left ? L[4] : R[4];
-    const double SK = left ? f.SL : f.SR, m = left ? mL : mR;
+    const double SK = left ? f.SL : f.SR, m = star ? (left ? mL : mR) : 0.0;
     const double S = star ? Sst : u;
     const double dK = SK - u, t = S - u;
-    const double id = fast_rcp(SK - S);
+    const double id = star ? fast_rcp(SK - S) : 0.0;
     const double q2 = u * u + v * v + w * w;
     const double EK = p * inv_gm1 + 0.5 * r * q2;
     const double ps = p + m * t;
-    const double Es = id * (dK * EK - p * u + ps * S);
-    const double a = m * id, mass = a * S;
+    const double Es = star ? id * (dK * EK - p * u + ps * S) : EK;
+    const double a = star ? m * id : r, mass = a * S;
 
     // the flux: mass, mass S + p*, mass v, mass w, S (E* + p*)
     const double eb = Fb[4] * S;
@@ -275,7 +278,7 @@ __device__ __forceinline__ void hllc_adjoint(double g, double inv_gm1, const dou
     // E* = id N
     const double Nb = eb * id;
     double dKb = Nb * EK;
-    const double EKb = Nb * dK;
+    const double EKb = star ? Nb * dK : eb;
     psb += Nb * S;
     Sb += Nb * ps;
     // mass = a S, a = m id, id = 1 / (S_K - S)
@@ -288,7 +291,7 @@ __device__ __forceinline__ void hllc_adjoint(double g, double inv_gm1, const dou
     // m = r (S_K - u)
     dKb += mb * r;
     const double h = EKb * r;
-    const double rb = EKb * 0.5 * q2 + mb * dK;
+    const double rb = EKb * 0.5 * q2 + (star ? mb * dK : ab);
     double ub = h * u - Nb * p - psb * m - dKb;
     const double pb = psb - Nb * u + EKb * inv_gm1;
     vb += h * v;
