@@ -117,18 +117,18 @@ __device__ __forceinline__ int interior_index(const Geo &g, int i, int j, int k)
     return (k * g.ny + j) * g.nx + i;
 }
 
+// What decides a branch -- primitives, slopes, face states, wave speeds and S* --
+// is computed by the forward step's functions or by its expressions with the
+// same products fused, so that near ties the adjoint takes the branch that the
+// step took.
+
 // Conserved -> primitive with floors.
 __device__ __forceinline__ void to_prim(const Geo &g, const double U[5], double W[5],
                                         double &inv_rho)
 {
-    double rho = U[0];
-    if (rho < g.rho_floor) rho = g.rho_floor;
-    inv_rho = fast_rcp(rho);
-    double u = U[1] * inv_rho, v = U[2] * inv_rho, w = U[3] * inv_rho;
-    double kin = 0.5 * (U[1] * u + U[2] * v + U[3] * w);
-    double p = (g.gamma - 1.0) * (U[4] - kin);
-    if (p < g.p_floor) p = g.p_floor;
-    W[0] = rho; W[1] = u; W[2] = v; W[3] = w; W[4] = p;
+    const Phys<double> ph{ g.gamma, g.gamma - 1.0, g.inv_gm1, g.rho_floor, g.p_floor };
+    int unused = 0;
+    prim_from_cons(U, W, inv_rho, ph, unused);
 }
 
 // Branch of a limited slope: 0 zero slope, 1 the a-branch, 2 the b-branch,
@@ -167,6 +167,7 @@ struct Fwd {
 
 __device__ __forceinline__ void speeds(double g, const double L[5], const double R[5], Fwd &f)
 {
+#pragma clang fp contract(off)
     const double gl = g * L[4], gr = g * R[4];
     f.yL = fast_rsqrt(gl * L[0]);
     f.yR = fast_rsqrt(gr * R[0]);
@@ -250,10 +251,16 @@ __device__ __forceinline__ void hllc_adjoint(double g, double inv_gm1, const dou
 {
     Fwd f;
     speeds(g, L, R, f);
-    const double dL = f.SL - L[1], dR = f.SR - R[1];
-    const double mL = L[0] * dL, mR = R[0] * dR;
-    const double iden = fast_rcp(mL - mR);
-    const double Sst = (R[4] - L[4] + mL * L[1] - mR * R[1]) * iden;
+    double dL, dR, mL, mR, iden, Sst;
+    {
+#pragma clang fp contract(off)
+        dL = f.SL - L[1];
+        dR = f.SR - R[1];
+        mL = L[0] * dL;
+        mR = R[0] * dR;
+        iden = fast_rcp(mL - mR);
+        Sst = fma(-mR, R[1], fma(mL, L[1], R[4] - L[4])) * iden;
+    }
     const bool supL = f.SL >= 0.0;
     const bool left = supL || Sst >= 0.0;
     const bool star = !supL && (left || f.SR > 0.0);
@@ -855,8 +862,8 @@ __device__ __forceinline__ void prim_adjoint(const Geo &g, const double U[5], co
     const double rho = rho_fl ? g.rho_floor : U[0];
     const double ir = fast_rcp(rho);
     const double vel[3] = { U[1] * ir, U[2] * ir, U[3] * ir };
-    const double kin = 0.5 * (U[1] * vel[0] + U[2] * vel[1] + U[3] * vel[2]);
-    const double p = (g.gamma - 1.0) * (U[4] - kin);
+    const double p = (g.gamma - 1.0) *
+                     fma(-0.5, fma(U[3], vel[2], fma(U[2], vel[1], U[1] * vel[0])), U[4]);
     const double pb = p < g.p_floor ? 0.0 : Wb[4];
     Ub[4] = (g.gamma - 1.0) * pb;
     const double kb = -(g.gamma - 1.0) * pb;
