@@ -57,7 +57,8 @@
  * device counters of its own -- the batched work queue and the CFL and MHD
  * speed accumulators -- so steps, batched steps and CFL reductions in flight
  * together on different streams do not interfere (beyond 64 streams the
- * counter slots are shared round robin). The scratch memory of the adjoint,
+ * counter slots are shared round robin: calls in flight together on such a
+ * slot spoil each other's results). The scratch memory of the adjoint,
  * PPM and MHD steps and the cached batch tables are one per context: two
  * calls of those kinds with different sizes or descriptors in flight
  * together on different streams race; give each stream its own gd_ctx.

@@ -48,6 +48,14 @@ struct Slot {
     unsigned long long *u64;   // [1] cfl max bits, [2] fused cfl max bits,
                                // [4..5] MHD speed maxima, [6..7] fused MHD maxima
     unsigned *u32;             // [0..1] work queue, [2] cfl done, [3] fused cfl done
+    bool shared;               // lent to a stream beyond the first NSLOT
+
+    // The counter of finished workgroups of a reduction, by which the last one
+    // stores dt. Only the slot's own stream counts: two grids in flight on one
+    // counter could both step over their own end, and leave it wrong for good. For
+    // the others a launch of its own stores dt, and what overlaps spoils no later
+    // call.
+    unsigned *done(int i) const { return shared ? nullptr : u32 + i; }
 };
 
 }  // namespace
@@ -197,6 +205,7 @@ bool capturing(hipStream_t s)
 Slot slot_for(gd_ctx *ctx, hipStream_t s)
 {
     int i = -1;
+    bool shared = false;
     for (size_t k = 0; k < ctx->slot_stream.size(); ++k)
         if (ctx->slot_stream[k] == s) { i = (int)k; break; }
     if (i < 0) {
@@ -205,9 +214,10 @@ Slot slot_for(gd_ctx *ctx, hipStream_t s)
             i = (int)ctx->slot_stream.size() - 1;
         } else {
             i = (int)(ctx->slot_shared++ % NSLOT);
+            shared = true;
         }
     }
-    return Slot{ ctx->d_u64 + SLOT_U64 * (i + 1), ctx->d_u32 + SLOT_U32 * i };
+    return Slot{ ctx->d_u64 + SLOT_U64 * (i + 1), ctx->d_u32 + SLOT_U32 * i, shared };
 }
 
 // Free a device buffer that is being replaced, unless a capture used it.
@@ -651,7 +661,7 @@ int step_impl(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int nz, int ng,
         // the PPM step of one patch: one fused launch, no scratch (its
         // stencils reach three cells past a tile, which two wraps of a
         // periodic coordinate cover only for extents of 2 and more)
-        gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.u32 + 3 };
+        gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.done(3) };
         int e = gd::launch_ppm_tile(opts->dtype, opts->limiter, opts->riemann, P, u_in, u_out, bflux,
                                     dt_dev, sc, ctx->d_u64, 2 * ctx->num_cus, co, s);
         if (e) return hip_fail(ctx, e, "PPM step launch");
@@ -667,12 +677,12 @@ int step_impl(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int nz, int ng,
             gd::PatchDesc Po = P;
             Po.periodic = 1; Po.ng = 0;
             e = gd::launch_cfl_single(opts->dtype, Po, u_out, sc, cfl, dt_next, slot.u64 + 2,
-                                      slot.u32 + 3, s);
+                                      slot.done(3), s);
             if (e) return hip_fail(ctx, e, "PPM step CFL launch");
         }
         return GD_OK;
     }
-    gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.u32 + 3 };
+    gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.done(3) };
     // the workgroups the chip holds at once: fewer leave CUs idle
     int shape = ctx->shape_single[opts->dtype], zlen = ctx->zlen_single[opts->dtype], fill = 0;
     if (shape == gd::TILE_16x16 && zlen == 32)
@@ -731,7 +741,7 @@ int step_batched_impl(gd_ctx *ctx, const gd_opts *opts, int npatch, const gd_pat
             return r;
         const BatchCache &c = ctx->ppm_batch;
         gd::Scalars sc{ gamma, opts->rho_floor, opts->p_floor };
-        gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.u32 + 3 };
+        gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.done(3) };
         int e = gd::launch_ppm_batched(opts->dtype, opts->limiter, opts->riemann, c.d_patches,
                                        c.d_items, c.nitems, u_in_base, u_out_base, bflux_base, dt_dev,
                                        sc, ctx->d_u64, slot.u32, ctx->num_cus, co, s);
@@ -745,7 +755,7 @@ int step_batched_impl(gd_ctx *ctx, const gd_opts *opts, int npatch, const gd_pat
     int per_cu = resident_blocks(ctx, opts->dtype, opts->limiter, opts->riemann, c.run_shape);
     int grid = std::min(c.nitems, per_cu * ctx->num_cus);
     gd::Scalars sc{ gamma, opts->rho_floor, opts->p_floor };
-    gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.u32 + 3 };
+    gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.done(3) };
     int e = gd::launch_step_batched(opts->dtype, opts->limiter, opts->riemann, c.run_shape, c.d_patches,
                                     c.d_items, c.nitems, u_in_base, u_out_base, bflux_base, dt_dev,
                                     sc, ctx->d_u64, slot.u32, std::max(grid, 1), co, s);
@@ -813,13 +823,13 @@ int cfl_dt(gd_ctx *ctx, const gd_opts *opts, int npatch, const gd_patch *patches
     if (npatch == 1) {
         gd::PatchDesc P = to_desc(patches[0], periodic);
         e = gd::launch_cfl_single(opts->dtype, P, u_base, sc, cfl, dt_dev, slot.u64 + 1,
-                                  slot.u32 + 2, s);
+                                  slot.done(2), s);
     } else {
         if ((r = build_cfl_tables(ctx, periodic, npatch, patches, s))) return r;
         const BatchCache &c = ctx->cfl;
         int grid = std::min(c.ncfl, 8 * ctx->num_cus);
         e = gd::launch_cfl(opts->dtype, c.d_patches, c.d_cfl_items, c.ncfl, u_base, sc, cfl, dt_dev,
-                           slot.u64 + 1, slot.u32 + 2, std::max(grid, 1), s);
+                           slot.u64 + 1, slot.done(2), std::max(grid, 1), s);
     }
     if (e) return hip_fail(ctx, e, "cfl_dt launch");
     return GD_OK;
@@ -1696,7 +1706,7 @@ int godunov_step_batched_streamed(gd_ctx *ctx, const gd_opts *opts, int npatch,
     const int per_cu = resident_blocks(ctx, opts->dtype, opts->limiter, opts->riemann, st.run_shape);
     gd::Scalars sc{ gamma, opts->rho_floor, opts->p_floor };
     const Slot cslot = slot_for(ctx, st.s_comp);
-    gd::CflOut co{ 0.0, nullptr, cslot.u64 + 2, cslot.u32 + 3 };
+    gd::CflOut co{ 0.0, nullptr, cslot.u64 + 2, cslot.done(3) };
     const char *hin = (const char *)u_in_host;
     char *hout = (char *)u_out_host, *hfl = (char *)bflux_host;
     for (size_t c = 0; c < st.chunks.size() && e == hipSuccess; ++c) {
