@@ -228,8 +228,10 @@ int cfl_dt(gd_ctx *ctx, const gd_opts *opts, int npatch, const gd_patch *patches
  * the pair 16x8 + 24x8 in one launch (each patch in the shape that covers its
  * x-y extent with fewer padded columns, 16x8 on a tie); z-ranges of 16, 32
  * and 64 planes (single patch) or of 8 planes, 16 planes and the whole patch
- * (batched). The batched candidate index is 3 * (position of the shape in
- * that list) + z policy, 0..17. */
+ * (batched). The candidate index is 3 * (position of the shape in that list) +
+ * the position of the z-range, 0..14 (batched 0..17). The library's own choice
+ * (see gd_get_config) is timed beside them, and kept instead of the fastest
+ * candidate where it is faster still. */
 int gd_autotune_step(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int nz, int ng,
                      const void *u_in, void *u_out, double gamma, double dx, double dt,
                      void *hip_stream, int *choice);
@@ -239,21 +241,19 @@ int gd_autotune_batched(gd_ctx *ctx, const gd_opts *opts, int npatch, const gd_p
 
 /* The configuration in use: tile shape index (0: 16x16, 1: 8x8, 2: 32x8,
  * 3: 16x8, 4: 24x8; batched also 5: the pair 16x8 + 24x8, the shape
- * chosen per patch)
+ * chosen per patch; -1, the initial state: shape and z-range by the library's
+ * own choice from the sizes of each call, the z value then being unused)
  * and z-range length (single patch) or z-range policy (batched: 0 = 8
  * planes, 1 = 16, 2 = whole patch) for dtype. */
 int gd_get_config(gd_ctx *ctx, int dtype, int *shape_single, int *zlen_single,
                   int *shape_batched, int *zpolicy_batched);
 
 /* Set the configuration explicitly (e.g. one stored from an earlier
- * autotuning run). shape_single in [0, 4], shape_batched in [0, 5];
+ * autotuning run). shape_single in [-1, 4], shape_batched in [-1, 5];
  * zlen_single in [1, 4096];
  * zpolicy_batched in {0, 1, 2}. zlen_single is an upper bound: a patch that
  * would give fewer workgroups than the device holds at once is cut into
- * shorter z-ranges (down to one plane). The initial values (16x16 tiles with
- * ranges of 32 planes for a single patch, 16x16 with policy 1 for a batch)
- * stand for the library's own choice by the sizes of each call, and setting
- * them returns to it. The choice never changes results: every
+ * shorter z-ranges (down to one plane). The choice never changes results: every
  * face flux and every update is evaluated by the same arithmetic whatever
  * the tiling, so outputs are bitwise identical across configurations. */
 int gd_set_config(gd_ctx *ctx, int dtype, int shape_single, int zlen_single, int shape_batched,

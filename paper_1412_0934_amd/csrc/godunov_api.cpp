@@ -104,11 +104,10 @@ struct gd_ctx {
     struct Choice { int key[6]; int shape, zlen; };
     Choice choice[16] = {};
     unsigned choice_next = 0;
-    // tuned configuration per dtype (index 0: FP64, 1: FP32); these initial
-    // values stand for the library's own choice by size
+    // configuration per dtype (index 0: FP64, 1: FP32)
     int zlen_single[2] = { 32, 32 };
-    int shape_single[2] = { gd::TILE_16x16, gd::TILE_16x16 };
-    int shape_batched[2] = { gd::TILE_16x16, gd::TILE_16x16 };
+    int shape_single[2] = { gd::TILE_AUTO, gd::TILE_AUTO };
+    int shape_batched[2] = { gd::TILE_AUTO, gd::TILE_AUTO };
     int zpolicy_batched[2] = { 1, 1 };
 };
 
@@ -447,7 +446,7 @@ int build_step_tables(gd_ctx *ctx, int dtype, int shape, int zpolicy, int npatch
                              { &c.cap_patches, &c.cap_items }, "batch tables")))
         return r;
     const int asked = shape;
-    if (shape == gd::TILE_16x16 && zpolicy == 1) choose_batched(ctx, dtype, npatch, patches, &shape, &zpolicy);
+    if (shape == gd::TILE_AUTO) choose_batched(ctx, dtype, npatch, patches, &shape, &zpolicy);
     std::vector<gd::PatchDesc> desc(npatch);
     std::vector<gd::WorkItem> items;
     std::vector<std::pair<int64_t, int>> order;     // (cells, patch): largest first
@@ -685,7 +684,7 @@ int step_impl(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int nz, int ng,
     gd::CflOut co{ cfl, dt_next, slot.u64 + 2, slot.done(3) };
     // the workgroups the chip holds at once: fewer leave CUs idle
     int shape = ctx->shape_single[opts->dtype], zlen = ctx->zlen_single[opts->dtype], fill = 0;
-    if (shape == gd::TILE_16x16 && zlen == 32)
+    if (shape == gd::TILE_AUTO)
         choose_single(ctx, opts->dtype, opts->limiter, opts->riemann, nx, ny, nz, &shape, &zlen);
     else
         fill = resident_blocks(ctx, opts->dtype, opts->limiter, opts->riemann, shape) * ctx->num_cus;
@@ -919,17 +918,18 @@ int gd_autotune_step(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int nz, i
     if (capturing((hipStream_t)hip_stream))
         return fail(ctx, GD_E_UNSUPPORTED, "the autotuner waits on the host and cannot be captured");
     const int dt_i = opts->dtype;
-    const int shapes[5] = { gd::TILE_16x16, gd::TILE_32x8, gd::TILE_8x8, gd::TILE_16x8,
-                            gd::TILE_24x8 };
+    // the last one, once, is the library's own choice
+    const int shapes[6] = { gd::TILE_16x16, gd::TILE_32x8, gd::TILE_8x8, gd::TILE_16x8,
+                            gd::TILE_24x8, gd::TILE_AUTO };
     const int zlens[3] = { 16, 32, 64 };
     const int keep_shape = ctx->shape_single[dt_i], keep_zlen = ctx->zlen_single[dt_i];
     // the first pass runs every candidate once (clocks and caches settle);
     // the next two time each candidate over 4 calls; a candidate's time is its
     // best pass, so a transient slowdown does not decide the choice
-    float best_ms[15];
+    float best_ms[16];
     for (float &m : best_ms) m = 1e30f;
     for (int round = 0; round < 3; ++round)
-        for (int c = 0; c < 15; ++c) {
+        for (int c = 0; c < 16; ++c) {
             ctx->shape_single[dt_i] = shapes[c / 3];
             ctx->zlen_single[dt_i] = zlens[c % 3];
             float ms = 0.f;
@@ -947,9 +947,14 @@ int gd_autotune_step(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int nz, i
     int best_i = 0;
     for (int c = 1; c < 15; ++c)
         if (best_ms[c] < best_ms[best_i]) best_i = c;
-    ctx->shape_single[dt_i] = shapes[best_i / 3];
-    ctx->zlen_single[dt_i] = zlens[best_i % 3];
     if (choice) *choice = best_i;
+    if (best_ms[15] < best_ms[best_i]) {
+        ctx->shape_single[dt_i] = gd::TILE_AUTO;
+        ctx->zlen_single[dt_i] = 32;
+    } else {
+        ctx->shape_single[dt_i] = shapes[best_i / 3];
+        ctx->zlen_single[dt_i] = zlens[best_i % 3];
+    }
     return GD_OK;
 }
 
@@ -964,15 +969,16 @@ int gd_autotune_batched(gd_ctx *ctx, const gd_opts *opts, int npatch, const gd_p
     if (capturing((hipStream_t)hip_stream))
         return fail(ctx, GD_E_UNSUPPORTED, "the autotuner waits on the host and cannot be captured");
     const int dt_i = opts->dtype;
-    const int shapes[6] = { gd::TILE_16x16, gd::TILE_32x8, gd::TILE_8x8, gd::TILE_16x8,
-                            gd::TILE_24x8, gd::TILE_PAIR_24x8 };
+    // the last one, once, is the library's own choice
+    const int shapes[7] = { gd::TILE_16x16, gd::TILE_32x8, gd::TILE_8x8, gd::TILE_16x8,
+                            gd::TILE_24x8, gd::TILE_PAIR_24x8, gd::TILE_AUTO };
     const int keep_shape = ctx->shape_batched[dt_i], keep_pol = ctx->zpolicy_batched[dt_i];
     // the same protocol as gd_autotune_step: a warm-up round, then the best
     // of two timed rounds per candidate
-    float best_ms[18];
+    float best_ms[19];
     for (float &m : best_ms) m = 1e30f;
     for (int round = 0; round < 3; ++round)
-        for (int c = 0; c < 18; ++c) {
+        for (int c = 0; c < 19; ++c) {
             ctx->shape_batched[dt_i] = shapes[c / 3];
             ctx->zpolicy_batched[dt_i] = c % 3;
             float ms = 0.f;
@@ -990,9 +996,14 @@ int gd_autotune_batched(gd_ctx *ctx, const gd_opts *opts, int npatch, const gd_p
     int best_i = 0;
     for (int c = 1; c < 18; ++c)
         if (best_ms[c] < best_ms[best_i]) best_i = c;
-    ctx->shape_batched[dt_i] = shapes[best_i / 3];
-    ctx->zpolicy_batched[dt_i] = best_i % 3;
     if (choice) *choice = best_i;
+    if (best_ms[18] < best_ms[best_i]) {
+        ctx->shape_batched[dt_i] = gd::TILE_AUTO;
+        ctx->zpolicy_batched[dt_i] = 1;
+    } else {
+        ctx->shape_batched[dt_i] = shapes[best_i / 3];
+        ctx->zpolicy_batched[dt_i] = best_i % 3;
+    }
     return GD_OK;
 }
 
@@ -1013,8 +1024,8 @@ int gd_set_config(gd_ctx *ctx, int dtype, int shape_single, int zlen_single, int
 {
     if (!ctx) return fail(ctx, GD_E_ARG, "ctx is NULL");
     if (dtype != GD_F64 && dtype != GD_F32) return fail(ctx, GD_E_ARG, "bad dtype %d", dtype);
-    if (shape_single < 0 || shape_single >= gd::NUM_TILE_SHAPES || shape_batched < 0 ||
-        shape_batched >= gd::NUM_BATCHED_SHAPES)
+    if (shape_single < gd::TILE_AUTO || shape_single >= gd::NUM_TILE_SHAPES ||
+        shape_batched < gd::TILE_AUTO || shape_batched >= gd::NUM_BATCHED_SHAPES)
         return fail(ctx, GD_E_ARG, "bad tile shape");
     if (zlen_single < 1 || zlen_single > 4096) return fail(ctx, GD_E_ARG, "bad z-range length");
     if (zpolicy_batched < 0 || zpolicy_batched > 2) return fail(ctx, GD_E_ARG, "bad z-range policy");
@@ -1540,7 +1551,7 @@ int build_stream_plan(gd_ctx *ctx, gd_stream_state &st, const gd_opts *opts, int
         st.chunk_bytes == chunk_bytes && (int)st.host.size() == npatch &&
         std::memcmp(st.host.data(), patches, npatch * sizeof(gd_patch)) == 0)
         return GD_OK;
-    if (shape == gd::TILE_16x16 && zp == 1) choose_batched(ctx, dtype, npatch, patches, &shape, &zp);
+    if (shape == gd::TILE_AUTO) choose_batched(ctx, dtype, npatch, patches, &shape, &zp);
     const size_t es = elem_size(opts);
     // patches in host-memory order of their inputs, so that packed batches
     // copy in one run per chunk and buffer

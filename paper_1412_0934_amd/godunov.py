@@ -494,12 +494,16 @@ def step_adjoint(u, lam_out, gamma, dx, dt, *, lam_bflux=None, ng=2, periodic=Fa
 TILE_SHAPES = ("16x16", "8x8", "32x8", "16x8", "24x8")
 # a batched launch may also pair 16x8 and 24x8 tiles, the shape chosen per patch
 BATCHED_SHAPES = TILE_SHAPES + ("16x8+24x8",)
+# the initial state: tile and z-range by the library's own choice from the sizes of
+# each call
+AUTO = "auto"
 
 
 def autotune_step(u, gamma, dx, dt, *, ng=2, periodic=False, limiter="minmod", riemann="hllc",
                   out=None, rho_floor=RHO_FLOOR, p_floor=P_FLOOR, stream=None) -> int:
     """Time the tile/z-range candidates of godunov_step on this problem and
-    keep the fastest in the context. Returns the candidate index."""
+    keep the fastest in the context, or the library's own choice where that is
+    faster still. Returns the index of the fastest candidate."""
     _check_tensor(u, "u")
     nx, ny, nz = interior_shape(u, ng, periodic)
     if out is None:
@@ -536,16 +540,28 @@ def get_config(dtype=torch.float64) -> dict:
     ctx = context()
     v = [ctypes.c_int() for _ in range(4)]
     ctx.check(ctx.lib.gd_get_config(ctx.handle, DTYPES[dtype], *[ctypes.byref(x) for x in v]))
-    return {"shape_single": TILE_SHAPES[v[0].value], "zlen_single": v[1].value,
-            "shape_batched": BATCHED_SHAPES[v[2].value], "zpolicy_batched": v[3].value}
+    single, zlen, batched, zpolicy = (x.value for x in v)
+    return {"shape_single": AUTO if single < 0 else TILE_SHAPES[single], "zlen_single": zlen,
+            "shape_batched": AUTO if batched < 0 else BATCHED_SHAPES[batched],
+            "zpolicy_batched": zpolicy}
 
 
-def set_config(dtype=torch.float64, *, shape_single="16x16", zlen_single=32,
-               shape_batched="16x16", zpolicy_batched=1) -> None:
+def set_config(dtype=torch.float64, *, shape_single=None, zlen_single=None, shape_batched=None,
+               zpolicy_batched=None) -> None:
+    """Set the tiles; what is left out returns to the library's own choice (AUTO), or
+    to 16x16 tiles where only the z-range is given, and to z-ranges of 32 planes and
+    policy 1 where only the shape is."""
+    def index(names, shape, z):
+        if shape is None:
+            shape = AUTO if z is None else "16x16"
+        return -1 if shape == AUTO else names.index(shape)
+
     ctx = context()
-    ctx.check(ctx.lib.gd_set_config(ctx.handle, DTYPES[dtype], TILE_SHAPES.index(shape_single),
-                                    int(zlen_single), BATCHED_SHAPES.index(shape_batched),
-                                    int(zpolicy_batched)))
+    ctx.check(ctx.lib.gd_set_config(ctx.handle, DTYPES[dtype],
+                                    index(TILE_SHAPES, shape_single, zlen_single),
+                                    int(32 if zlen_single is None else zlen_single),
+                                    index(BATCHED_SHAPES, shape_batched, zpolicy_batched),
+                                    int(1 if zpolicy_batched is None else zpolicy_batched)))
 
 
 class GodunovRollout(torch.autograd.Function):
