@@ -1235,13 +1235,19 @@ static void launch_mhd_tiles(const mhd::Par<T> &P, const mhd::Dynamic &D, const 
     const int ntx = (P.nx + TX - 1) / TX, nty = (P.ny + TY - 1) / TY;
     // z-ranges: as many as the chip holds workgroups, as long as that leaves
     // four planes to a range (a range recomputes the plane below it and the
-    // plane above it)
-    const int resident = 2 * num_cus;
-    int nseg = std::max(1, resident / std::max(1, ntx * nty));
+    // plane above it). Shorter ranges, down to one plane, where all of them find a
+    // CU of their own: there a step takes the time of one range, 6 to 7 us a plane
+    // (16^3 box with MC limiter: 43 us in ranges of four planes, 21 us in ranges
+    // of one; 32^3: 44 and 22 us; 64^3, whose ranges of one to three planes share
+    // CUs: 67 us in ranges of four, 63 to 85 in shorter ones).
+    const int resident = 2 * num_cus, ntiles = ntx * nty;
+    int nseg = std::max(1, resident / ntiles);
     nseg = std::min(nseg, (P.nz + 3) / 4);
-    const int zlen = (P.nz + nseg - 1) / nseg;
+    int zlen = (P.nz + nseg - 1) / nseg;
+    for (int z = std::min(zlen - 1, 3); z >= 1 && ntiles * ((P.nz + z - 1) / z) <= num_cus; --z)
+        zlen = z;
     nseg = (P.nz + zlen - 1) / zlen;
-    const int nitem = ntx * nty * nseg, per_xcd = (nitem + 7) / 8;
+    const int nitem = ntiles * nseg, per_xcd = (nitem + 7) / 8;
     hipLaunchKernelGGL((mhd::k_step<T, LIM, TX, TY>), dim3(8 * per_xcd), dim3(tile_threads(TX, TY)), 0,
                        st, P, D, sc.dt, sc.ch, (const T *)u_in, (T *)u_out, ntx, nty, zlen, nitem,
                        per_xcd, acc);
