@@ -274,15 +274,11 @@ __device__ __forceinline__ void euler_flux_rotated(const T W[5], const Phys<T> &
     else if constexpr (SQ & SQ_PPM) E = fma(W[4], ph.inv_gm1, T(0.5) * W[0] * q2);
     else E = W[4] * ph.inv_gm1 + T(0.5) * W[0] * q2;
     T mass = W[0] * W[1];
-    F[0] = mass; F[2] = mass * W[2]; F[3] = mass * W[3];
-    if constexpr (sizeof(T) == 8) {
-#pragma clang fp contract(off)
-        F[1] = fma(mass, W[1], W[4]);
-        F[4] = W[1] * (E + W[4]);
-    } else {
-        F[1] = mass * W[1] + W[4];
-        F[4] = W[1] * (E + W[4]);
-    }
+    F[0] = mass;
+    if constexpr (sizeof(T) == 8) F[1] = fma(mass, W[1], W[4]);
+    else F[1] = mass * W[1] + W[4];
+    F[2] = mass * W[2]; F[3] = mass * W[3];
+    F[4] = W[1] * (E + W[4]);
     U[0] = W[0]; U[1] = mass; U[2] = W[0] * W[2]; U[3] = W[0] * W[3]; U[4] = E;
 }
 
@@ -290,8 +286,6 @@ template <int SQ, typename T>
 __device__ __forceinline__ void hll_rotated(const T L[5], const T R[5], const Phys<T> &ph, T F[5])
 {
     T FL[5], FR[5], UL[5], UR[5];
-    euler_flux_rotated<SQ>(L, ph, FL, UL);
-    euler_flux_rotated<SQ>(R, ph, FR, UR);
     if constexpr (sizeof(T) == 8) {
 #pragma clang fp contract(off)
         const T gpL = ph.gamma * L[4], gpR = ph.gamma * R[4];
@@ -299,6 +293,8 @@ __device__ __forceinline__ void hll_rotated(const T L[5], const T R[5], const Ph
         const T cR = gpR * fast_rsqrt(gpR * R[0]);
         const T SL = fmin(L[1] - cL, R[1] - cR);
         const T SR = fmax(L[1] + cL, R[1] + cR);
+        euler_flux_rotated<SQ>(L, ph, FL, UL);
+        euler_flux_rotated<SQ>(R, ph, FR, UR);
         const T inv = fast_rcp(SR - SL);
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
@@ -312,6 +308,8 @@ __device__ __forceinline__ void hll_rotated(const T L[5], const T R[5], const Ph
         T cR = gpR * fast_rsqrt(gpR * R[0]);
         T SL = fmin(L[1] - cL, R[1] - cR);
         T SR = fmax(L[1] + cL, R[1] + cR);
+        euler_flux_rotated<SQ>(L, ph, FL, UL);
+        euler_flux_rotated<SQ>(R, ph, FR, UR);
         T inv = fast_rcp(SR - SL);
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
