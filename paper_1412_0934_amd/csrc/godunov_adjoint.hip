@@ -456,8 +456,8 @@ struct MarchSmem {
 // us): an adjoint step 0.56 -> 0.42 ms. Tile waves run unmasked (masked lane by
 // lane, 26 registers of the minmod and 64 of the MC variant spilled, now 8 and
 // 35): a 112 x 84 x 60 ghosted patch with MC limiter and flux adjoints
-// 0.267 -> 0.174 -> 0.155 ms, ten steps of a 128^3 box and their adjoint
-// 7.74 -> 5.63 -> 5.35 ms.
+// 0.267 -> 0.174 -> 0.157 ms, ten steps of a 128^3 box and their adjoint
+// 7.74 -> 5.63 -> 5.36 ms.
 template <int LIM, int RS>
 __global__ __launch_bounds__(Tile::NT) __attribute__((amdgpu_waves_per_eu(2))) void k_march(
     Geo g, const double *__restrict__ u, const double *__restrict__ lam_out,

@@ -349,14 +349,16 @@ int resident_blocks(gd_ctx *ctx, int dtype, int limiter, int riemann, int shape)
 // and the planes below and above the range that it predicts again); the chip
 // runs `resident` workgroups at once, a round that is not full takes between
 // 0.7 of a full one's time and all of it, and long ranges lose about 1% per 1.5
-// planes because neighbouring tiles drift apart and re-read their halos. The
-// cost formed from these picks, among 16x8 and 24x8 tiles and every z-range up
-// to 64 planes, a configuration within 4% of the best of twenty measured ones
-// on each of twenty-two boxes of 64^3 to 256^3 in both precisions but one (8%),
-// in the mean no slower than it (256^3 FP64: 0.64 ms, where 16x16 tiles with ranges of 32
-// take 0.88; 250 x 190 x 141 FP32 0.13 against 0.29; 128^3 FP64 0.077 against
-// 0.11). 8x8, 32x8 and 16x16 tiles were the best on none: their rings or their
-// LDS leave fewer columns on a CU.
+// planes because neighbouring tiles drift apart and re-read their halos. Among
+// 16x8 and 24x8 tiles and every even cut into ranges of up to 64 planes the lowest
+// cost wins; 8x8, 32x8 and 16x16 tiles leave fewer columns on a CU with their
+// rings and their LDS. Steps without a fused time step (minmod, HLLC) on twelve
+// boxes of 64 to 300 cells a side in both precisions, against all five shapes with
+// ranges of 8 to 64 planes: 0.4% slower than the best of them in the median, 10% at
+// most (128^3 FP32, 46.6 us against 42.3 us in 16x16 tiles; 250 x 190 x 141 FP64 7%),
+// and up to 17% faster, by ranges that the list does not have (100^3 FP64). 256^3
+// FP64 0.63 ms, where 16x16 tiles with ranges of 32 take 0.84; 250 x 190 x 141 FP32
+// 0.124 against 0.162; 128^3 FP64 0.077 against 0.103.
 void choose_single(gd_ctx *ctx, int dtype, int limiter, int riemann, int nx, int ny, int nz,
                    int *shape, int *zlen)
 {
@@ -404,7 +406,9 @@ void choose_single(gd_ctx *ctx, int dtype, int limiter, int riemann, int nx, int
 // 40% off (when the weights were fitted, 4096 cubic patches of 8 to 32 cells,
 // FP64: 1.11 ms in the pair with whole patches, 1.23 with ranges of 8; 500 uneven
 // patches of 6 to 40: 0.224 ms in 24x8 tiles with ranges of 8, 0.273 with whole
-// patches; with the march as it is now the chosen ones take 0.98 and 0.208).
+// patches; with the march as it is now the chosen ones take 0.97 and 0.208). The
+// batched kernels of every shape, limiter and solver run three waves per SIMD in
+// FP64 and four in FP32: three and four workgroups per CU of the 24x8 tiles weighed.
 void choose_batched(gd_ctx *ctx, int dtype, int npatch, const gd_patch *patches, int *shape,
                     int *zpolicy)
 {
@@ -857,7 +861,7 @@ int godunov_step_adjoint(gd_ctx *ctx, const gd_opts *opts, int nx, int ny, int n
     P.flux_off = lam_bflux ? 0 : -1;
     P.dx = dx; P.dt = dt;
     if (!gd::adjoint_fits_32bit(P))
-        return fail(ctx, GD_E_UNSUPPORTED, "the adjoint supports boxes of up to 2^31/15 extended cells");
+        return fail(ctx, GD_E_UNSUPPORTED, "the adjoint supports boxes of up to 2^31/20 extended cells");
     if (!ctx) return fail(ctx, GD_E_ARG, "ctx is NULL");
     if ((r = set_device(ctx))) return r;
     hipStream_t s = (hipStream_t)hip_stream;

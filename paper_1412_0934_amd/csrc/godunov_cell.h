@@ -46,9 +46,8 @@ __device__ __forceinline__ T floored(T x, T floor, int &hits)
 // Conserved -> primitive. In double precision products and sums are fused as
 // written, by fma() and not by the compiler's choice, here and in the functions
 // below: every kernel that inlines them gets the same bits. In single precision
-// the expressions are left to the compiler: the time step taken from a single
-// precision state is a double that callers compare to far below a single ulp,
-// so the state keeps the bits it always had.
+// the expressions are left to the compiler, which fuses them as it always did:
+// single-precision results are kept bit for bit.
 template <typename T>
 __device__ __forceinline__ void prim_from_cons(const T U[5], T W[5], T &inv_rho,
                                                const Phys<T> &ph, int &hits)

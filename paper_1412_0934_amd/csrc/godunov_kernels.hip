@@ -141,8 +141,8 @@ __attribute__((amdgpu_waves_per_eu(waves_per_eu<T>()))) void step_batched_kernel
 
 // A batch in two tile shapes: the same work queue, each item naming its
 // shape (A = 16x8 or B). Workgroups are sized for the larger tile; a thread
-// that owns no column of a smaller tile only shares the staging and the face
-// solves. The two shapes' LDS buffers overlap.
+// that owns no column of a smaller tile only passes the barriers. The two
+// shapes' LDS buffers overlap.
 template <typename T, int LIM, int RS, int TXB, int TYB>
 __global__ __launch_bounds__(pair_threads(TXB, TYB))
 __attribute__((amdgpu_waves_per_eu(waves_per_eu<T>()))) void step_batched_pair_kernel(

@@ -21,8 +21,7 @@
 // (one thread per cell: 7-point stencil, slopes, half step, six predicted face
 // states) and a flux sweep (z-marching column tiles: x and y faces through LDS,
 // z faces in registers, the update, and optionally the signal speeds of the
-// new state). Its time step is a double that callers compare to far below a
-// single ulp, so the state keeps the bits it always had.
+// new state): its results are kept bit for bit.
 // Every value is written by one thread and the reductions are maxima:
 // deterministic.
 #include "godunov_internal.h"

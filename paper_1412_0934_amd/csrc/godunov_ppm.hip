@@ -1237,9 +1237,7 @@ ppm_ring_traced(const double (&w)[5][NY][NX], int ly, int lx, const double W[5],
 }
 
 // The same step in double precision (the single-precision tile above keeps its
-// arithmetic bit for bit, which these forms would not: the time step of a
-// single-precision state is a double that callers compare far below a single
-// ulp). Every face is solved by the owner of the cell on its lower side, which
+// results bit for bit, which these forms would not). Every face is solved by the owner of the cell on its lower side, which
 // keeps that cell's upper states in registers, with two barriers a plane. Per
 // plane k:
 //   I   the x-y flux divergence of plane k-1; the parabolas of the 15
@@ -1257,7 +1255,7 @@ ppm_ring_traced(const double (&w)[5][NY][NX], int ly, int lx, const double W[5],
 // throughout the branch.
 // Bound by the registers of two waves per SIMD (256): vector instructions and
 // the latency that two workgroups per CU leave open. Against the four-barrier
-// tile with face states of both sides through LDS: 256^3 box 1.67 -> 1.09 ms
+// tile with face states of both sides through LDS: 256^3 box 1.67 -> 1.10 ms
 // (Hancock), 2.04 -> 1.33 ms (tracing); 1024 patches of 8^3 to 32^3 0.755 ->
 // 0.495 and 0.976 -> 0.641 ms. Of these, the parabola in deviations with the z
 // interface carried, and the owner's solve, gave 1.67 -> 1.17 ms; the scalar

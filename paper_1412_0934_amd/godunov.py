@@ -177,9 +177,9 @@ class Context:
 _contexts: dict = {}
 
 
-# A call on a small patch is bound by this module's own work (13 us a call for
-# an 8^3 patch whose kernel takes 6), so the helpers of every call are kept
-# cheap: no availability query once a context exists, the stream handle
+# A call on a small patch is bound by this module's own work (an 8^3 patch, whose
+# kernel takes 6 us: 12 us a call before, 8 with what follows), so the helpers of
+# every call are kept cheap: no availability query once a context exists, the stream handle
 # without a Stream object, pointers as plain integers, and the option records
 # (a function of their values alone, only read by the library) kept for reuse.
 
