@@ -43,10 +43,11 @@ GAMMA = 5.0 / 3.0
 HBM_PEAK_GBS = 8000.0
 METRIC = "Mcell-updates/s per Godunov step (plain vs batched), % HBM roofline; adjoint/fwd"
 # the step kernel's own code (its launch interface lives in godunov_internal.h,
-# whose other declarations do not change the kernel)
+# whose other declarations do not change the kernel), and the host layer, which
+# chooses the tile and z-range of the "auto" configuration
 KERNEL_SRC = [os.path.join(ROOT, "paper_1412_0934_amd", "csrc", f)
               for f in ("godunov_kernels.hip", "godunov_tile.h", "godunov_cell.h",
-                        "godunov_math.h")]
+                        "godunov_math.h", "godunov_api.cpp")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_kernel_periodic256_traffic.txt")
 VALU_FILE = os.path.join(ROOT, "profiles", "step_kernel_periodic256_valu.txt")
 
@@ -939,7 +940,8 @@ def main():
                     help="SHAPE/POLICY for the batched leg instead of autotuning, e.g. 24x8/2")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run a plain 1 GiB device copy (for counter scaling)")
-    ap.add_argument("--tile", choices=["16x16", "8x8", "32x8", "16x8", "24x8"], default=None,
+    ap.add_argument("--tile", choices=["auto", "16x16", "8x8", "32x8", "16x8", "24x8"],
+                    default=None,
                     help="fix the step kernel's tile shape instead of autotuning")
     ap.add_argument("--zlen", type=int, default=None, help="z-range length with --tile")
     args = ap.parse_args()
