@@ -263,7 +263,7 @@ __device__ __forceinline__ void hllc_adjoint(double g, double inv_gm1, const dou
     }
     const bool supL = f.SL >= 0.0;
     const bool left = supL || Sst >= 0.0;
-    const bool star = !supL && (left || f.SR > 0.0);
+    const bool star = !supL && (left || !(f.SR <= 0.0));
     const double r = left ? L[0] : R[0], u = left ? L[1] : R[1], v = left ? L[2] : R[2];
     const double w = left ? L[3] : R[3], p = left ? L[4] : R[4];
     const double SK = left ? f.SL : f.SR, m = star ? (left ? mL : mR) : 0.0;

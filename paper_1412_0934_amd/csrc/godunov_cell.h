@@ -187,7 +187,9 @@ __device__ __forceinline__ void hllc_rotated(const T L[5], const T R[5], const P
 
         const bool supL = SL >= T(0);
         const bool left = supL || Sst >= T(0);
-        const bool star = !supL && (left || SR > T(0));
+        // (wave speeds that are no numbers, of a gas without pressure, go into the
+        // star state, and from there into the flux)
+        const bool star = !supL && (left || !(SR <= T(0)));
         const T rK = left ? L[0] : R[0];
         const T uK = left ? L[1] : R[1];
         const T vK = left ? L[2] : R[2];

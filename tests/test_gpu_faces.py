@@ -69,6 +69,22 @@ def test_supersonic_face_has_the_upwind_flux(gd, lim, axis, cold):
             assert (np.abs(got - F[:, None]) <= 2 * np.spacing(np.abs(F))[:, None]).all(), (U, got, F)
 
 
+@pytest.mark.parametrize("lim", ["minmod", "ppm"])
+def test_gas_without_pressure_or_floor_is_no_number(gd, lim):
+    """With a zero floor a gas without pressure has no sound speed and no upwind
+    side: its fluxes are NaN, not those of whichever side comes last."""
+    n, ng = 3, 3
+    rho = np.full((n + 2 * ng,) * 3, 2.0)
+    u = np.stack([rho, 4.0 * rho, 0.0 * rho, 0.0 * rho, 8.0 * rho])
+    say("no pressure", lim)
+    _, b = gd.step(dev(u), G, 1 / 16, 1 / 1024, ng=ng, limiter=lim, rho_floor=0.0, p_floor=0.0)
+    assert np.isnan(sheet(host(b), 0, 0, n)).all()
+    lam = np.ones((5, n, n, n))
+    got = host(gd.step_adjoint(dev(u), dev(lam), G, 1 / 16, 1 / 1024, ng=ng, rho_floor=0.0,
+                               p_floor=0.0))
+    assert not np.isfinite(got[:, ng:-ng, ng:-ng, ng:-ng]).all()
+
+
 def rotate(v, axis, fields=((1, 2, 3),)):
     """Variables of data along x turned to an axis (cyclically)."""
     v = np.array(v)
