@@ -300,7 +300,8 @@ __device__ __forceinline__ void hll_rotated(const T L[5], const T R[5], const Ph
 #pragma unroll
         for (int q = 0; q < 5; ++q) {
             const T Fm = fma(SL * SR, UR[q] - UL[q], fma(SR, FL[q], -(SL * FR[q]))) * inv;
-            F[q] = SL >= T(0) ? FL[q] : (SR <= T(0) ? FR[q] : Fm);
+            const T up = SR <= T(0) ? FR[q] : Fm;
+            F[q] = SL >= T(0) ? FL[q] : up;
         }
     } else {
         const T g = ph.gamma;
