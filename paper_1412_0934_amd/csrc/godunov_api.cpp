@@ -395,45 +395,97 @@ void choose_single(gd_ctx *ctx, int dtype, int limiter, int riemann, int nx, int
     c.zlen = *zlen;
 }
 
-// Tile shape and z-range policy of a batch where the caller set none: 24x8
-// tiles alone or paired with 16x8 ones, and one of the three policies, by the
-// shortest schedule -- the planes of all items and one more each (its
-// prologue), a 16x8 item at 0.92 of a 24x8 one, the pair's larger workgroups at
-// 1.06, over the workgroups the chip holds at once, and a twentieth of the
-// longest item for the tail. Over thirteen batches in both precisions (64 to
-// 4096 patches of 4 to 40 cells, cubic and not) the choice is 2% from the best
-// of all shapes and policies in the mean, 8% at most; one fixed choice is up to
-// 40% off (when the weights were fitted, 4096 cubic patches of 8 to 32 cells,
-// FP64: 1.11 ms in the pair with whole patches, 1.23 with ranges of 8; 500 uneven
-// patches of 6 to 40: 0.224 ms in 24x8 tiles with ranges of 8, 0.273 with whole
-// patches; with the march as it is now the chosen ones take 0.97 and 0.208). The
-// batched kernels of every shape, limiter and solver run three waves per SIMD in
-// FP64 and four in FP32: three and four workgroups per CU of the 24x8 tiles weighed.
+// What the choice below needs of a batch in one tile shape: its items and their
+// longest z-range by policy, the planes of all tiles, and the same weighted with
+// the waves that a tile's item keeps busy (rows of a clipped tile and ring waves
+// without a column are skipped).
+struct BatchLoad {
+    double planes = 0.0, wave_planes = 0.0, items[3] = {};
+    int longest[3] = {};
+};
+
+BatchLoad batch_load(int shape, int npatch, const gd_patch *patches)
+{
+    BatchLoad l;
+    for (int i = 0; i < npatch; ++i) {
+        const gd_patch &p = patches[i];
+        const int ps = gd::patch_tile_shape(shape, p.nx, p.ny);
+        const int tx = gd::tile_tx(ps), ty = gd::tile_ty(ps);
+        const int fx = p.nx / tx, ex = p.nx - fx * tx, fy = p.ny / ty, ey = p.ny - fy * ty;
+        auto waves = [&](int ax, int ay) { return (ay * tx + 63) / 64 + (2 * (ax + ay) + 63) / 64; };
+        const double tiles = (double)(fx + (ex > 0)) * (fy + (ey > 0));
+        double w = (double)fx * fy * waves(tx, ty);
+        if (ex) w += (double)fy * waves(ex, ty);
+        if (ey) w += (double)fx * waves(tx, ey);
+        if (ex && ey) w += waves(ex, ey);
+        l.planes += tiles * p.nz;
+        l.wave_planes += w * p.nz;
+        for (int pol = 0; pol < 3; ++pol) {
+            const int z = batched_zlen(p.nz, pol);
+            l.items[pol] += tiles * ((p.nz + z - 1) / z);
+            l.longest[pol] = std::max(l.longest[pol], z);
+        }
+    }
+    return l;
+}
+
+// Tile shape and z-range policy of a batch where the caller set none: 16x16 or
+// 24x8 tiles, or the pair of 16x8 and 24x8, with one of the three policies, by the
+// shortest schedule. A workgroup's plane takes `latency` and `issue` for each wave
+// that its CU keeps busy; an item, its planes and `start` more, which grow with
+// the workgroups that start together; a CU holds `resident` workgroups (the same
+// for every limiter and solver: registers in FP64, five waves on four SIMDs at
+// 16x16). Items that all find a place take the time of the longest; more take
+// rounds if they are alike, and the mean rate and a share of the longest item if
+// not; long ranges drift apart and re-read their halos.
+// The constants are fitted to all eighteen configurations of 590 batches (1 to
+// 4096 patches of 4 to 100 cells a side, alike and mixed, cubic, uneven and flat,
+// 267 of them FP32). The choice is 3% slower than the best of the
+// eighteen in the mean and 10% or less in nine of ten; the planes over the
+// resident workgroups alone, without 16x16 tiles, were 6% and 20% (64 patches of
+// 32^3 FP32 0.090 ms, in 16x16 tiles 0.068; 256 of 16^3 FP64 0.084 against 0.067).
 void choose_batched(gd_ctx *ctx, int dtype, int npatch, const gd_patch *patches, int *shape,
                     int *zpolicy)
 {
-    const double resident = (dtype == GD_F32 ? 4.0 : 3.0) * ctx->num_cus;
+    struct Shape { int shape, resident; double weight; };
+    const bool f32 = dtype == GD_F32;
+    const Shape shapes[3] = { { gd::TILE_16x16, f32 ? 2 : 1, f32 ? 1.01 : 1.07 },
+                              { gd::TILE_24x8, f32 ? 4 : 3, 1.0 },
+                              { gd::TILE_PAIR_24x8, f32 ? 4 : 3, f32 ? 1.04 : 1.055 } };
+    const double latency = f32 ? 2.8 : 1.3, issue = f32 ? 0.12 : 0.25;      // us
+    const double start = f32 ? 1.8 : 3.0, crowd = f32 ? 1.2 : 0.6;          // planes
+    const double tail = f32 ? 0.65 : 0.8, drift = f32 ? 0.01 : 0.005;
+    *shape = gd::TILE_24x8;
+    *zpolicy = 1;
     double best = 1e300;
-    for (int sh : { gd::TILE_24x8, gd::TILE_PAIR_24x8 })
+    for (const Shape &sh : shapes) {
+        const BatchLoad l = batch_load(sh.shape, npatch, patches);
+        const double busy = l.wave_planes / l.planes;
+        auto plane = [&](double n) { return latency + issue * busy * n; };
         for (int pol = 0; pol < 3; ++pol) {
-            double planes = 0.0;
-            int longest = 0;
-            for (int i = 0; i < npatch; ++i) {
-                const gd_patch &p = patches[i];
-                const int ps = gd::patch_tile_shape(sh, p.nx, p.ny), z = batched_zlen(p.nz, pol);
-                const int tx = gd::tile_tx(ps), ty = gd::tile_ty(ps);
-                planes += (ps == gd::TILE_16x8 ? 0.92 : 1.0) * ((p.nx + tx - 1) / tx) *
-                          ((p.ny + ty - 1) / ty) * (p.nz + (p.nz + z - 1) / z);
-                longest = std::max(longest, z + 1);
+            const double n = l.items[pol] / ctx->num_cus;       // items per CU
+            const double extra = start + crowd * (std::min(std::max(n, 1.0), (double)sh.resident) - 1.0);
+            const double mean = l.planes / l.items[pol] + extra, longest = l.longest[pol] + extra;
+            double cost;
+            if (n <= sh.resident) {
+                cost = longest * plane(std::max(1.0, std::ceil(n)));
+            } else {
+                const double full = std::floor(n / sh.resident), part = n - full * sh.resident;
+                const double alike = std::pow(mean / longest, 6.0);
+                const double rounds = full * plane(sh.resident) + (part > 0.0 ? plane(std::ceil(part)) : 0.0);
+                const double mixed = n / sh.resident * plane(sh.resident) + tail * plane(1.0) * longest / mean;
+                cost = std::max(mean * (alike * rounds + (1.0 - alike) * mixed),
+                                0.9 * longest * plane(sh.resident)) *
+                       (1.0 + drift * std::max(0.0, l.planes / l.items[pol] - 20.0));
             }
-            const double cost =
-                (sh == gd::TILE_PAIR_24x8 ? 1.06 : 1.0) * planes / resident + 0.05 * longest;
+            cost *= sh.weight;
             if (cost < best) {
                 best = cost;
-                *shape = sh;
+                *shape = sh.shape;
                 *zpolicy = pol;
             }
         }
+    }
 }
 
 int build_step_tables(gd_ctx *ctx, int dtype, int shape, int zpolicy, int npatch,

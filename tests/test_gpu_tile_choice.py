@@ -127,3 +127,34 @@ def test_batches(gd, dtype):
         gd.set_config(dt_)
     for a, b in zip(own, fixed):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,npatch,n", [("float32", 64, 32), ("float64", 256, 16)])
+def test_batches_of_patches_that_fill_16x16_tiles(gd, dtype, npatch, n):
+    """Alike patches whose 16x16 tiles find one place each on the chip: those are
+    chosen (by 20 to 25% the fastest), and give the bits of the tile pair."""
+    import torch
+    dt_ = getattr(torch, dtype)
+    states = [inputs.random_patch(n, n, n, seed=q, generic=True) for q in range(4)]
+    batch = inputs.pack_batch([states[p % 4] for p in range(npatch)], 2, 1 / 64, order_seed=2)
+    table = gd.patch_table(batch.dims, 2, batch.u_in_off, batch.u_out_off, batch.flux_off,
+                           batch.dx, 1e-3)
+    u_in = torch.from_numpy(batch.u_in).cuda().to(dt_)
+
+    def step():
+        out = torch.zeros(batch.u_out_size, dtype=dt_, device="cuda")
+        flux = torch.zeros(batch.flux_size, dtype=dt_, device="cuda")
+        gd.step_batched(u_in, table, G, out=out, bflux=flux)
+        return out, flux
+
+    say("alike patches", dtype, npatch, n)
+    own, ran = traced(step)
+    assert len(ran) == 1 and ", 16, 16>" in ran[0]
+    try:
+        gd.set_config(dt_, shape_batched="16x8+24x8", zpolicy_batched=2)
+        pair, ran = traced(step)
+        assert len(ran) == 1 and "pair" in ran[0]
+    finally:
+        gd.set_config(dt_)
+    for a, b in zip(own, pair):
+        assert torch.equal(a, b)
