@@ -223,8 +223,8 @@ enum { ROLE_NONE = -1, ROLE_INT = 0, ROLE_BOTTOM = 1, ROLE_TOP = 2, ROLE_LEFT = 
 // with loads a plane ahead: 4096 patches of 8^3 to 32^3 FP64 2.03 -> 1.10 -> 0.97
 // ms (the first with its tile choice), 250 x 190 x 141 FP32 0.336 -> 0.176 ->
 // 0.171 ms, 256^3 FP64 box 1.04 -> 0.640 -> 0.648 ms; two-level step of a 128^3
-// box and 1024 small patches 0.761 -> 0.592 -> 0.551 ms (the last with the seams'
-// paired accesses).
+// box and 1024 small patches 0.761 -> 0.592 -> 0.532 ms (the last with the seams'
+// paired accesses and the tiles that choose_batched now takes for its batch).
 // STREAM_OUT: write the new state with streaming (non-temporal) stores. The
 // batched launches do: there the outputs of many small patches would
 // otherwise evict from the L2 the inputs that neighbouring tiles still read
